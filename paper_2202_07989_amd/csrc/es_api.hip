@@ -128,11 +128,17 @@ void build_params(const es_grid* g, Phys& ph, Geo& geo)
     for (int m = 0; m < 3; m++) ph.alpha[m] = A[g->w - 1][m];
     for (int m = 0; m < 3; m++) ph.chi[m] = g->chi[m];
     ph.eps = g->weno_eps;
+    ph.wc[0] = g->chi[1] / 6.0;
+    ph.wc[1] = g->chi[1] / 3.0;
+    ph.wc[2] = 11.0 / 60.0 - ph.wc[0];
+    ph.wc[3] = 0.4 - ph.wc[1];
     ph.stol64 = g->sign_tol;
     ph.stol32 = g->sign_tol32;
     ph.r21 = g->nspec == 2 ? ph.Rg[1] / ph.Rg[0] : 1.0;
     ph.sr21 = sqrt(ph.r21);
     ph.isr21 = 1.0 / ph.sr21;
+    ph.isa = 1.0 / (2.0 * ph.gam[0] * ph.Rg[0]);
+    ph.ise = 1.0 / ph.cvgam[0];
 
     geo.dim = g->dim;
     geo.ng = g->ng;

@@ -34,7 +34,7 @@ k_stage2d_batched(Phys ph, const Geo* __restrict__ geos, const int4* __restrict_
     constexpr int NW = NT / 64;
     static_assert((TX + 1) * TY <= NT && (TY + 1) * TX <= NT && 3 * TX <= 64 && 3 * TY <= 64 && NT % 64 == 0,
                   "region does not fit");
-    __shared__ NodeTile<N, D, NN> S;
+    __shared__ NodeTile<N, D, NN, R> S;
     __shared__ R Xbuf[NC * NX];
 
     const int t = threadIdx.x;
@@ -61,7 +61,7 @@ k_stage2d_batched(Phys ph, const Geo* __restrict__ geos, const int4* __restrict_
             if (!(cx || cy)) continue;                       // corners are never read
             const int gx = ox + lx - 3, gy = oy + ly - 3;
             if (gx >= nx + 3 || gy >= ny + 3) continue;      // beyond a ragged last region
-            bad |= node_state<N, D, NN>(ph, S, q, JUs, Js, P, gidx(gx, gy));
+            bad |= node_state<N, D, NN, R>(ph, S, q, JUs, Js, P, gidx(gx, gy));
         }
 
         // node owned by this thread in the node phases

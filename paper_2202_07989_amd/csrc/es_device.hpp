@@ -19,8 +19,10 @@ struct Phys {
     double pinf_tot;
     double alpha[3];          // alpha_{w,m}
     double chi[3], eps;       // MR-WENO linear weights and epsilon
+    double wc[4];             // chi_2/6, chi_2/3, 11/60 - chi_2/6, 2/5 - chi_2/3 (mr5_jump64)
     double r21;               // R_2 / R_1 (N = 2)
     double sr21, isr21;       // sqrt(R_2 / R_1) and its reciprocal
+    double isa, ise;          // N = 1: 1/(2 Gamma R) and 1/(c_v Gamma), the scalings of R's columns
     double stol64, stol32;    // zero tolerances of the sign matrix (FP64, FP32 arithmetic)
 };
 
@@ -69,21 +71,38 @@ __device__ __forceinline__ float rcp(float x)
     return fmaf(r, fmaf(-x, r, 1.0f), r);
 }
 
-// square root of a finite, positive, normal x: the hardware 1/sqrt estimate
-// y, then s = x y, h = y/2 refined by one Goldschmidt step and two
-// corrections s += (x - s^2) h, within about an ulp; IEEE sqrt adds the
-// scaling of tiny operands and the selects for 0 and infinity
-__device__ __forceinline__ double sqrt_pos(double x)
+// The same for the FP64 flux arithmetic, in one third-order step: with
+// e = 1 - x r the reciprocal is r (1 + e + e^2) up to e^3, and the estimate's
+// e is below 2^-22 (the instruction's stated accuracy), so the dropped term is
+// below 2^-66.  One instruction less than the two Newton steps (the estimate
+// itself issues for four), the same half-ulp last rounding.  The mixed form
+// keeps rcp(): its FP32 results follow the bits of its FP64 inputs.
+__device__ __forceinline__ double rcp64(double x)
+{
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
+}
+
+// 1/sqrt and sqrt of a finite, positive, normal x in the same way: with
+// e = 1 - x y^2 the inverse root is y (1 + e/2 + 3 e^2/8) up to e^3 (below
+// 2^-66); the root takes one Goldschmidt step (relative error below 2^-44)
+// and one correction s += (x - s^2) h
+__device__ __forceinline__ double rsqrt64(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+__device__ __forceinline__ double sqrt64(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
     double sq = x * y, h = 0.5 * y;
     const double r = fma(-h, sq, 0.5);
     sq = fma(sq, r, sq);
     h = fma(h, r, h);
-    double d = fma(-sq, sq, x);
-    sq = fma(d, h, sq);
-    d = fma(-sq, sq, x);
-    return fma(d, h, sq);
+    return fma(fma(-sq, sq, x), h, sq);
 }
 
 __device__ __forceinline__ float sqrt_pos(float x) { return sqrtf(x); }
@@ -248,10 +267,6 @@ __device__ __forceinline__ void js5_diff(R D0, R D1, R D2, R D3, R eps, R& num, 
     R e1 = eps + (R(13.0 / 12.0) * (s1 * s1) + R(0.25) * (t1 * t1));
     R e2 = eps + (R(13.0 / 12.0) * (s2 * s2) + R(0.25) * (t2 * t2));
     e0 *= e0; e1 *= e1; e2 *= e2;
-    if constexpr (sizeof(R) == 4) {   // keep the products in float range
-        const R em = rcp(fmax(fmax(e0, e1), e2));
-        e0 *= em; e1 *= em; e2 *= em;
-    }
     const R p0 = R(0.1) * (e1 * e2), p1 = R(0.6) * (e0 * e2), p2 = R(0.3) * (e0 * e1);
     const R c0 = (R(5) * D1 - R(2) * D0) * R(1.0 / 6.0);
     const R c1 = (D1 + R(2) * D2) * R(1.0 / 6.0);
@@ -265,24 +280,63 @@ __device__ __forceinline__ void js5_diff(R D0, R D1, R D2, R D3, R eps, R& num, 
 // (W_0..W_4) at the right face of node i, wp that of the mirrored
 // (W_5..W_1) at the left face of node i+1.  With D_k = W_{k+1} - W_k,
 // wm = W_2 + Nm/Dm from (D_0, D_1, D_2, D_3) and wp = W_3 + Np/Dp from
-// (-D_4, -D_3, -D_2, -D_1), so wp - wm = D_2 + Np/Dp - Nm/Dm; FP64 takes the
-// two quotients over one denominator.  jump_out = W_3 - W_2 = D_2.
-// JS selects the classical reconstruction instead of MR.
-template <typename R, bool JS = false>
+// (-D_4, -D_3, -D_2, -D_1), so wp - wm = D_2 + Np/Dp - Nm/Dm.
+// jump_out = W_3 - W_2 = D_2.
+template <typename R>
 __device__ __forceinline__ R mr5_jump(R q0, R q1, R q2, R q3, R q4, R q5, const Weno<R>& W, R& jump_out)
 {
     const R D0 = q1 - q0, D1 = q2 - q1, D2 = q3 - q2, D3 = q4 - q3, D4 = q5 - q4;
     R nm, dm, np, dp;
-    if constexpr (JS) {
-        js5_diff<R>(D0, D1, D2, D3, W.eps, nm, dm);
-        js5_diff<R>(-D4, -D3, -D2, -D1, W.eps, np, dp);
-    } else {
-        mr5_diff<R>(D0, D1, D2, D3, W, nm, dm);
-        mr5_diff<R>(-D4, -D3, -D2, -D1, W, np, dp);
-    }
+    mr5_diff<R>(D0, D1, D2, D3, W, nm, dm);
+    mr5_diff<R>(-D4, -D3, -D2, -D1, W, np, dp);
     jump_out = D2;
-    if constexpr (sizeof(R) == 8) return D2 + (np * dm - nm * dp) * rcp(dp * dm);
-    else return D2 + (np * rcp(dp) - nm * rcp(dm));
+    return D2 + (np * rcp(dp) - nm * rcp(dm));
+}
+
+// The jump in FP64 (JS: by the classical reconstruction): every multiply-add
+// one instruction, the squares of D_1..D_3 shared by the two sides, the linear
+// weight chi_2 folded into the reconstruction coefficients on the host (wc),
+// tau / 4 taken inside the weights' multiply-adds and the two quotients taken
+// over one denominator: 48 instead of 60 instructions a side.
+__device__ __forceinline__ void mr5_side64(double D0, double D1, double D2, double D3, double q1, double q2,
+                                           const Phys& ph, double& num, double& den)
+{
+    const double S03 = D0 + D3, S12 = D1 + D2, A03 = D0 - D3, A21 = D2 - D1;
+    const double b1 = fmin(q1, q2);
+    const double b2 = fma((13.0 / 12.0) * A21, A21, 0.25 * (S12 * S12));
+    const double u1 = fma(7.0, S12, -S03), u2 = fma(163.0, A21, 11.0 * A03);
+    const double u3 = S03 - S12, u4 = fma(3.0, A21, A03);
+    double b3 = ((1.0 / 144.0) * u1) * u1;
+    b3 = fma((13.0 / 3.0 / 67600.0) * u2, u2, b3);
+    b3 = fma((781.0 / 20.0 / 144.0) * u3, u3, b3);
+    b3 = fma((1421461.0 / 2275.0 / 576.0) * u4, u4, b3);
+    const double t = fabs(b3 - b1) + fabs(b3 - b2), tq = 0.25 * t;
+    const double c2 = fma(ph.wc[0], D1, ph.wc[1] * D2);
+    const double c3 = fma(ph.wc[2], D1, fma(ph.wc[3], D2, fma(-1.0 / 30.0, D0, -0.05 * D3)));
+    const double d1 = ph.eps + b1, d2 = ph.eps + b2, d3 = ph.eps + b3;
+    const double e1 = fma(tq, t, d1) * (d2 * d3);
+    const double e2 = fma(tq, t, d2) * (d1 * d3);
+    const double e3 = fma(tq, t, d3) * (d1 * d2);
+    num = fma(e2, c2, e3 * c3);
+    den = fma(ph.chi[0], e1, fma(ph.chi[1], e2, ph.chi[2] * e3));
+}
+
+template <bool JS>
+__device__ __forceinline__ double weno_jump64(const double (&w)[6], const Phys& ph, double& jump)
+{
+    const double D0 = w[1] - w[0], D1 = w[2] - w[1], D2 = w[3] - w[2], D3 = w[4] - w[3], D4 = w[5] - w[4];
+    double nm, dm, np, dp;
+    jump = D2;
+    if constexpr (JS) {
+        js5_diff<double>(D0, D1, D2, D3, ph.eps, nm, dm);
+        js5_diff<double>(D4, D3, D2, D1, ph.eps, np, dp);
+    } else {
+        const double q1 = D1 * D1, q2 = D2 * D2, q3 = D3 * D3;
+        mr5_side64(D0, D1, D2, D3, q1, q2, ph, nm, dm);
+        mr5_side64(D4, D3, D2, D1, q3, q2, ph, np, dp);
+    }
+    // both sides are odd in the differences: the mirrored stencil's are -D_4..-D_1
+    return fma(-fma(np, dm, nm * dp), rcp64(dp * dm), D2);
 }
 
 // --------------------------------------------------------------------------

@@ -9,7 +9,11 @@ namespace es {
 
 enum { MODE_WRITE = 0, MODE_ADD = 1, MODE_RK = 2 };
 
-template <int N, int D, int NN>
+// R is the precision of the interface arithmetic.  The FP64 tile keeps the
+// species entropy variables y_l (formed once per node, read by up to 18
+// interface stencils of it); the FP32 one forms them per interface from the
+// FP64 node logs.
+template <int N, int D, int NN, typename R = double>
 struct NodeTile {
     double rho[N][NN];     // species densities
     double lrho[N][NN];    // their logs
@@ -23,9 +27,20 @@ struct NodeTile {
                            // interface average is then one sum; halving is exact)
 };
 
-// mixture Gamma, gas constant and pressure of tile node q (N = 2)
 template <int N, int D, int NN>
-__device__ __forceinline__ void mixture(const Phys& ph, const NodeTile<N, D, NN>& S, int q,
+struct NodeTile<N, D, NN, double> {
+    double rho[N][NN];
+    double lrho[N][NN];
+    double v[D][NN];
+    double b[NN];
+    double lb[NN];
+    double y[N][NN];       // y_l = c_vl ln beta + R_l ln rho_l + c_vl Gamma_l - beta |v|^2 / 2
+    double m[D + 1][NN];
+};
+
+// mixture Gamma, gas constant and pressure of tile node q (N = 2)
+template <int N, int D, int NN, typename R>
+__device__ __forceinline__ void mixture(const Phys& ph, const NodeTile<N, D, NN, R>& S, int q,
                                         double& gm, double& rm, double& p)
 {
     const double r0 = S.rho[0][q], r1 = S.rho[1][q];
@@ -47,7 +62,7 @@ __device__ __forceinline__ void mixture(const Phys& ph, const NodeTile<N, D, NN>
 // p_inf are both ~p_inf, so neither difference may be left to FP32.
 // (M: the halved metrics of the direction, indexed like the tile)
 template <int N, int D, int NN, typename R>
-__device__ __forceinline__ void ec_pair(const Phys& ph, const NodeTile<N, D, NN>& S, const double (*M)[NN],
+__device__ __forceinline__ void ec_pair(const Phys& ph, const NodeTile<N, D, NN, R>& S, const double (*M)[NN],
                                         int ia, int ib, R* F)
 {
     constexpr int NC = N + D + 1;
@@ -88,12 +103,15 @@ __device__ __forceinline__ void ec_pair(const Phys& ph, const NodeTile<N, D, NN>
     F[NC - 1] = eng + vv * Mt + R(Pi) * vdn + R(ph.pinf_tot) * nt;
 }
 
+// (ec_pair and dissipation serve the FP32 interface arithmetic of the mixed
+// form; the FP64 sweeps take pair_means, ec_flux64 and dissipation64 below)
+//
 // ES dissipation 1/2 s T^T R Y [[W]]^WENO at the interface between tile
 // nodes iL (= i) and iR (= i+1); st[t] are the tile indices of nodes
 // i-2..i+3.  Interface metrics, averages and R follow Section 3.4.  MG: the
 // acoustic and species fields in one group or two.
-template <int N, int D, int NN, int RC, typename R, int MG>
-__device__ __forceinline__ void dissipation(const Phys& ph, const NodeTile<N, D, NN>& S, const double (*M)[NN],
+template <int N, int D, int NN, typename R, int MG>
+__device__ __forceinline__ void dissipation(const Phys& ph, const NodeTile<N, D, NN, R>& S, const double (*M)[NN],
                                             const int st[6], const Weno<R>& Wc, R* Dout)
 {
     constexpr int NC = N + D + 1;
@@ -138,8 +156,8 @@ __device__ __forceinline__ void dissipation(const Phys& ph, const NodeTile<N, D,
     } else {
         R rl[2];
         double gmL, gmR, rmL, rmR, pL, pR;
-        mixture<N, D, NN>(ph, S, iL, gmL, rmL, pL);
-        mixture<N, D, NN>(ph, S, iR, gmR, rmR, pR);
+        mixture<N, D, NN, R>(ph, S, iL, gmL, rmL, pL);
+        mixture<N, D, NN, R>(ph, S, iR, gmR, rmR, pR);
         const R Rm[2] = {R(rmL), R(rmR)};
         const R Gm[2] = {R(gmL), R(gmR)};
 #pragma unroll
@@ -191,7 +209,7 @@ __device__ __forceinline__ void dissipation(const Phys& ph, const NodeTile<N, D,
     // isentropic flow the entropy field's do; those count as sign 0.
     auto weno_field = [&](const R (&w)[6], R mag) -> R {
         R jump;
-        const R jw = mr5_jump<R, RC == 1>(w[0], w[1], w[2], w[3], w[4], w[5], Wc, jump);
+        const R jw = mr5_jump<R>(w[0], w[1], w[2], w[3], w[4], w[5], Wc, jump);
         const bool y = (jw * jump > R(0)) && (fabs(jump) > Wc.zero_tol * mag);
         return y ? jw : R(0);
     };
@@ -317,6 +335,530 @@ __device__ __forceinline__ void dissipation(const Phys& ph, const NodeTile<N, D,
     Dout[NC - 1] = hs * RZ[NC - 1];
 }
 
+// ---------------------------------------------------------------------------
+// FP64 interface arithmetic.  The sweeps issue FP64 instructions for most of
+// their time, so the formulas of ec_pair and dissipation above are arranged
+// here for the fewest of them (the frame, the sign matrix and its tolerance,
+// the reconstruction and the fluxes are the same):
+//   - every multiply-add is one instruction;
+//   - the reciprocals of a pair are taken two at a time over their product;
+//   - F(l, l+1) and the dissipation share their logarithmic means;
+//   - W_m of a stencil node is a dot product with the scaled column of R,
+//     folded into interface constants: with t = vbar.v,
+//       acoustic  c0 y_0 + c1 y_1 + beta (cv.v - cH) -+ beta (cn.v - ck),
+//       species   d1 y_0 + d2 y_1 + beta ((d1 + d2) t - ce),
+//       tangential  beta (ct.v - ck);
+//   - the two middle nodes' W decide whether the wave needs the other four
+//     and the reconstruction, and before the frame is formed the entropy
+//     variables of the two nodes decide whether the wave has any dissipation.
+// Each node's W goes through one instruction sequence, so identical states
+// give identical W.
+// ---------------------------------------------------------------------------
+
+// makes the compiler form x here: it otherwise sinks sums to their last use
+// and holds every operand of them in registers until then
+__device__ __forceinline__ void form_here(double& x) { asm volatile("" : "+v"(x)); }
+
+// logarithmic means of a node pair: of the species densities and the inverse
+// of that of beta
+template <int N>
+struct PairMeans {
+    double rho[N], ib;
+};
+
+// x / atanh(x) and atanh(x) / x from u = x^2 < 1e-4 (the series of logmean
+// and inv_logmean)
+__device__ __forceinline__ double lm_series(double u)
+{
+    return fma(-u, fma(u, fma(u, 44.0 / 945.0, 4.0 / 45.0), 1.0 / 3.0), 1.0);
+}
+__device__ __forceinline__ double ilm_series(double u)
+{
+    return fma(u, fma(u, fma(u, 1.0 / 7.0, 1.0 / 5.0), 1.0 / 3.0), 1.0);
+}
+
+template <int N, int D, int NN>
+__device__ __forceinline__ void pair_means(const NodeTile<N, D, NN, double>& S, int ia, int ib,
+                                           PairMeans<N>& pm, double& isb)
+{
+    double d[N], s[N];
+    bool ser[N];
+    bool any = false;
+#pragma unroll
+    for (int l = 0; l < N; l++) {
+        const double ra = S.rho[l][ia], rb = S.rho[l][ib];
+        d[l] = ra - rb;
+        s[l] = ra + rb;
+        ser[l] = d[l] * d[l] < 1.0e-4 * (s[l] * s[l]);
+        any = any || !ser[l];
+    }
+    const double ba = S.b[ia], bb = S.b[ib];
+    const double db = ba - bb, sb = ba + bb;
+    const bool serb = db * db < 1.0e-4 * (sb * sb);
+    any = any || !serb;
+    if (!__any(any)) {   // the whole wave on the series
+        isb = rcp64(sb);
+        const double f = db * isb;
+        pm.ib = 2.0 * isb * ilm_series(f * f);
+        double is[N];
+        if constexpr (N == 2) {
+            const double r = rcp64(s[0] * s[1]);
+            is[0] = r * s[1];
+            is[1] = r * s[0];
+        } else {
+            is[0] = rcp64(s[0]);
+        }
+#pragma unroll
+        for (int l = 0; l < N; l++) {
+            const double x = d[l] * is[l];
+            pm.rho[l] = 0.5 * s[l] * lm_series(x * x);
+        }
+    } else {             // lane by lane, the divisor selected
+        const double e = serb ? 1.0 : db;
+        const double rb = rcp64(sb * e);
+        isb = rb * e;
+        const double f = db * isb;
+        const double ibs = 2.0 * isb * ilm_series(f * f);
+        const double ibl = (S.lb[ia] - S.lb[ib]) * (rb * sb);
+        pm.ib = serb ? ibs : ibl;
+        double q[N], iq[N];
+#pragma unroll
+        for (int l = 0; l < N; l++) q[l] = ser[l] ? s[l] : S.lrho[l][ia] - S.lrho[l][ib];
+        if constexpr (N == 2) {
+            const double r = rcp64(q[0] * q[1]);
+            iq[0] = r * q[1];
+            iq[1] = r * q[0];
+        } else {
+            iq[0] = rcp64(q[0]);
+        }
+#pragma unroll
+        for (int l = 0; l < N; l++) {
+            const double x = d[l] * iq[l];
+            const double xs = 0.5 * s[l] * lm_series(x * x);
+            pm.rho[l] = ser[l] ? xs : x;
+        }
+    }
+}
+
+// logarithmic mean of two positive values without node logs: off the series
+// ln(a/b) is taken of the quotient (one logarithm where a lane needs it)
+__device__ __forceinline__ double logmean64(double a, double b)
+{
+    const double d = a - b, s = a + b;
+    const double f = d * rcp64(s), u = f * f;
+    double r = 0.5 * s * lm_series(u);
+    if (!(d * d < 1.0e-4 * (s * s))) r = d * rcp64(ln_pos(a * rcp64(b)));
+    return r;
+}
+
+// the two-point flux of ec_pair from the pair's means; vs = v_a + v_b and
+// n, nt are returned for the dissipation
+template <int N, int D, int NN>
+__device__ __forceinline__ void ec_flux64(const Phys& ph, const NodeTile<N, D, NN, double>& S,
+                                          const double (*M)[NN], int ia, int ib, const PairMeans<N>& pm,
+                                          double isb, double* F)
+{
+    constexpr int NC = N + D + 1;
+    const double nt = M[0][ia] + M[0][ib];
+    double n[D], vs[D];
+    double w = 0.0, s2 = 0.0, vv = 0.0;   // 2 {v}.n, sum of squares, 4 |{v}|^2
+#pragma unroll
+    for (int j = 0; j < D; j++) {
+        n[j] = M[1 + j][ia] + M[1 + j][ib];
+        const double va = S.v[j][ia], vb = S.v[j][ib];
+        vs[j] = va + vb;
+        s2 = fma(va, va, fma(vb, vb, s2));
+        w = fma(vs[j], n[j], w);
+        vv = fma(vs[j], vs[j], vv);
+    }
+    const double vn = fma(0.5, w, nt);
+    double Rr = ph.Rg[0] * (S.rho[0][ia] + S.rho[0][ib]);
+    if constexpr (N == 2) Rr = fma(ph.Rg[1], S.rho[1][ia] + S.rho[1][ib], Rr);
+    const double Pi = Rr * isb;
+    const double phat = Pi - ph.pinf_tot;
+    double Mt = 0.0, ce = 0.0;
+#pragma unroll
+    for (int l = 0; l < N; l++) {
+        F[l] = pm.rho[l] * vn;
+        Mt += F[l];
+        ce = l == 0 ? ph.cv[0] * F[0] : fma(ph.cv[l], F[l], ce);
+    }
+    const double hM = 0.5 * Mt;
+#pragma unroll
+    for (int j = 0; j < D; j++) F[N + j] = fma(vs[j], hM, phat * n[j]);
+    // energy = 1/{beta}^ln sum c_vl M_l + M (|{v}|^2 - {|v|^2}/2) + Pi {v}.n + p_inf n_t
+    const double k = fma(0.25, vv, -0.25 * s2);
+    F[NC - 1] = fma(ce, pm.ib, fma(Mt, k, fma(0.5 * Pi, w, ph.pinf_tot * nt)));
+}
+
+// ES dissipation of the interface (iL, iR) = (st[2], st[3]), in Dout
+template <int N, int D, int NN, int RC>
+__device__ __forceinline__ void dissipation64(const Phys& ph, const NodeTile<N, D, NN, double>& S,
+                                              const double (*M)[NN], const int st[6],
+                                              const PairMeans<N>& pm, double* Dout)
+{
+    constexpr int NC = N + D + 1;
+    const int iL = st[2], iR = st[3];
+    const double tol = ph.stol64;
+#pragma unroll
+    for (int c = 0; c < NC; c++) Dout[c] = 0.0;
+    // node parts of the sign test's tolerance (see dissipation): sum_l |y_l|,
+    // beta |v|_1 and beta of both nodes
+    double ay = 0.0, av, aE;
+    // B_m >= max_l |R_lm| ay + sum_e |R_em| av + |R_Em| aE, so where the
+    // entropy variables of the two nodes differ by no more than the tolerance
+    // times ay, av and aE every |[[W_m]]| <= tol B_m and Y = 0.  The computed
+    // jump is within 16 u B_m of the exact one: the test keeps 32 u of distance,
+    // and below that asks for equality.
+    {
+        const double tq = fmax(0.0, 0.99 * (tol - 7.2e-15));
+        const double bL = S.b[iL], bR = S.b[iR];
+        double dy = 0.0, dm = 0.0, aL = 0.0, aR = 0.0;
+#pragma unroll
+        for (int l = 0; l < N; l++) {
+            const double yL = S.y[l][iL], yR = S.y[l][iR];
+            dy += fabs(yL - yR);
+            ay += fabs(yL);
+            ay += fabs(yR);
+        }
+#pragma unroll
+        for (int j = 0; j < D; j++) {
+            const double vL = S.v[j][iL], vR = S.v[j][iR];
+            dm += fabs(fma(bL, vL, -(bR * vR)));
+            aL += fabs(vL);
+            aR += fabs(vR);
+        }
+        aE = fabs(bL) + fabs(bR);
+        av = fma(fabs(bL), aL, fabs(bR) * aR);
+        const bool flat = (dy <= tq * ay) && (dm <= tq * av) && (fabs(bL - bR) <= tq * aE);
+        if (!__any(!flat)) return;
+    }
+    // interface normal, its rotation rows and the averaged velocity
+    // (read again from the tile by each group)
+    auto averaged = [&](double (&vb)[D]) {
+#pragma unroll
+        for (int j = 0; j < D; j++) vb[j] = 0.5 * (S.v[j][iL] + S.v[j][iR]);
+    };
+    double n[D], vb[D];
+    averaged(vb);
+    const double nt = M[0][iL] + M[0][iR];
+    double nn2 = 0.0, vn = 0.0, K = 0.0;
+#pragma unroll
+    for (int j = 0; j < D; j++) {
+        n[j] = M[1 + j][iL] + M[1 + j][iR];
+        nn2 = fma(n[j], n[j], nn2);
+        vn = fma(vb[j], n[j], vn);
+        K = fma(vb[j], vb[j], K);
+    }
+    K *= 0.5;
+    const bool nz = nn2 > 0.0;
+    const double inn = nz ? rsqrt64(nn2) : 0.0;
+    const double nn = nn2 * inn;
+    // the rotation's angle factors (its rows are formed where they are used)
+    double ct, sn, cp = 1.0, sp = 0.0;
+    if constexpr (D == 2) {
+        ct = nz ? n[0] * inn : 1.0;
+        sn = n[1] * inn;
+    } else {
+        const double r2 = fma(n[0], n[0], n[1] * n[1]);
+        const bool tz = r2 > 0.0;
+        const double ir = tz ? rsqrt64(r2) : 0.0;
+        ct = tz ? n[0] * ir : 1.0;
+        sn = n[1] * ir;
+        cp = nz ? (r2 * ir) * inn : 1.0;
+        sp = n[2] * inn;
+    }
+    // rotated averaged velocity and the sum of its tangential magnitudes
+    auto rotated = [&](const double (&vb)[D], double (&vh)[D], double& vt) {
+        const double a = fma(ct, vb[0], sn * vb[1]);
+        vh[0] = a;
+        vh[1] = fma(ct, vb[1], -(sn * vb[0]));
+        if constexpr (D == 3) {
+            vh[0] = fma(cp, a, sp * vb[2]);
+            vh[2] = fma(cp, vb[2], -(sp * a));
+        }
+        vt = fabs(vh[1]);
+        if constexpr (D == 3) vt += fabs(vh[2]);
+    };
+    // averaged state and the scaled columns of R
+    const double Tb = pm.ib;
+    double c, H, sa, irho = 0.0;
+    double syg = 0.0, sqg = 0.0, e2[2] = {0.0, 0.0}, se = 0.0;
+    if constexpr (N == 1) {
+        c = sqrt64(ph.gam[0] * ph.Rg[0] * Tb);
+        H = fma(ph.cvgam[0], Tb, K);
+        sa = sqrt64(pm.rho[0] * ph.isa);
+        se = sqrt64(pm.rho[0] * ph.ise);
+    } else {
+        // (the scheduling fences keep the steps from overlapping: together they
+        // need more registers than four waves a SIMD have)
+        __builtin_amdgcn_sched_barrier(0);
+        double Gb, Rb, pp, rho;
+        {
+            const double r0L = S.rho[0][iL], r1L = S.rho[1][iL], r0R = S.rho[0][iR], r1R = S.rho[1][iR];
+            const double rtL = r0L + r1L, rtR = r0R + r1R;
+            // means of the mixture Gamma, R and p + p_inf, each over one divisor
+            {
+                const double cvL = fma(ph.cv[0], r0L, ph.cv[1] * r1L), cvR = fma(ph.cv[0], r0R, ph.cv[1] * r1R);
+                const double cgL = fma(ph.cvgam[0], r0L, ph.cvgam[1] * r1L);
+                const double cgR = fma(ph.cvgam[0], r0R, ph.cvgam[1] * r1R);
+                Gb = 0.5 * fma(cgL, cvR, cgR * cvL) * rcp64(cvL * cvR);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            const double RL = fma(ph.Rg[0], r0L, ph.Rg[1] * r1L), RR = fma(ph.Rg[0], r0R, ph.Rg[1] * r1R);
+            Rb = 0.5 * fma(RL, rtR, RR * rtL) * rcp64(rtL * rtR);
+            __builtin_amdgcn_sched_barrier(0);
+            const double bL = S.b[iL], bR = S.b[iR];
+            pp = 0.5 * fma(RL, bR, RR * bL) * rcp64(bL * bR);
+            __builtin_amdgcn_sched_barrier(0);
+            rho = logmean64(rtL, rtR);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const double Gm = Gb - 1.0;
+        const double ig = rcp64(rho * Gm);
+        irho = ig * Gm;
+        // rho h = {p} + sum (c_vl rho_l T + p_inf,l): the p_inf cancel by hand
+        H = fma(fma(fma(ph.cv[0], pm.rho[0], ph.cv[1] * pm.rho[1]), Tb, pp), irho, K);
+        const double Tg = Tb * (ig * rho);
+#pragma unroll
+        for (int l = 0; l < 2; l++) e2[l] = fma(-(fma(-Gb, ph.cv[l], ph.cvgam[l])), Tg, K);
+        __builtin_amdgcn_sched_barrier(0);
+        const double GR = Gb * Rb, i = rcp64(GR);
+        c = sqrt64(GR * Tb);
+        __builtin_amdgcn_sched_barrier(0);
+        const double q = rho * i;
+        syg = sqrt64((pm.rho[0] * irho * pm.rho[1]) * (Gb * i));
+        __builtin_amdgcn_sched_barrier(0);
+        sa = sqrt64(q) * 0.70710678118654752440;
+        __builtin_amdgcn_sched_barrier(0);
+        sqg = sqrt64(q * Gm);
+    }
+    double hs = 0.5 * fma(nn, c, fabs(nt + vn));   // s / 2
+    form_here(hs);
+
+    // one characteristic field per column: w(q) at tile node q for the fields
+    // of a group, NF of them; Z of the group
+    auto group = [&](auto nf_, auto w, const double* mg, double* Z) {
+        constexpr int NF = decltype(nf_)::value;
+        double W[NF][6];
+        {
+            double a[NF], b[NF];
+            w(st[2], a);
+            w(st[3], b);
+#pragma unroll
+            for (int f = 0; f < NF; f++) { W[f][2] = a[f]; W[f][3] = b[f]; Z[f] = 0.0; }
+        }
+        bool need = false;
+#pragma unroll
+        for (int f = 0; f < NF; f++) need = need || fabs(W[f][3] - W[f][2]) > tol * mg[f];
+        if (__any(need)) {
+#pragma unroll
+            for (int t = 0; t < 6; t++) {
+                if (t == 2 || t == 3) continue;
+                __builtin_amdgcn_sched_barrier(0);
+                double a[NF];
+                w(st[t], a);
+#pragma unroll
+                for (int f = 0; f < NF; f++) W[f][t] = a[f];
+            }
+#pragma unroll
+            for (int f = 0; f < NF; f++) {
+                double jump;
+                __builtin_amdgcn_sched_barrier(0);
+                const double jw = weno_jump64<RC == 1>(W[f], ph, jump);
+                if ((jw * jump > 0.0) && (fabs(jump) > tol * mg[f])) Z[f] = jw;
+            }
+        }
+    };
+    auto dotv = [&](const double* a, int q, double c0) {
+        double r = c0;
+#pragma unroll
+        for (int j = 0; j < D; j++) r = fma(a[j], S.v[j][q], r);
+        return r;
+    };
+
+    // R Z: species rows R0, R1, the sum that multiplies vbar, the other momentum
+    // parts mo and the energy row En
+    double R0, R1 = 0.0, zsum, En, mo[D];
+    // species (entropy) fields
+    asm volatile("" ::: "memory");
+    {
+        constexpr int NF = N == 1 ? 1 : 2;
+        double mg[NF], Z[NF], sd[NF], ce[NF], cd[NF][N];
+        double vb[D], vh[D], vt;
+        averaged(vb);
+        rotated(vb, vh, vt);
+        const double va = (fabs(vh[0]) + vt) * av;
+        if constexpr (N == 1) {
+            cd[0][0] = se;
+            sd[0] = se;
+            ce[0] = se * K;
+            mg[0] = se * fma(K, aE, ay + va);
+        } else {
+            cd[0][0] = -syg * ph.sr21;
+            cd[0][1] = syg * ph.isr21;
+            cd[1][0] = pm.rho[0] * (irho * sqg);
+            cd[1][1] = pm.rho[1] * (irho * sqg);
+#pragma unroll
+            for (int f = 0; f < 2; f++) {
+                sd[f] = cd[f][0] + cd[f][1];
+                ce[f] = fma(cd[f][0], e2[0], cd[f][1] * e2[1]);
+                mg[f] = fma(fabs(ce[f]), aE, fma(fabs(sd[f]), va, fmax(fabs(cd[f][0]), fabs(cd[f][1])) * ay));
+            }
+        }
+        group(std::integral_constant<int, NF>{},
+              [&](int q, double* o) {
+                  const double b = S.b[q];
+                  const double t = dotv(vb, q, 0.0);
+#pragma unroll
+                  for (int f = 0; f < NF; f++) {
+                      double r = b * fma(sd[f], t, -ce[f]);
+#pragma unroll
+                      for (int l = 0; l < N; l++) r = fma(cd[f][l], S.y[l][q], r);
+                      o[f] = r;
+                  }
+              },
+              mg, Z);
+        if constexpr (N == 1) {
+            const double z = se * Z[0];
+            R0 = zsum = z;
+            En = K * z;
+        } else {
+            const double z1 = fma(cd[0][0], Z[0], cd[1][0] * Z[1]), z2 = fma(cd[0][1], Z[0], cd[1][1] * Z[1]);
+            R0 = z1;
+            R1 = z2;
+            zsum = z1 + z2;
+            En = fma(ce[0], Z[0], ce[1] * Z[1]);
+        }
+    }
+    form_here(R0);
+    form_here(zsum);
+    form_here(En);
+    if constexpr (N == 2) form_here(R1);
+    // tangential fields
+    asm volatile("" ::: "memory");
+    {
+        const double sct = N == 1 ? sqrt64(pm.rho[0] * pm.ib) : 1.41421356237309504880 * sa * c;
+        double tc[D - 1][D], ck[D - 1], mg[D - 1], Z[D - 1];
+        double vb[D], vh[D], vt;
+        averaged(vb);
+        rotated(vb, vh, vt);
+#pragma unroll
+        for (int f = 0; f < D - 1; f++) {
+#pragma unroll
+            for (int j = 0; j < D; j++) tc[f][j] = 0.0;
+            ck[f] = sct * vh[1 + f];
+            mg[f] = fma(fabs(ck[f]), aE, sct * av);
+        }
+        tc[0][0] = -sct * sn;
+        tc[0][1] = sct * ct;
+        if constexpr (D == 3) {
+            const double q = -sct * sp;
+            tc[1][0] = q * ct;
+            tc[1][1] = q * sn;
+            tc[1][2] = sct * cp;
+        }
+        group(std::integral_constant<int, D - 1>{},
+              [&](int q, double* o) {
+                  const double b = S.b[q];
+#pragma unroll
+                  for (int f = 0; f < D - 1; f++) {
+                      double r = fma(tc[f][0], S.v[0][q], -ck[f]);
+                      r = fma(tc[f][1], S.v[1][q], r);
+                      if (D == 3 && f == 1) r = fma(tc[f][D - 1], S.v[D - 1][q], r);
+                      o[f] = b * r;
+                  }
+              },
+              mg, Z);
+#pragma unroll
+        for (int j = 0; j < D; j++) mo[j] = tc[0][j] * Z[0];
+        En = fma(ck[0], Z[0], En);
+        if constexpr (D == 3) {
+#pragma unroll
+            for (int j = 0; j < D; j++) mo[j] = fma(tc[1][j], Z[1], mo[j]);
+            En = fma(ck[1], Z[1], En);
+        }
+    }
+    form_here(En);
+#pragma unroll
+    for (int j = 0; j < D; j++) form_here(mo[j]);
+    // acoustic fields
+    asm volatile("" ::: "memory");
+    {
+        double cv[D], cn[D], row[D], mg[2], Z[2], cY[N];
+        double vb[D], vh[D], vt;
+        averaged(vb);
+        rotated(vb, vh, vt);
+        const double cv0 = c * vh[0];
+        row[0] = cp * ct;
+        row[1] = cp * sn;
+        if constexpr (D == 3) row[2] = sp;
+        const double cH = sa * H, sc = sa * c, ck = sa * cv0;
+#pragma unroll
+        for (int j = 0; j < D; j++) {
+            cv[j] = sa * vb[j];
+            cn[j] = sc * row[j];
+        }
+#pragma unroll
+        for (int l = 0; l < N; l++) cY[l] = N == 1 ? sa : pm.rho[l] * (irho * sa);
+        double ya = ay;
+        if constexpr (N == 2) ya = fmax(fabs(pm.rho[0]), fabs(pm.rho[1])) * fabs(irho) * ay;
+        mg[0] = sa * fma(fabs(H - cv0), aE, fma(fabs(vh[0] - c) + vt, av, ya));
+        mg[1] = sa * fma(fabs(H + cv0), aE, fma(fabs(vh[0] + c) + vt, av, ya));
+        group(std::integral_constant<int, 2>{},
+              [&](int q, double* o) {
+                  const double b = S.b[q];
+                  double r = b * dotv(cv, q, -cH);
+#pragma unroll
+                  for (int l = 0; l < N; l++) r = fma(cY[l], S.y[l][q], r);
+                  const double u = b * dotv(cn, q, -ck);
+                  o[0] = r - u;
+                  o[1] = r + u;
+              },
+              mg, Z);
+        const double zs = sa * (Z[0] + Z[1]), zd = sa * (Z[1] - Z[0]);
+        zsum += zs;
+        const double cz = c * zd;
+#pragma unroll
+        for (int j = 0; j < D; j++) mo[j] = fma(cz, row[j], mo[j]);
+        En = fma(H, zs, fma(cv0, zd, En));
+        if constexpr (N == 1) R0 += zs;
+        else {
+            const double zr = irho * zs;
+            R0 = fma(pm.rho[0], zr, R0);
+            R1 = fma(pm.rho[1], zr, R1);
+        }
+    }
+    form_here(R0);
+    form_here(zsum);
+    form_here(En);
+    if constexpr (N == 2) form_here(R1);
+#pragma unroll
+    for (int j = 0; j < D; j++) form_here(mo[j]);
+    asm volatile("" ::: "memory");
+    averaged(vb);
+    Dout[0] = hs * R0;
+    if constexpr (N == 2) Dout[1] = hs * R1;
+#pragma unroll
+    for (int j = 0; j < D; j++) Dout[N + j] = hs * fma(vb[j], zsum, mo[j]);
+    Dout[NC - 1] = hs * En;
+}
+
+// two-point EC flux in the precision of the sweep
+template <int N, int D, int NN, typename R>
+__device__ __forceinline__ void two_point(const Phys& ph, const NodeTile<N, D, NN, R>& S, const double (*M)[NN],
+                                          int ia, int ib, R* F)
+{
+    if constexpr (sizeof(R) == 8) {
+        PairMeans<N> pm;
+        double isb;
+        pair_means<N, D, NN>(S, ia, ib, pm, isb);
+        ec_flux64<N, D, NN>(ph, S, M, ia, ib, pm, isb, F);
+    } else {
+        ec_pair<N, D, NN, R>(ph, S, M, ia, ib, F);
+    }
+}
+
 // Numerical flux at the TL + 1 interfaces of each of TC lines of a tile
 // (the interface form of eq ECFlux_curv_2p minus the ES dissipation of eq
 // HOstable), left in X slot f + 1 of line c.
@@ -345,7 +887,7 @@ __device__ __forceinline__ void dissipation(const Phys& ph, const NodeTile<N, D,
 // wave); interface_fluxes takes the tile's own metrics and fixed sizes.
 template <int N, int D, int NN, int XS, bool XALIAS, int RC, typename R, int MG, typename LI, typename XI,
           typename LOK>
-__device__ __forceinline__ void interface_fluxes_m(const Phys& ph, const NodeTile<N, D, NN>& S,
+__device__ __forceinline__ void interface_fluxes_m(const Phys& ph, const NodeTile<N, D, NN, R>& S,
                                                    const double (*M)[NN], R (*X)[XS], LI lidx, XI xidx,
                                                    LOK line_ok, int fi, int fc, bool f_ok, int hid,
                                                    int TL, int TC)
@@ -356,24 +898,42 @@ __device__ __forceinline__ void interface_fluxes_m(const Phys& ph, const NodeTil
     R G[NC], A2[NC], B3[NC];
     if (f_ok) {
         R F[NC];
-        if (ph.dissipation) {
+        if constexpr (sizeof(R) == 8) {
+            PairMeans<N> pm;
+            double isb;
+            pair_means<N, D, NN>(S, lidx(fl, fc), lidx(fl + 1, fc), pm, isb);
+            if (ph.dissipation) {
+                int st[6];
+#pragma unroll
+                for (int q = 0; q < 6; q++) st[q] = lidx(fl - 2 + q, fc);
+                dissipation64<N, D, NN, RC>(ph, S, M, st, pm, G);
+            } else {
+#pragma unroll
+                for (int cc = 0; cc < NC; cc++) G[cc] = 0.0;
+            }
+            // (1 / (beta_a + beta_b) is taken again and the node values are read
+            // again: fewer registers across the dissipation)
+            asm volatile("" ::: "memory");
+            isb = rcp64(S.b[lidx(fl, fc)] + S.b[lidx(fl + 1, fc)]);
+            ec_flux64<N, D, NN>(ph, S, M, lidx(fl, fc), lidx(fl + 1, fc), pm, isb, F);
+        } else if (ph.dissipation) {
             // zero tolerance of the sign test, relative to the size of the
             // terms of W, in the precision of the arithmetic (0: the sign
             // test as printed)
-            const Weno<R> Wc = make_weno<R>(ph.chi, ph.eps, sizeof(R) == 8 ? ph.stol64 : ph.stol32);
+            const Weno<R> Wc = make_weno<R>(ph.chi, ph.eps, ph.stol32);
             int st[6];
 #pragma unroll
             for (int q = 0; q < 6; q++) st[q] = lidx(fl - 2 + q, fc);
-            dissipation<N, D, NN, RC, R, MG>(ph, S, M, st, Wc, G);
+            dissipation<N, D, NN, R, MG>(ph, S, M, st, Wc, G);
         } else {
 #pragma unroll
             for (int cc = 0; cc < NC; cc++) G[cc] = R(0);
         }
-        ec_pair<N, D, NN, R>(ph, S, M, lidx(fl, fc), lidx(fl + 1, fc), F);
+        if constexpr (sizeof(R) == 4) ec_pair<N, D, NN, R>(ph, S, M, lidx(fl, fc), lidx(fl + 1, fc), F);
 #pragma unroll
         for (int cc = 0; cc < NC; cc++) G[cc] = a1 * F[cc] - G[cc];
         if (a2 != R(0)) {
-            ec_pair<N, D, NN, R>(ph, S, M, lidx(fl, fc), lidx(fl + 2, fc), F);
+            two_point<N, D, NN, R>(ph, S, M, lidx(fl, fc), lidx(fl + 2, fc), F);
         } else {
 #pragma unroll
             for (int cc = 0; cc < NC; cc++) F[cc] = R(0);
@@ -381,7 +941,7 @@ __device__ __forceinline__ void interface_fluxes_m(const Phys& ph, const NodeTil
 #pragma unroll
         for (int cc = 0; cc < NC; cc++) A2[cc] = a2 * F[cc];
         if (a3 != R(0)) {
-            ec_pair<N, D, NN, R>(ph, S, M, lidx(fl, fc), lidx(fl + 3, fc), F);
+            two_point<N, D, NN, R>(ph, S, M, lidx(fl, fc), lidx(fl + 3, fc), F);
         } else {
 #pragma unroll
             for (int cc = 0; cc < NC; cc++) F[cc] = R(0);
@@ -399,7 +959,7 @@ __device__ __forceinline__ void interface_fluxes_m(const Phys& ph, const NodeTil
         const R am = (h == 2) ? a2 : a3;
         hslot = (h == 0) ? 0 : ((h == 1) ? 1 : TL + 3);
         if (line_ok(hc) && am != R(0)) {
-            ec_pair<N, D, NN, R>(ph, S, M, lidx(h == 0 ? 0 : 1, hc), lidx(h == 1 ? 4 : 3, hc), Bh);
+            two_point<N, D, NN, R>(ph, S, M, lidx(h == 0 ? 0 : 1, hc), lidx(h == 1 ? 4 : 3, hc), Bh);
         } else {
 #pragma unroll
             for (int cc = 0; cc < NC; cc++) Bh[cc] = R(0);
@@ -451,7 +1011,7 @@ __device__ __forceinline__ void interface_fluxes_m(const Phys& ph, const NodeTil
 
 template <int N, int D, int NN, int TL, int TC, bool XALIAS, int RC, typename R,
           int MG = (sizeof(R) == 8 ? 2 : 1), typename LI, typename XI, typename LOK>
-__device__ __forceinline__ void interface_fluxes(const Phys& ph, const NodeTile<N, D, NN>& S,
+__device__ __forceinline__ void interface_fluxes(const Phys& ph, const NodeTile<N, D, NN, R>& S,
                                                  R (*X)[(TL + 4) * TC], LI lidx, XI xidx,
                                                  LOK line_ok, int fi, int fc, bool f_ok, int hid)
 {
@@ -459,26 +1019,48 @@ __device__ __forceinline__ void interface_fluxes(const Phys& ph, const NodeTile<
                                                                   f_ok, hid, TL, TC);
 }
 
-// primitive node quantities of node gi of (JU, J) into tile slot li; returns
-// the status bits of the node (1: rho_l <= 0, T <= 0 or non-finite; 2: J <= 0)
-template <int N, int D, int NN>
-__device__ __forceinline__ unsigned node_state(const Phys& ph, NodeTile<N, D, NN>& S, int li,
-                                               const double* __restrict__ JU,
-                                               const double* __restrict__ Jv, long P, long gi)
+// J U and J of one node as loaded
+template <int NC>
+struct NodeRaw {
+    double U[NC], J;
+};
+
+template <int NC>
+__device__ __forceinline__ void node_load(NodeRaw<NC>& r, const double* __restrict__ JU,
+                                          const double* __restrict__ Jv, long P, long gi)
+{
+    r.J = Jv[gi];
+#pragma unroll
+    for (int cc = 0; cc < NC; cc++) r.U[cc] = JU[cc * P + gi];
+}
+
+// the reciprocal of the sweep's precision R (see rcp64)
+template <typename R>
+__device__ __forceinline__ double inv(double x)
+{
+    if constexpr (sizeof(R) == 8) return rcp64(x);
+    else return rcp(x);
+}
+
+// primitive node quantities of a loaded node into tile slot li; returns the
+// status bits of the node (1: rho_l <= 0, T <= 0 or non-finite; 2: J <= 0)
+template <int N, int D, int NN, typename R>
+__device__ __forceinline__ unsigned node_state(const Phys& ph, NodeTile<N, D, NN, R>& S, int li,
+                                               const NodeRaw<N + D + 1>& raw)
 {
     constexpr int NC = N + D + 1;
-    const double Jq = Jv[gi];
-    const double iJ = rcp(Jq);
+    const double Jq = raw.J;
+    const double iJ = inv<R>(Jq);
     double U[NC];
 #pragma unroll
-    for (int cc = 0; cc < NC; cc++) U[cc] = JU[cc * P + gi] * iJ;
+    for (int cc = 0; cc < NC; cc++) U[cc] = raw.U[cc] * iJ;
     double rt = 0.0, cvr = 0.0;
 #pragma unroll
     for (int sp = 0; sp < N; sp++) {
         rt += U[sp];
         cvr += ph.cv[sp] * U[sp];
     }
-    const double ir = rcp(rt);
+    const double ir = inv<R>(rt);
     double kin = 0.0;
 #pragma unroll
     for (int j = 0; j < D; j++) {
@@ -487,7 +1069,7 @@ __device__ __forceinline__ unsigned node_state(const Phys& ph, NodeTile<N, D, NN
         kin += 0.5 * U[N + j] * vj;
     }
     const double e = U[NC - 1] - kin - ph.pinf_tot;
-    const double beta = cvr * rcp(e);
+    const double beta = cvr * inv<R>(e);
     S.b[li] = beta;
     const double lbeta = ln_pos(beta);
     S.lb[li] = lbeta;
@@ -505,15 +1087,33 @@ __device__ __forceinline__ unsigned node_state(const Phys& ph, NodeTile<N, D, NN
         S.rho[sp][li] = U[sp];
         const double lr = ln_pos(U[sp]);
         S.lrho[sp][li] = lr;
-        ysum += fabs(ph.cv[sp] * lbeta + ph.Rg[sp] * lr + ph.cvgam[sp] - 0.5 * beta * v2);
+        if constexpr (sizeof(R) == 8) {
+            const double y = fma(-0.5 * beta, v2, fma(ph.Rg[sp], lr, fma(ph.cv[sp], lbeta, ph.cvgam[sp])));
+            S.y[sp][li] = y;
+        } else {
+            ysum += fabs(ph.cv[sp] * lbeta + ph.Rg[sp] * lr + ph.cvgam[sp] - 0.5 * beta * v2);
+        }
         ok = ok && (U[sp] > 0.0);
     }
-    S.ay[li] = float(ysum);
-    S.av[li] = float(fabs(beta) * v1);
-    if constexpr (N == 2) S.lrt[li] = ln_pos(rt);
+    if constexpr (sizeof(R) == 4) {
+        S.ay[li] = float(ysum);
+        S.av[li] = float(fabs(beta) * v1);
+    }
+    if constexpr (N == 2 && sizeof(R) == 4) S.lrt[li] = ln_pos(rt);
     unsigned bad = ok ? 0u : 1u;
     if (!(Jq > 0.0)) bad |= 2u;
     return bad;
+}
+
+// the same of node gi of (JU, J)
+template <int N, int D, int NN, typename R>
+__device__ __forceinline__ unsigned node_state(const Phys& ph, NodeTile<N, D, NN, R>& S, int li,
+                                               const double* __restrict__ JU,
+                                               const double* __restrict__ Jv, long P, long gi)
+{
+    NodeRaw<N + D + 1> raw;
+    node_load<N + D + 1>(raw, JU, Jv, P, gi);
+    return node_state<N, D, NN, R>(ph, S, li, raw);
 }
 
 }  // namespace es

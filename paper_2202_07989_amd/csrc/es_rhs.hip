@@ -22,13 +22,16 @@
 
 namespace es {
 
-// waves per SIMD: four for the FP64 x and y sweeps, whose dissipation takes
-// the acoustic and species fields in two groups to stay within 128
-// registers; three for the FP64 z sweep (its strided loads gain less from a
-// fourth wave than its spills cost) and for FP32 (one group: splitting it
+// What bounds a sweep: FP64 issue and the latency of its loads and barriers,
+// hidden by four blocks a compute unit (39.7 KB of LDS and 118 registers for
+// two species in 3D).  At 256^3 (water / air, moving mesh) a stage takes 3.11 ms
+// against 4.05 ms with the arithmetic written term by term (2.34 against
+// 3.06 thousand VALU instructions a wave), the loads of a block's nodes waited for one
+// after the other and the stage epilogue's loads and stores alternating.
+// Waves per SIMD: four in FP64, three in FP32 (one field group: splitting it
 // costs more than a fourth wave gains)
 template <int N, int D, int K, int TL, int TC, int MODE, typename R, int RC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((sizeof(R) == 8 && K != 2) ? 4 : 3, 8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 4 : 3, 8)))
 k_rhs_dir(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict__ Jv,
           const double* __restrict__ jxx, const double* __restrict__ jxt,
           double* __restrict__ accU, double* __restrict__ accJ, RkArgs rk,
@@ -44,7 +47,7 @@ k_rhs_dir(Phys ph, Geo g, const double* __restrict__ JU, const double* __restric
     static_assert(NI <= NT && 3 * TC <= 64 && TL * TC <= NT, "tile does not fit the block");
     constexpr int FA = (K == 0) ? 1 : 0;   // across index that runs fastest
     constexpr int SA = (K == 2) ? 1 : 2;   // slowest across index
-    __shared__ NodeTile<N, D, NN> S;
+    __shared__ NodeTile<N, D, NN, R> S;
     // the flux exchange overlays the node quantities (not the metrics, which
     // the GCL term reads afterwards): 37 KB of LDS in all for two species in
     // 3D, so four blocks share a compute unit
@@ -81,19 +84,42 @@ k_rhs_dir(Phys ph, Geo g, const double* __restrict__ JU, const double* __restric
     __syncthreads();
 
     // ---- phase 1: node quantities of the tile (+ halo) into LDS ----------
+    // all loads of the thread's nodes are issued before the first is used:
+    // the block then waits for memory once
     unsigned bad = 0;
     const double itd = rk.tdiv ? 1.0 / *rk.tdiv : 1.0;
-    for (int q = t; q < NN; q += NT) {
-        const int l = (K == 0) ? (q % NL) : (q / TC);
-        const int c = (K == 0) ? (q / NL) : (q % TC);
-        const int along = g.ng + seg0 + l - 3;
-        if (along >= g.np[K] || line0 + c >= nlines) continue;
-        const long gi = s_base[c] + along * sK;
-        const int li = lidx(l, c);
-        bad |= node_state<N, D, NN>(ph, S, li, JU, Jv, P, gi);
-        S.m[0][li] = jxt ? 0.5 * (jxt[(long)K * P + gi] * itd) : 0.0;
+    {
+        constexpr int NQ = (NN + NT - 1) / NT;
+        NodeRaw<NC> raw[NQ];
+        double mt[NQ], mx[NQ][D];
+        bool have[NQ];
+        int li[NQ];
+        const double* __restrict__ jt = jxt ? jxt : jxx;   // (a fixed mesh reads it and drops it)
 #pragma unroll
-        for (int j = 0; j < D; j++) S.m[1 + j][li] = 0.5 * jxx[(long)(K * D + j) * P + gi];
+        for (int r = 0; r < NQ; r++) {
+            const int q = t + r * NT;
+            const int l = (K == 0) ? (q % NL) : (q / TC);
+            const int c = (K == 0) ? (q / NL) : (q % TC);
+            const int along = g.ng + seg0 + l - 3;
+            have[r] = q < NN && along < g.np[K] && line0 + c < nlines;
+            li[r] = lidx(l, c);
+            // (a node that does not exist reads the tile's first node: a branch
+            // would make the loads wait for each other)
+            const long gi = have[r] ? s_base[c] + along * sK : s_base[0] + (g.ng + seg0) * sK;
+            node_load<NC>(raw[r], JU, Jv, P, gi);
+            mt[r] = jt[(long)K * P + gi];
+#pragma unroll
+            for (int j = 0; j < D; j++) mx[r][j] = jxx[(long)(K * D + j) * P + gi];
+        }
+#pragma unroll
+        for (int r = 0; r < NQ; r++) {
+            if (have[r]) {
+                bad |= node_state<N, D, NN, R>(ph, S, li[r], raw[r]);
+                S.m[0][li[r]] = jxt ? 0.5 * (mt[r] * itd) : 0.0;
+#pragma unroll
+                for (int j = 0; j < D; j++) S.m[1 + j][li[r]] = 0.5 * mx[r][j];
+            }
+        }
     }
     if (bad) atomicOr(status, bad);
     __syncthreads();
@@ -121,30 +147,32 @@ k_rhs_dir(Phys ph, Geo g, const double* __restrict__ JU, const double* __restric
             const long gi = s_base[c] + (g.ng + seg0 + lo) * sK;
             const double h = g.idxi[K];
             const double dJ = -gcl * h;   // S.m holds half the metrics
+            // every operand is loaded before the first result is stored (the
+            // output may be the accumulator or Q_n, so a load after a store
+            // would wait for it: seven round trips to memory instead of one)
+            double ac[NC + 1], qs[NC + 1], qn[NC + 1];
+            // stage 0 has a = 0: Q_s stands in for Q_n, which is not read
+            const double* qnU = MODE == MODE_RK && rk.a != 0.0 ? rk.JUn : JU;
+            const double* qnJ = MODE == MODE_RK && rk.a != 0.0 ? rk.Jn : Jv;
 #pragma unroll
-            for (int cc = 0; cc < NC; cc++) {
-                const double d = -(double)(X[cc][xidx(lo + 2, c)] - X[cc][xidx(lo + 1, c)]) * h;
-                double* o = accU + cc * P + gi;
-                if constexpr (MODE == MODE_WRITE) {
-                    *o = d;
-                } else if constexpr (MODE == MODE_ADD) {
-                    *o += d;
-                } else {
-                    const double L = *o + d;
-                    double* w = (rk.outU ? rk.outU : accU) + cc * P + gi;
-                    // stage 0 has a = 0: Q_n is not read at all
-                    const double qn = rk.a != 0.0 ? rk.JUn[cc * P + gi] : 0.0;
-                    *w = rk.a * qn + rk.b * (JU[cc * P + gi] + dt * L);
+            for (int cc = 0; cc <= NC; cc++) {
+                if constexpr (MODE != MODE_WRITE) ac[cc] = cc < NC ? accU[cc * P + gi] : accJ[gi];
+                if constexpr (MODE == MODE_RK) {
+                    qs[cc] = cc < NC ? JU[cc * P + gi] : Jv[gi];
+                    qn[cc] = cc < NC ? qnU[cc * P + gi] : qnJ[gi];
                 }
             }
-            if constexpr (MODE == MODE_WRITE) {
-                accJ[gi] = dJ;
-            } else if constexpr (MODE == MODE_ADD) {
-                accJ[gi] += dJ;
-            } else {
-                const double L = accJ[gi] + dJ;
-                const double qn = rk.a != 0.0 ? rk.Jn[gi] : 0.0;
-                (rk.outJ ? rk.outJ : accJ)[gi] = rk.a * qn + rk.b * (Jv[gi] + dt * L);
+            double* oU = MODE == MODE_RK && rk.outU ? rk.outU : accU;
+            double* oJ = MODE == MODE_RK && rk.outJ ? rk.outJ : accJ;
+#pragma unroll
+            for (int cc = 0; cc <= NC; cc++) {
+                const double d = cc < NC ? -(double)(X[cc < NC ? cc : 0][xidx(lo + 2, c)] -
+                                                     X[cc < NC ? cc : 0][xidx(lo + 1, c)]) * h
+                                         : dJ;
+                double o = d;
+                if constexpr (MODE != MODE_WRITE) o = ac[cc] + d;
+                if constexpr (MODE == MODE_RK) o = rk.a * qn[cc] + rk.b * (qs[cc] + dt * o);
+                (cc < NC ? oU[cc * P + gi] : oJ[gi]) = o;
             }
         }
     }
@@ -179,7 +207,7 @@ k_rhs_xy(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict
     constexpr int XS = XSX > XSY ? XSX : XSY;
     static_assert((TX + 1) * TY <= NT / 2 && (TY + 1) * TX <= NT / 2 && 3 * TX <= 64 && 3 * TY <= 64,
                   "tile does not fit the block");
-    __shared__ NodeTile<N, D, NN> S;     // S.m: the x metrics
+    __shared__ NodeTile<N, D, NN, R> S;     // S.m: the x metrics
     __shared__ double My[D + 1][NN];     // the y metrics
     static_assert(sizeof(R) * 2 * NC * XS <= sizeof(S) - sizeof(S.m), "exchange does not fit the tile");
     R (*Xb)[XS] = reinterpret_cast<R (*)[XS]>(&S.rho[0][0]);   // x rows 0..NC-1, y rows NC..2NC-1
@@ -195,30 +223,45 @@ k_rhs_xy(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict
     const int t = threadIdx.x;
 
     // ---- node quantities and metrics of the patch -------------------------
+    // one node a thread, all of its loads issued before the first is used
+    static_assert(NN <= NT, "one node a thread");
     unsigned bad = 0;
-    for (int q = t; q < NN; q += NT) {
-        const int lx = q % NEX, ly = q / NEX;
+    const double itd = tdiv ? 1.0 / *tdiv : 1.0;
+    {
+        const int lx = t % NEX, ly = t / NEX;
         const bool cx = lx >= 3 && lx < 3 + TX, cy = ly >= 3 && ly < 3 + TY;
-        if (!(cx || cy)) continue;                                        // corners
-        if (ox + lx - 3 + ng >= np0 || oy + ly - 3 + ng >= np1) continue;  // beyond a ragged tile
-        bad |= node_state<N, D, NN>(ph, S, q, JU, Jv, P, base + (long)ly * np0 + lx);
+        // corners are never read, nodes beyond a ragged tile do not exist
+        const bool have = t < NN && (cx || cy) && ox + lx - 3 + ng < np0 && oy + ly - 3 + ng < np1;
+        const long gi = base + (long)ly * np0 + lx;
+        if (have) {
+            NodeRaw<NC> raw;
+            double mx[D + 1], my[D + 1];
+            node_load<NC>(raw, JU, Jv, P, gi);
+            const double* __restrict__ jt = jxt ? jxt : jxx;   // (a fixed mesh reads it and drops it)
+            if (cy) {
+                mx[0] = jt[gi];
+#pragma unroll
+                for (int j = 0; j < D; j++) mx[1 + j] = jxx[(long)j * P + gi];
+            }
+            if (cx) {
+                my[0] = jt[P + gi];
+#pragma unroll
+                for (int j = 0; j < D; j++) my[1 + j] = jxx[(long)(D + j) * P + gi];
+            }
+            bad = node_state<N, D, NN, R>(ph, S, t, raw);
+            if (cy) {
+                S.m[0][t] = jxt ? 0.5 * (mx[0] * itd) : 0.0;
+#pragma unroll
+                for (int j = 0; j < D; j++) S.m[1 + j][t] = 0.5 * mx[1 + j];
+            }
+            if (cx) {
+                My[0][t] = jxt ? 0.5 * (my[0] * itd) : 0.0;
+#pragma unroll
+                for (int j = 0; j < D; j++) My[1 + j][t] = 0.5 * my[1 + j];
+            }
+        }
     }
     if (bad) atomicOr(status, bad);
-    const double itd = tdiv ? 1.0 / *tdiv : 1.0;
-    for (int q = t; q < NEX * TY + TX * NEY; q += NT) {
-        const bool ydir = q >= NEX * TY;
-        const int u = ydir ? q - NEX * TY : q;
-        const int lx = ydir ? 3 + u % TX : u % NEX;
-        const int ly = ydir ? u / TX : 3 + u / NEX;
-        if (ox + lx - 3 + ng >= np0 || oy + ly - 3 + ng >= np1) continue;
-        const long gi = base + (long)ly * np0 + lx;
-        const int K = ydir ? 1 : 0;
-        double (*Mk)[NN] = ydir ? My : S.m;
-        const int li = lx + NEX * ly;
-        Mk[0][li] = jxt ? 0.5 * (jxt[(long)K * P + gi] * itd) : 0.0;
-#pragma unroll
-        for (int j = 0; j < D; j++) Mk[1 + j][li] = 0.5 * jxx[(long)(K * D + j) * P + gi];
-    }
     __syncthreads();
 
     // ---- interface fluxes: x in waves 0-3, y in waves 4-7 ------------------
