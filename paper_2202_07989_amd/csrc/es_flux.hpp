@@ -844,6 +844,10 @@ __device__ __forceinline__ void dissipation64(const Phys& ph, const NodeTile<N, 
     Dout[NC - 1] = hs * En;
 }
 
+struct NoPre {
+    __device__ __forceinline__ void operator()() const {}
+};
+
 // two-point EC flux in the precision of the sweep
 template <int N, int D, int NN, typename R>
 __device__ __forceinline__ void two_point(const Phys& ph, const NodeTile<N, D, NN, R>& S, const double (*M)[NN],
@@ -884,13 +888,14 @@ __device__ __forceinline__ void two_point(const Phys& ph, const NodeTile<N, D, N
 // interface_fluxes_m is the general form: the metrics M of the direction
 // are passed in, X rows are XS slots long, and the tile's TL and TC may be
 // run-time values (a block that sweeps two directions at once picks them per
-// wave); interface_fluxes takes the tile's own metrics and fixed sizes.
+// wave), and pre() runs between the fluxes and the exchange (loads that the
+// caller wants in flight through the latter); interface_fluxes takes the tile's own metrics and fixed sizes.
 template <int N, int D, int NN, int XS, bool XALIAS, int RC, typename R, int MG, typename LI, typename XI,
-          typename LOK>
+          typename LOK, typename PRE>
 __device__ __forceinline__ void interface_fluxes_m(const Phys& ph, const NodeTile<N, D, NN, R>& S,
                                                    const double (*M)[NN], R (*X)[XS], LI lidx, XI xidx,
                                                    LOK line_ok, int fi, int fc, bool f_ok, int hid,
-                                                   int TL, int TC)
+                                                   int TL, int TC, PRE pre)
 {
     constexpr int NC = N + D + 1;
     const R a1 = R(ph.alpha[0]), a2 = R(ph.alpha[1]), a3 = R(ph.alpha[2]);
@@ -967,6 +972,7 @@ __device__ __forceinline__ void interface_fluxes_m(const Phys& ph, const NodeTil
 #pragma unroll
         for (int cc = 0; cc < NC; cc++) Bh[cc] = am * Bh[cc];
     }
+    pre();
     if constexpr (XALIAS) __syncthreads();   // node reads end before X overwrites them
     if (halo) {
 #pragma unroll
@@ -1010,13 +1016,14 @@ __device__ __forceinline__ void interface_fluxes_m(const Phys& ph, const NodeTil
 }
 
 template <int N, int D, int NN, int TL, int TC, bool XALIAS, int RC, typename R,
-          int MG = (sizeof(R) == 8 ? 2 : 1), typename LI, typename XI, typename LOK>
+          int MG = (sizeof(R) == 8 ? 2 : 1), typename LI, typename XI, typename LOK, typename PRE = NoPre>
 __device__ __forceinline__ void interface_fluxes(const Phys& ph, const NodeTile<N, D, NN, R>& S,
                                                  R (*X)[(TL + 4) * TC], LI lidx, XI xidx,
-                                                 LOK line_ok, int fi, int fc, bool f_ok, int hid)
+                                                 LOK line_ok, int fi, int fc, bool f_ok, int hid,
+                                                 PRE pre = PRE())
 {
     interface_fluxes_m<N, D, NN, (TL + 4) * TC, XALIAS, RC, R, MG>(ph, S, S.m, X, lidx, xidx, line_ok, fi, fc,
-                                                                  f_ok, hid, TL, TC);
+                                                                  f_ok, hid, TL, TC, pre);
 }
 
 // J U and J of one node as loaded

@@ -2,13 +2,17 @@
 // fused SSP-RK3 stage (Section 5) on gfx950.
 //
 // k_rhs_dir is one launch per direction k; k_rhs_xy (below) builds the x and
-// y directions of a 3D grid in one launch, and 3D stages take it and then
-// the z sweep.  In k_rhs_dir a block of 256 threads owns a tile of TL
-// nodes along k on TC grid lines (consecutive in the line ordering, so the
-// fastest other index runs along the lines and global loads coalesce),
-// stages the node quantities of the tile plus a 3-node halo along k in LDS,
-// and builds the full numerical flux at each of the TL + 1 interfaces of
-// every line, one thread per interface:
+// y directions of a 3D grid in one launch.  A 3D stage takes the z sweep, which
+// writes its term, and then k_rhs_xy, which adds the others and applies the
+// stage combination: the z sweep is bound by HBM (its halo along z is read
+// again by every tile), the x-y launch by FP64 issue, so the operands of the
+// combination are read beside the latter (2.78 against 2.99 ms a stage at
+// 256^3 with the combination in the z sweep).  In k_rhs_dir a block of 256
+// threads owns a tile of TL nodes along k on TC grid lines (consecutive in the
+// line ordering, so the fastest other index runs along the lines and global
+// loads coalesce), stages the node quantities of the tile plus a 3-node halo
+// along k in LDS, and builds the full numerical flux at each of the TL + 1
+// interfaces of every line, one thread per interface:
 //   F_{i+1/2} = sum_m alpha_m sum_{s<m} F(i-s, i-s+m)  -  D_{i+1/2}
 // (the interface form of eq ECFlux_curv_2p minus the ES dissipation
 // 1/2 s T^T R Y [[W]]^WENO of eq HOstable).  Each two-point flux
@@ -16,7 +20,7 @@
 // a; the m interfaces that use it collect it through an LDS exchange in
 // three barrier-separated steps.  The node update is then the interface
 // difference plus the GCL term delta_k[n_t] (eq GCL_flux), times -1/dxi_k,
-// accumulated into the output; the last direction's epilogue can apply the
+// accumulated into the output; the last launch's epilogue can apply the
 // Shu-Osher stage combination.
 #include "es_flux.hpp"
 
@@ -24,7 +28,7 @@ namespace es {
 
 // What bounds a sweep: FP64 issue and the latency of its loads and barriers,
 // hidden by four blocks a compute unit (39.7 KB of LDS and 118 registers for
-// two species in 3D).  At 256^3 (water / air, moving mesh) a stage takes 3.11 ms
+// two species in 3D).  At 256^3 (water / air, moving mesh) a stage took 3.11 ms
 // against 4.05 ms with the arithmetic written term by term (2.34 against
 // 3.06 thousand VALU instructions a wave), the loads of a block's nodes waited for one
 // after the other and the stage epilogue's loads and stores alternating.
@@ -185,18 +189,14 @@ k_rhs_dir(Phys ph, Geo g, const double* __restrict__ JU, const double* __restric
 // once, then waves 0-3 build the x fluxes of the tile's TY rows and waves
 // 4-7 the y fluxes of its TX columns at the same time, each with the
 // interface scheme of interface_fluxes.  A node's output is the x
-// difference plus the y difference, each rounded on its own as the two
-// separate sweeps round them, so the sum equals the x-sweep-then-y-sweep
-// accumulation bit for bit; the z sweep then adds its own term.  Against the
-// two separate sweeps this loads 1.8 instead of 2.6 nodes per owned node and
-// skips the accumulator's round trip through memory.  LDS: 70 KB at
-// 16 x 15 with two species, two blocks (four waves per SIMD) per compute
-// unit.
-template <int N, int TX, int TY, typename R, int RC, int MG>
+// difference plus the y difference, each rounded on its own, plus the
+// accumulated z term.  LDS: 70 KB at 16 x 15 with two species, two blocks
+// (four waves per SIMD) per compute unit; bound by FP64 issue and by the
+// waits of the two blocks' phases (VALU busy 65 % of the cycles).
+template <int N, int TX, int TY, int MODE, typename R, int RC, int MG>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8)))
 k_rhs_xy(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict__ Jv,
-         const double* __restrict__ jxx, const double* __restrict__ jxt, double* __restrict__ accU,
-         double* __restrict__ accJ, const double* __restrict__ tdiv, unsigned* __restrict__ status)
+         const double* __restrict__ jxx, const double* __restrict__ jxt, double* accU, double* accJ, RkArgs rk, unsigned* __restrict__ status)
 {
     constexpr int D = 3;
     constexpr int NT = 512;
@@ -216,7 +216,7 @@ k_rhs_xy(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict
     const int ng = g.ng, np0 = g.np[0], np1 = g.np[1];
     const int nx = g.n[0], ny = g.n[1];
     int bx, by, bz;
-    xcd_tile(bx, by, bz);
+    xcd_plane(bx, by, bz);
     const int ox = bx * TX, oy = by * TY;
     // padded index of patch node (0, 0), at interior (ox - 3, oy - 3) of plane bz
     const long base = ((long)(ng + bz) * np1 + (oy + ng - 3)) * np0 + (ox + ng - 3);
@@ -226,7 +226,7 @@ k_rhs_xy(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict
     // one node a thread, all of its loads issued before the first is used
     static_assert(NN <= NT, "one node a thread");
     unsigned bad = 0;
-    const double itd = tdiv ? 1.0 / *tdiv : 1.0;
+    const double itd = rk.tdiv ? 1.0 / *rk.tdiv : 1.0;
     {
         const int lx = t % NEX, ly = t / NEX;
         const bool cx = lx >= 3 && lx < 3 + TX, cy = ly >= 3 && ly < 3 + TY;
@@ -265,15 +265,18 @@ k_rhs_xy(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict
     __syncthreads();
 
     // ---- interface fluxes: x in waves 0-3, y in waves 4-7 ------------------
-    // x: interface fi of row fc (along-fastest, so a wave reads consecutive
-    // nodes of a row); y: interface fi of column fc (column-fastest).  The
-    // direction is uniform over a wave; read from the first lane, everything
+    // x: interface fi of row fc, rows fastest; y: interface fi of column fc,
+    // interfaces fastest.  Either way consecutive lanes are one patch row
+    // (22 doubles) apart: 16 of them fall on the even banks and the next 16,
+    // one node on, on the odd ones.  (Lanes along the contiguous index break a
+    // row every 16 or 17 lanes and met conflicts for a third of the LDS time.)
+    // The direction is uniform over a wave; read from the first lane, everything
     // derived from it lives in scalar registers
     const bool ydir = __builtin_amdgcn_readfirstlane(t / (NT / 2)) != 0;
     const int u = t & (NT / 2 - 1);
     const int TL = ydir ? TY : TX, TC = ydir ? TX : TY;
-    const int fi = ydir ? u / TX : u % (TX + 1);
-    const int fc = ydir ? u % TX : u / (TX + 1);
+    const int fi = ydir ? u % (TY + 1) : u / TY;
+    const int fc = ydir ? u / (TY + 1) : u % TY;
     const int o_along = ydir ? oy : ox, o_line = ydir ? ox : oy;
     const int n_line = ydir ? nx : ny, np_along = ydir ? np1 : np0;
     const bool f_ok = (u < (TL + 1) * TC) && (o_line + fc < n_line) && (o_along + fi + 2 + ng < np_along);
@@ -282,37 +285,67 @@ k_rhs_xy(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict
     // direction's arithmetic on its own under a branch took 4 % longer: the
     // join spills registers)
     const int sl = ydir ? NEX : 1, sc = ydir ? 1 : NEX, l0 = ydir ? 3 : 3 * NEX;
-    const int xl = ydir ? TX : 1, xc = ydir ? 1 : TX + 4;
+    const int xl = ydir ? 1 : TY, xc = ydir ? TY + 4 : 1;
+    // each half of the block writes half of the components (J U, then J) of the
+    // tile's nodes; their operands are fetched before the exchange
+    constexpr int NH = NC / 2 + 1;
+    const int ni = u % TX, nj = u / TX, c0 = ydir ? NH : 0;
+    const bool own = u < TX * TY && ox + ni < nx && oy + nj < ny;
+    const long gn = own ? base + (long)(nj + 3) * np0 + (ni + 3) : base + 3L * np0 + 3;
+    double ac[NH], qs[NH], qn[NH];
+    auto fetch = [&] {
+#pragma unroll
+        for (int i = 0; i < NH; i++) {
+            const int cc = c0 + i < NC ? c0 + i : NC;
+            const bool isJ = cc == NC;
+            if constexpr (MODE != MODE_WRITE) ac[i] = (isJ ? accJ : accU + cc * P)[gn];
+            if constexpr (MODE == MODE_RK) {
+                qs[i] = (isJ ? Jv : JU + cc * P)[gn];
+                // stage 0 has a = 0: Q_s stands in for Q_n, which is not read
+                const double* nU = rk.a != 0.0 ? rk.JUn : JU;
+                const double* nJ = rk.a != 0.0 ? rk.Jn : Jv;
+                qn[i] = (isJ ? nJ : nU + cc * P)[gn];
+            }
+        }
+    };
     interface_fluxes_m<N, D, NN, XS, true, RC, R, MG>(
         ph, S, ydir ? My : S.m, ydir ? Xb + NC : Xb, [=](int l, int c) { return l0 + l * sl + c * sc; },
         [=](int s, int c) { return s * xl + c * xc; }, [=](int c) { return o_line + c < n_line; }, fi, fc,
-        f_ok, u - (int)(blockIdx.x & 3) * 64, TL, TC);
+        f_ok, u - (int)(blockIdx.x & 3) * 64, TL, TC, fetch);
 
-    // ---- node outputs: x difference + y difference -------------------------
-    if (t < TX * TY) {
-        const int ni = t % TX, nj = t / TX;
-        if (ox + ni < nx && oy + nj < ny) {
-            const long gi = base + (long)(nj + 3) * np0 + (ni + 3);
-            auto lx_ = [](int l, int c) { return l + NEX * (c + 3); };
-            auto ly_ = [](int l, int c) { return (c + 3) + NEX * l; };
-            double gx = 0.0, gy = 0.0;
+    // ---- node outputs: z term + (x difference + y difference) --------------
+    if (own) {
+        const double hx = g.idxi[0], hy = g.idxi[1], dt = MODE == MODE_RK ? *rk.dt : 0.0;
+        const R (*Xx)[XS] = Xb;
+        const R (*Xy)[XS] = Xb + NC;
+        auto xs = [&](int s) { return nj + TY * (ni + s); };
+        auto ys = [&](int s) { return (nj + s) + (TY + 4) * ni; };
 #pragma unroll
-            for (int m = 1; m <= 3; m++) {
-                gx += ph.alpha[m - 1] * (S.m[0][lx_(ni + 3 + m, nj)] - S.m[0][lx_(ni + 3 - m, nj)]);
-                gy += ph.alpha[m - 1] * (My[0][ly_(nj + 3 + m, ni)] - My[0][ly_(nj + 3 - m, ni)]);
-            }
-            const double hx = g.idxi[0], hy = g.idxi[1];
-            const R (*Xx)[XS] = Xb;
-            const R (*Xy)[XS] = Xb + NC;
+        for (int i = 0; i < NH; i++) {
+            const int cc = c0 + i;
+            if (cc > NC) break;
+            double dx, dy;
+            if (cc < NC) {
+                dx = -(double)(Xx[cc][xs(2)] - Xx[cc][xs(1)]) * hx;
+                dy = -(double)(Xy[cc][ys(2)] - Xy[cc][ys(1)]) * hy;
+            } else {
+                auto lx_ = [&](int l) { return l + NEX * (nj + 3); };
+                auto ly_ = [&](int l) { return (ni + 3) + NEX * l; };
+                double gx = 0.0, gy = 0.0;
 #pragma unroll
-            for (int cc = 0; cc < NC; cc++) {
-                const double dx = -(double)(Xx[cc][(ni + 2) + (TX + 4) * nj] - Xx[cc][(ni + 1) + (TX + 4) * nj]) * hx;
-                const double dy = -(double)(Xy[cc][ni + TX * (nj + 2)] - Xy[cc][ni + TX * (nj + 1)]) * hy;
-                accU[cc * P + gi] = dx + dy;
+                for (int m = 1; m <= 3; m++) {
+                    gx += ph.alpha[m - 1] * (S.m[0][lx_(ni + 3 + m)] - S.m[0][lx_(ni + 3 - m)]);
+                    gy += ph.alpha[m - 1] * (My[0][ly_(nj + 3 + m)] - My[0][ly_(nj + 3 - m)]);
+                }
+                dx = -gx * hx;   // S.m and My hold half the metrics
+                dy = -gy * hy;
             }
-            const double dJx = -gx * hx;   // S.m and My hold half the metrics
-            const double dJy = -gy * hy;
-            accJ[gi] = dJx + dJy;
+            double o = dx + dy;
+            if constexpr (MODE != MODE_WRITE) o = o + ac[i];
+            if constexpr (MODE == MODE_RK) o = rk.a * qn[i] + rk.b * (qs[i] + dt * o);
+            double* out = cc < NC ? (MODE == MODE_RK && rk.outU ? rk.outU : accU) + cc * P
+                                  : (MODE == MODE_RK && rk.outJ ? rk.outJ : accJ);
+            out[gn] = o;
         }
     }
 }
@@ -345,16 +378,16 @@ static hipError_t launch_dir(const Phys& ph, const Geo& g, const double* JU, con
 }
 
 // the x and y directions of a 3D grid in one launch (k_rhs_xy)
-template <int N, typename R, int RC, int MG>
+template <int N, int MODE, typename R, int RC, int MG>
 static hipError_t launch_xy(const Phys& ph, const Geo& g, const double* JU, const double* J,
                             const double* jxx, const double* jxt, double* accU, double* accJ,
-                            const double* tdiv, unsigned* status, hipStream_t s)
+                            const RkArgs& rk, unsigned* status, hipStream_t s)
 {
     constexpr int TX = 16, TY = 15;
     const long gx = (g.n[0] + TX - 1) / TX, gy = (g.n[1] + TY - 1) / TY, gz = g.n[2];
     if (g.ng < 3 || gx * gy * gz > 0x7fffffffL || gy > 65535 || gz > 65535) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((k_rhs_xy<N, TX, TY, R, RC, MG>), dim3((unsigned)gx, (unsigned)gy, (unsigned)gz), dim3(512), 0, s,
-                       ph, g, JU, J, jxx, jxt, accU, accJ, tdiv, status);
+    hipLaunchKernelGGL((k_rhs_xy<N, TX, TY, MODE, R, RC, MG>), dim3((unsigned)gx, (unsigned)gy, (unsigned)gz), dim3(512), 0, s,
+                       ph, g, JU, J, jxx, jxt, accU, accJ, rk, status);
     return hipGetLastError();
 }
 
@@ -365,14 +398,14 @@ static hipError_t rhs_all(const Phys& ph, const Geo& g, const double* JU, const 
 {
     RkArgs none{nullptr, nullptr, nullptr, 0.0, 0.0};
     if (rk) none.tdiv = rk->tdiv;
-    // 3D: x and y in one launch, then the z sweep (bitwise the three sweeps'
-    // result, in both precisions; two field groups in the dissipation, which
-    // keeps the FP32 launch at 90 registers)
+    // 3D: the z sweep, then x and y in one launch with the stage combination
+    // (two field groups in the FP32 dissipation, which keeps that launch at 90
+    // registers)
     if constexpr (D == 3) {
-        hipError_t e = launch_xy<N, R, RC, 2>(ph, g, JU, J, jxx, jxt, outU, outJ, none.tdiv, status, s);
+        hipError_t e = launch_dir<N, D, 2, MODE_WRITE, R, RC>(ph, g, JU, J, jxx, jxt, outU, outJ, none, status, s);
         if (e != hipSuccess) return e;
-        if (rk) return launch_dir<N, D, 2, MODE_RK, R, RC>(ph, g, JU, J, jxx, jxt, outU, outJ, *rk, status, s);
-        return launch_dir<N, D, 2, MODE_ADD, R, RC>(ph, g, JU, J, jxx, jxt, outU, outJ, none, status, s);
+        if (rk) return launch_xy<N, MODE_RK, R, RC, 2>(ph, g, JU, J, jxx, jxt, outU, outJ, *rk, status, s);
+        return launch_xy<N, MODE_ADD, R, RC, 2>(ph, g, JU, J, jxx, jxt, outU, outJ, none, status, s);
     } else {
         hipError_t e = launch_dir<N, D, 0, MODE_WRITE, R, RC>(ph, g, JU, J, jxx, jxt, outU, outJ, none,
                                                           status, s);
