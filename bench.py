@@ -914,7 +914,7 @@ def main():
         "hbm_frac_of_peak_step": BYTES_PER_CELL_STAGE[key] * r["value"] / 1e9 / PEAK_HBM_GBS,
         "roofline": {"bound": "alu", "achieved": r["achieved"], "peak": r["peak"], "unit": "TFLOP/s",
                      "frac": r["achieved"] / r["peak"], "traffic": traffic,
-                     "kernel": "es_rk_stage (k_rhs_xy for x and y, k_rhs_dir along z with the stage epilogue)",
+                     "kernel": "es_rk_stage (k_rhs_z, then k_rhs_xy with the stage combination)",
                      "ms_per_launch": r["ms_stage"], "algorithmic_hbm_GBs": r["hbm_gbs"],
                      "algorithmic_hbm_frac": r["hbm_gbs"] / PEAK_HBM_GBS,
                      "flops_per_cell_stage": FLOPS_PER_CELL_STAGE[key],

@@ -604,23 +604,25 @@ __device__ __forceinline__ void xcd_tile(int& bx, int& by, int& bz)
 }
 
 // Tile of this block for plane-tile kernels whose work differs from tile to
-// tile: an XCD takes whole planes, every eighth, so the tiles of a plane share
-// an L2 and a front that crosses some planes or columns loads all XCDs alike
-// (with one run of planes per XCD the x-y sweep took 2.19 instead of 2.12 ms
-// at 256^3; with the tiles dealt in launch order, whose columns then stay with
-// one XCD, 2.69).  The planes past the last multiple of 8 keep launch order.
+// tile: an XCD takes whole planes (in 2D rows of tiles), every eighth, so the
+// tiles of a plane share an L2 and a front that crosses some planes or columns
+// loads all XCDs alike (with one run of planes per XCD the 3D x-y launch took 2.19
+// instead of 2.12 ms at 256^3; with the tiles dealt in launch order, whose
+// columns then stay with one XCD, 2.69).  What is left past the last multiple
+// of 8 keeps launch order.
+template <int D>
 __device__ __forceinline__ void xcd_plane(int& bx, int& by, int& bz)
 {
-    const unsigned gx = gridDim.x, gy = gridDim.y, pl = gx * gy;
+    const unsigned gx = gridDim.x, gy = gridDim.y, pl = D == 3 ? gx * gy : gx, npl = D == 3 ? gridDim.z : gy;
     const unsigned L = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
     bx = (int)blockIdx.x;
     by = (int)blockIdx.y;
     bz = (int)blockIdx.z;
-    if (L < gridDim.z / 8 * 8 * pl) {
-        const unsigned i = L >> 3, p = i / pl, r = i - p * pl;
-        bz = (int)(p * 8 + (L & 7));
-        by = (int)(r / gx);
-        bx = (int)(r - by * gx);
+    if (L < npl / 8 * 8 * pl) {
+        const unsigned i = L >> 3, p = i / pl, r = i - p * pl, q = p * 8 + (L & 7);
+        by = (int)(D == 3 ? r / gx : q);
+        bz = (int)(D == 3 ? q : 0);
+        bx = (int)(r % gx);
     }
 }
 

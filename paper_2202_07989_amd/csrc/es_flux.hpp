@@ -7,8 +7,6 @@
 
 namespace es {
 
-enum { MODE_WRITE = 0, MODE_ADD = 1, MODE_RK = 2 };
-
 // R is the precision of the interface arithmetic.  The FP64 tile keeps the
 // species entropy variables y_l (formed once per node, read by up to 18
 // interface stencils of it); the FP32 one forms them per interface from the
@@ -1110,17 +1108,6 @@ __device__ __forceinline__ unsigned node_state(const Phys& ph, NodeTile<N, D, NN
     unsigned bad = ok ? 0u : 1u;
     if (!(Jq > 0.0)) bad |= 2u;
     return bad;
-}
-
-// the same of node gi of (JU, J)
-template <int N, int D, int NN, typename R>
-__device__ __forceinline__ unsigned node_state(const Phys& ph, NodeTile<N, D, NN, R>& S, int li,
-                                               const double* __restrict__ JU,
-                                               const double* __restrict__ Jv, long P, long gi)
-{
-    NodeRaw<N + D + 1> raw;
-    node_load<N + D + 1>(raw, JU, Jv, P, gi);
-    return node_state<N, D, NN, R>(ph, S, li, raw);
 }
 
 }  // namespace es
