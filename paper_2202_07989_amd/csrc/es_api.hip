@@ -179,7 +179,7 @@ int alloc_workspace(es_ctx* c)
     if (!rc) rc = dalloc(&c->mesh.xb, d * P);
     if (!rc) rc = dalloc(&c->mesh.phi, P);
     if (!rc) rc = dalloc(&c->mesh.part, 8 * 2048);
-    if (!rc) rc = dalloc(&c->mesh.scal, 8);
+    if (!rc) rc = dalloc(&c->mesh.scal, 16);
     if (!rc) rc = dalloc(&c->bufA, (nc + 1) * P);
     if (!rc) rc = dalloc(&c->bufB, (nc + 1) * P);
     if (!rc) rc = dalloc(&c->jxx, d * d * P);

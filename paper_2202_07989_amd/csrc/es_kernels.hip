@@ -82,6 +82,69 @@ __device__ __forceinline__ double ghost_value(const Geo& g, int what, int c, con
     return v;
 }
 
+// ghost position of interior coordinate i (0 .. n-1) of direction k on side sd
+// (-1 / 0 / +1; 0: i itself); false where it has none in the ng layers
+__device__ __forceinline__ bool image_pos(const Geo& g, int k, int i, int sd, int& pos)
+{
+    const int n = g.n[k];
+    if (sd == 0) {
+        pos = i;
+        return true;
+    }
+    const bool per = g.bc[k][sd > 0] == BC_PERIODIC;
+    pos = sd < 0 ? (per ? i - n : -1 - i) : (per ? i + n : 2 * n - 1 - i);
+    return sd < 0 ? pos >= -g.ng : pos < n + g.ng;
+}
+
+// writes the D-dimensional interior node (i0, i1, i2) of an ncomp-component
+// field and its ghost images under the field's ghost rule
+template <int D, int NCOMP>
+__device__ __forceinline__ void put_images(const Geo& g, int what, int i0, int i1, int i2, const double (&v)[NCOMP],
+                                           double* __restrict__ a)
+{
+    const int ng = g.ng;
+    const int z0 = D == 3 ? ng : 0;
+    const long di = node_index(g, i0 + ng, i1 + ng, i2 + z0);
+#pragma unroll
+    for (int c = 0; c < NCOMP; c++) a[c * g.P + di] = v[c];
+    if (i0 >= ng && i0 < g.n[0] - ng && i1 >= ng && i1 < g.n[1] - ng &&
+        (D == 2 || (i2 >= ng && i2 < g.n[2] - ng)))
+        return;
+#pragma unroll 1
+    for (int q = 0; q < (D == 3 ? 27 : 9); q++) {
+        const int side[3] = {q % 3 - 1, (q / 3) % 3 - 1, D == 3 ? q / 9 - 1 : 0};
+        int p0, p1, p2 = 0;
+        if (!side[0] && !side[1] && !side[2]) continue;
+        if (!image_pos(g, 0, i0, side[0], p0) || !image_pos(g, 1, i1, side[1], p1)) continue;
+        if (D == 3 && !image_pos(g, 2, i2, side[2], p2)) continue;
+        const long gi = node_index(g, p0 + ng, p1 + ng, p2 + z0);
+#pragma unroll
+        for (int c = 0; c < NCOMP; c++) a[c * g.P + gi] = ghost_value(g, what, c, side, v[c]);
+    }
+}
+
+// interior coordinate (0 .. n-1) that coordinate i of direction k images, i any
+// distance outside, and the mesh rule along the way: the mesh component k at
+// i is sg times its value there plus off
+__device__ __forceinline__ int mesh_image(const Geo& g, int k, int i, double& sg, double& off)
+{
+    const int n = g.n[k];
+    sg = 1.0;
+    off = 0.0;
+    while (i < 0 || i >= n) {
+        const int hi = i >= n;
+        if (g.bc[k][hi] == BC_PERIODIC) {
+            i += hi ? -n : n;
+            off += sg * (hi ? g.len[k] : -g.len[k]);
+        } else {
+            i = hi ? 2 * n - 1 - i : -1 - i;
+            off += sg * 2.0 * g.wall[k][hi];
+            sg = -sg;
+        }
+    }
+    return i;
+}
+
 // The grid-stride kernels of this file that produce a field also write its ghost
 // layers when given the shell sizes (nzs + nys + nxs > 0): a ghost node
 // takes the value of the interior node it wraps or mirrors to, computed again
@@ -979,6 +1042,37 @@ hipError_t entropy_sum(const Phys& ph, const Geo& g, const double* JU, const dou
 // ---------------------------------------------------------------------------
 // mesh redistribution (Section 4)
 // ---------------------------------------------------------------------------
+// The 2D kernels keep a maximum or minimum over all blocks in a device scalar
+// that the call's first launch resets (order does not matter, so the result
+// is the two-pass reduction's): non-negative doubles compare like their bits.
+__device__ __forceinline__ void scalar_max(double* a, double v)
+{
+    if (v > *(volatile double*)a)
+        atomicMax((unsigned long long*)a, (unsigned long long)__double_as_longlong(v));
+}
+
+// any sign: bits that order like the doubles
+__device__ __forceinline__ unsigned long long order_key(double v)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+}
+__device__ __forceinline__ double order_value(unsigned long long k)
+{
+    return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
+}
+
+// scal: the maxima [0..7] to 0, the limiter's key [8] to that of 1; the
+// residuals to 0
+__global__ void k_mesh_begin(double* __restrict__ scal, double* __restrict__ resid, int nresid)
+{
+    const int t = threadIdx.x;
+    if (t < 8) scal[t] = 0.0;
+    if (t == 8) ((unsigned long long*)scal)[8] = order_key(1.0);
+    if (resid)
+        for (int q = t; q < nresid; q += blockDim.x) resid[q] = 0.0;
+}
+
 // |grad_xi sigma| by second-order central differences, for each monitor
 // variable; per-block maxima into part[s * RED_BLOCKS + block].  The form
 // with a Laplacian term also writes |lap_xi sigma| (second-order central
@@ -1214,7 +1308,7 @@ k_filter3(Geo g, const double* __restrict__ in, double* __restrict__ out, int zc
 // then Phi from the global maximum (1 where it is 0)
 template <int N, int D>
 __global__ void k_rho_grad(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict__ Jv,
-                           double* __restrict__ gr, double* __restrict__ part)
+                           double* __restrict__ gr, double* __restrict__ gmax)
 {
     const long P = g.P;
     const long nint = n_interior(g);
@@ -1235,7 +1329,7 @@ __global__ void k_rho_grad(Phys ph, Geo g, const double* __restrict__ JU, const 
         gm = fmax(gm, gr[i]);
     }
     const double r = block_reduce<RED_MAX>(gm);
-    if (threadIdx.x == 0) part[blockIdx.x] = r;
+    if (threadIdx.x == 0) scalar_max(gmax, r);
 }
 
 template <int N, int D>
@@ -1255,17 +1349,17 @@ __global__ void k_schlieren(Phys ph, Geo g, MonitorP mo, const double* __restric
             const double r = sigma_of<N, D>(ph, JU, Jv, P, i, 0, nullptr);
             psi = (mo.psi[0] * r1 + mo.psi[1] * (r - r1)) / r;
         }
-        phi[i] = G > 0.0 ? exp(-psi * gr[i] / G) : 1.0;
+        const double v[1] = {G > 0.0 ? exp(-psi * gr[i] / G) : 1.0};
+        put_images<D, 1>(g, GH_PLAIN, i0 - g.ng, i1 - g.ng, D == 3 ? i2 - g.ng : 0, v, phi);
     }
 }
 
 template <int N, int D>
 static void launch_schlieren(const Phys& ph, const Geo& g, const MonitorP& mo, const double* JU,
-                             const double* J, double* gr, double* part, double* gmax, double* phi, int nb,
-                             int gi, hipStream_t s)
+                             const double* J, double* gr, double* gmax, double* phi, int nb, int gi,
+                             hipStream_t s)
 {
-    hipLaunchKernelGGL((k_rho_grad<N, D>), dim3(nb), dim3(256), 0, s, ph, g, JU, J, gr, part);
-    hipLaunchKernelGGL(k_finish<RED_MAX>, dim3(1), dim3(256), 0, s, part, nb, gmax, 0, 0.0, nullptr);
+    hipLaunchKernelGGL((k_rho_grad<N, D>), dim3(nb), dim3(256), 0, s, ph, g, JU, J, gr, gmax);
     hipLaunchKernelGGL((k_schlieren<N, D>), dim3(gi), dim3(256), 0, s, ph, g, mo, JU, J, gr, gmax, phi);
 }
 
@@ -1334,6 +1428,196 @@ __global__ void k_filter(Geo g, const double* __restrict__ in, double* __restric
         long di;
         const long si = shell_image(g, t, nzs, nys, side, di);
         out[di] = filter_node(g, in, si);
+    }
+}
+
+// the movement limiter's bound at node i for the moved position xm (1 if none)
+template <int D>
+__device__ __forceinline__ double limiter_bound(const Geo& g, const double* __restrict__ xn, long i,
+                                                const double (&xm)[D])
+{
+    const long P = g.P;
+    double b = 1.0;
+#pragma unroll
+    for (int k = 0; k < D; k++) {
+        const long st = dir_stride(g, k);
+        const double x0 = xn[k * P + i], dx = xm[k] - x0;
+        if (dx < 0.0) b = fmin(b, -(x0 - xn[k * P + i - st]) / (2.0 * dx));
+        else if (dx > 0.0) b = fmin(b, (xn[k * P + i + st] - x0) / (2.0 * dx));
+    }
+    return b;
+}
+
+// ---------------------------------------------------------------------------
+// 2D: a few thousand to a few hundred thousand nodes, where a launch of a few
+// microseconds costs more than its work.  Each block owns a 32 x 16 tile and
+// takes several steps of the same kind in LDS on a halo that shrinks by one
+// node a step (the halo's updates are computed again by the neighbours);
+// nodes outside the grid are filled by the face rules and updated like
+// any other, which the updates commute with.  800 x 160, five-variable
+// monitor, 3 filter passes, 10 Jacobi sweeps: 8 launches instead of 29.
+// ---------------------------------------------------------------------------
+constexpr int TX2 = 32, TY2 = 16, STEPS2 = 5;
+constexpr int RX2 = TX2 + 2 * STEPS2, RY2 = TY2 + 2 * STEPS2;
+
+// the monitor variables of a tile and its one-node halo, evaluated once per
+// node, then |grad| (and |lap|) at the tile's nodes and their maxima
+template <int N, int SIG>
+__global__ void __launch_bounds__(256)
+k_monitor2(Phys ph, Geo g, MonitorP mo, const double* __restrict__ JU, const double* __restrict__ Jv,
+           double* __restrict__ grad, double* __restrict__ gmax)
+{
+    constexpr int HX = TX2 + 2, HY = TY2 + 2;
+    __shared__ double Sg[HY][HX];
+    const long P = g.P;
+    const int ox = blockIdx.x * TX2, oy = blockIdx.y * TY2;
+    const double ih0 = 1.0 / (2.0 * g.dxi[0]), ih1 = 1.0 / (2.0 * g.dxi[1]);
+    const double il0 = 1.0 / (g.dxi[0] * g.dxi[0]), il1 = 1.0 / (g.dxi[1] * g.dxi[1]);
+    for (int s = 0; s < mo.nsig; s++) {
+        for (int q = threadIdx.x; q < HX * HY; q += 256) {
+            const int hx = q % HX, hy = q / HX;
+            const int gx = ox + hx - 1 + g.ng, gy = oy + hy - 1 + g.ng;
+            if (gx < g.np[0] && gy < g.np[1])
+                Sg[hy][hx] = sigma_of<N, 2, SIG>(ph, JU, Jv, P, (long)gy * g.np[0] + gx, mo.sigma[s], mo.phi);
+        }
+        __syncthreads();
+        double mg = 0.0, ml = 0.0;
+        for (int q = threadIdx.x; q < TX2 * TY2; q += 256) {
+            const int hx = q % TX2 + 1, hy = q / TX2 + 1;
+            const int x = ox + hx - 1, y = oy + hy - 1;
+            if (x >= g.n[0] || y >= g.n[1]) continue;
+            const long i = (long)(y + g.ng) * g.np[0] + (x + g.ng);
+            const double xp = Sg[hy][hx + 1], xm = Sg[hy][hx - 1], yp = Sg[hy + 1][hx], ym = Sg[hy - 1][hx];
+            const double d0 = (xp - xm) * ih0, d1 = (yp - ym) * ih1;
+            const double gv = sqrt(d0 * d0 + d1 * d1);
+            grad[s * P + i] = gv;
+            mg = fmax(mg, gv);
+            if (mo.form) {
+                const double s0 = Sg[hy][hx];
+                const double lap = fabs((xp - 2.0 * s0 + xm) * il0 + (yp - 2.0 * s0 + ym) * il1);
+                grad[(mo.nsig + s) * P + i] = lap;
+                ml = fmax(ml, lap);
+            }
+        }
+        const double rg = block_reduce<RED_MAX>(mg);
+        const double rl = mo.form ? block_reduce<RED_MAX>(ml) : 0.0;
+        if (threadIdx.x == 0) {
+            scalar_max(gmax + s, rg);
+            if (mo.form) scalar_max(gmax + mo.nsig + s, rl);
+        }
+    }
+}
+
+// `steps` passes of the low-pass filter; with gmax, theta is formed from the
+// monitor's gradients `in` first
+__global__ void __launch_bounds__(256)
+k_filter2(Geo g, MonitorP mo, const double* __restrict__ in, const double* __restrict__ gmax,
+          double* __restrict__ out, int steps)
+{
+    __shared__ double F[2][RY2][RX2];
+    const int ox = blockIdx.x * TX2, oy = blockIdx.y * TY2;
+    const int rx = TX2 + 2 * steps, ry = TY2 + 2 * steps;
+    for (int q = threadIdx.x; q < rx * ry; q += 256) {
+        const int hx = q % rx, hy = q / rx;
+        double sg, off;
+        const int ix = mesh_image(g, 0, ox + hx - steps, sg, off), iy = mesh_image(g, 1, oy + hy - steps, sg, off);
+        const long i = (long)(iy + g.ng) * g.np[0] + (ix + g.ng);
+        F[0][hy][hx] = gmax ? theta_node(mo, in, gmax, g.P, i) : in[i];
+    }
+    __syncthreads();
+    for (int p = 1; p <= steps; p++) {
+        const double (*A)[RX2] = F[(p - 1) & 1];
+        double (*B)[RX2] = F[p & 1];
+        const int wx = rx - 2 * p, wy = ry - 2 * p;
+        for (int q = threadIdx.x; q < wx * wy; q += 256) {
+            const int x = p + q % wx, y = p + q / wx;
+            const double r0 = 0.25 * A[y - 1][x - 1] + 0.5 * A[y - 1][x] + 0.25 * A[y - 1][x + 1];
+            const double r1 = 0.25 * A[y][x - 1] + 0.5 * A[y][x] + 0.25 * A[y][x + 1];
+            const double r2 = 0.25 * A[y + 1][x - 1] + 0.5 * A[y + 1][x] + 0.25 * A[y + 1][x + 1];
+            B[y][x] = 0.25 * r0 + 0.5 * r1 + 0.25 * r2;
+        }
+        __syncthreads();
+    }
+    for (int q = threadIdx.x; q < TX2 * TY2; q += 256) {
+        const int x = q % TX2, y = q / TX2;
+        if (ox + x >= g.n[0] || oy + y >= g.n[1]) continue;
+        const double v[1] = {F[steps & 1][y + steps][x + steps]};
+        put_images<2, 1>(g, GH_PLAIN, ox + x, oy + y, 0, v, out);
+    }
+}
+
+// `steps` Jacobi sweeps of the mesh equations; resid: the sweeps' residuals;
+// with xn (the last launch of a call) also the movement limiter's bound
+// against it, into the ordered key `bound`
+__global__ void __launch_bounds__(256)
+k_jacobi2(Geo g, const double* __restrict__ th, const double* __restrict__ xa, double* __restrict__ xb, int steps,
+          double* __restrict__ resid, const double* __restrict__ xn, unsigned long long* __restrict__ bound)
+{
+    __shared__ double Ts[RY2][RX2];
+    __shared__ double Xs[2][2][RY2][RX2];   // buffer, component
+    const long P = g.P;
+    const int ox = blockIdx.x * TX2, oy = blockIdx.y * TY2;
+    const int rx = TX2 + 2 * steps, ry = TY2 + 2 * steps;
+    for (int q = threadIdx.x; q < rx * ry; q += 256) {
+        const int hx = q % rx, hy = q / rx;
+        double s0, b0, s1, b1;
+        const int ix = mesh_image(g, 0, ox + hx - steps, s0, b0), iy = mesh_image(g, 1, oy + hy - steps, s1, b1);
+        const long i = (long)(iy + g.ng) * g.np[0] + (ix + g.ng);
+        Ts[hy][hx] = th[i];
+        Xs[0][0][hy][hx] = fma(s0, xa[i], b0);
+        Xs[0][1][hy][hx] = fma(s1, xa[P + i], b1);
+    }
+    __syncthreads();
+    const double w0 = 1.0 / (g.dxi[0] * g.dxi[0]), w1 = 1.0 / (g.dxi[1] * g.dxi[1]);
+    for (int p = 1; p <= steps; p++) {
+        const double (*A0)[RX2] = Xs[(p - 1) & 1][0];
+        const double (*A1)[RX2] = Xs[(p - 1) & 1][1];
+        double (*B0)[RX2] = Xs[p & 1][0];
+        double (*B1)[RX2] = Xs[p & 1][1];
+        const int wx = rx - 2 * p, wy = ry - 2 * p;
+        double r = 0.0;
+        for (int q = threadIdx.x; q < wx * wy; q += 256) {
+            const int x = p + q % wx, y = p + q / wx;
+            const double t0 = Ts[y][x];
+            double tp0 = 0.5 * (t0 + Ts[y][x + 1]), tm0 = 0.5 * (t0 + Ts[y][x - 1]);
+            double tp1 = 0.5 * (t0 + Ts[y + 1][x]), tm1 = 0.5 * (t0 + Ts[y - 1][x]);
+            tp0 *= w0;
+            tm0 *= w0;
+            tp1 *= w1;
+            tm1 *= w1;
+            double den = tp0 + tm0;
+            den += tp1 + tm1;
+            const double iden = rcp(den);
+            double n0 = tp0 * A0[y][x + 1] + tm0 * A0[y][x - 1];
+            n0 += tp1 * A0[y + 1][x] + tm1 * A0[y - 1][x];
+            double n1 = tp0 * A1[y][x + 1] + tm0 * A1[y][x - 1];
+            n1 += tp1 * A1[y + 1][x] + tm1 * A1[y - 1][x];
+            n0 *= iden;
+            n1 *= iden;
+            B0[y][x] = n0;
+            B1[y][x] = n1;
+            const bool own = x >= steps && x < steps + TX2 && y >= steps && y < steps + TY2 &&
+                             ox + x - steps < g.n[0] && oy + y - steps < g.n[1];
+            if (own) r = fmax(r, fmax(fabs(n0 - A0[y][x]), fabs(n1 - A1[y][x])));
+        }
+        if (resid) {   // (holds the step's barrier)
+            r = block_reduce<RED_MAX>(r);
+            if (threadIdx.x == 0) scalar_max(resid + p - 1, r);
+        } else {
+            __syncthreads();
+        }
+    }
+    double b = 1.0;
+    for (int q = threadIdx.x; q < TX2 * TY2; q += 256) {
+        const int x = q % TX2, y = q / TX2;
+        if (ox + x >= g.n[0] || oy + y >= g.n[1]) continue;
+        const double v[2] = {Xs[steps & 1][0][y + steps][x + steps], Xs[steps & 1][1][y + steps][x + steps]};
+        put_images<2, 2>(g, GH_MESH, ox + x, oy + y, 0, v, xb);
+        if (xn) b = fmin(b, limiter_bound<2>(g, xn, (long)(oy + y + g.ng) * g.np[0] + (ox + x + g.ng), v));
+    }
+    if (xn) {
+        b = block_reduce<RED_MIN>(b);
+        if (threadIdx.x == 0 && order_key(b) < *(volatile unsigned long long*)bound) atomicMin(bound, order_key(b));
     }
 }
 
@@ -1513,13 +1797,10 @@ __global__ void k_limiter(Geo g, const double* __restrict__ xmu, const double* _
     for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < nint; q += (long)gridDim.x * blockDim.x) {
         int i0, i1, i2;
         const long i = interior_node(g, q, i0, i1, i2);
+        double xm[D];
 #pragma unroll
-        for (int k = 0; k < D; k++) {
-            const long st = dir_stride(g, k);
-            const double dx = xmu[k * P + i] - xn[k * P + i];
-            if (dx < 0.0) b = fmin(b, -(xn[k * P + i] - xn[k * P + i - st]) / (2.0 * dx));
-            else if (dx > 0.0) b = fmin(b, (xn[k * P + i + st] - xn[k * P + i]) / (2.0 * dx));
-        }
+        for (int k = 0; k < D; k++) xm[k] = xmu[k * P + i];
+        b = fmin(b, limiter_bound<D>(g, xn, i, xm));
     }
     b = block_reduce<RED_MIN>(b);
     if (threadIdx.x == 0) part[blockIdx.x] = b;
@@ -1557,16 +1838,82 @@ __global__ void k_disp(Geo g, const double* __restrict__ xmu, const double* __re
     }
 }
 
-template <int N, int D>
+// the same in 2D, a node and its images a thread; the limiter's key is
+// decoded here (Delta_tau into dtau and, when given, dtau_out)
+__global__ void k_disp2(Geo g, const double* __restrict__ xmu, const double* __restrict__ xn,
+                        const unsigned long long* __restrict__ bound, double* __restrict__ dtau,
+                        double* __restrict__ dtau_out, double* __restrict__ disp, double* __restrict__ xnext,
+                        unsigned* __restrict__ status)
+{
+    const long P = g.P;
+    const double d = fmin(1.0, order_value(*bound));
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *dtau = d;
+        if (dtau_out) *dtau_out = d;
+        if (!(d > 0.0)) atomicOr(status, 2u);
+    }
+    const long q = blockIdx.x * (long)blockDim.x + threadIdx.x;
+    if (q >= n_interior(g)) return;
+    int i0, i1, i2;
+    const long i = interior_node(g, q, i0, i1, i2);
+    double v[2], w[2];
+#pragma unroll
+    for (int c = 0; c < 2; c++) {
+        const double x0 = xn[c * P + i];
+        v[c] = d * (xmu[c * P + i] - x0);
+        w[c] = x0 + v[c];
+    }
+    put_images<2, 2>(g, GH_DISP, i0 - g.ng, i1 - g.ng, 0, v, disp);
+    if (xnext) put_images<2, 2>(g, GH_MESH, i0 - g.ng, i1 - g.ng, 0, w, xnext);
+}
+
+template <int N>
 static void launch_monitor(const Phys& ph, const Geo& g, const MonitorP& mo, int sigmode, const double* JU,
                            const double* J, double* grad, double* part, int nb, hipStream_t s)
 {
     if (sigmode == 2)
-        hipLaunchKernelGGL((k_monitor_grad<N, D, 2>), dim3(nb), dim3(256), 0, s, ph, g, mo, JU, J, grad, part);
+        hipLaunchKernelGGL((k_monitor_grad<N, 3, 2>), dim3(nb), dim3(256), 0, s, ph, g, mo, JU, J, grad, part);
     else if (sigmode == 1)
-        hipLaunchKernelGGL((k_monitor_grad<N, D, 1>), dim3(nb), dim3(256), 0, s, ph, g, mo, JU, J, grad, part);
+        hipLaunchKernelGGL((k_monitor_grad<N, 3, 1>), dim3(nb), dim3(256), 0, s, ph, g, mo, JU, J, grad, part);
     else
-        hipLaunchKernelGGL((k_monitor_grad<N, D, 0>), dim3(nb), dim3(256), 0, s, ph, g, mo, JU, J, grad, part);
+        hipLaunchKernelGGL((k_monitor_grad<N, 3, 0>), dim3(nb), dim3(256), 0, s, ph, g, mo, JU, J, grad, part);
+}
+
+// the launches of the 2D kernels after the schlieren function
+static hipError_t redistribute2(const Phys& ph, const Geo& g, const MonitorP& mo, int sigmode, const double* JU,
+                                const double* J, const double* xn, double* disp, MeshWork& w, double* dtau_out,
+                                double* resid_out, unsigned* status, hipStream_t s, double* xnext)
+{
+    const dim3 tiles((g.n[0] + TX2 - 1) / TX2, (g.n[1] + TY2 - 1) / TY2);
+    if (tiles.y > 65535) return hipErrorInvalidConfiguration;
+    auto* mon = ph.nspec == 1 ? (sigmode == 2 ? k_monitor2<1, 2> : (sigmode == 1 ? k_monitor2<1, 1> : k_monitor2<1, 0>))
+                              : (sigmode == 2 ? k_monitor2<2, 2> : (sigmode == 1 ? k_monitor2<2, 1> : k_monitor2<2, 0>));
+    hipLaunchKernelGGL(mon, tiles, dim3(256), 0, s, ph, g, mo, JU, J, w.grad, w.scal);
+    // (no filter pass: theta alone)
+    double *th = w.th0, *th2 = w.th1;
+    for (int left = mo.n_smooth, first = 1; first || left > 0; first = 0) {
+        const int steps = std::min(left, STEPS2);
+        hipLaunchKernelGGL(k_filter2, tiles, dim3(256), 0, s, g, mo, first ? w.grad : th,
+                           first ? w.scal : (const double*)nullptr, th2, steps);
+        std::swap(th, th2);
+        left -= steps;
+    }
+    const double* xcur = xn;
+    double *xa = w.xa, *xb = w.xb;
+    unsigned long long* key = reinterpret_cast<unsigned long long*>(w.scal + 8);
+    for (int nu = 0; nu < mo.n_sweeps;) {
+        const int steps = std::min(mo.n_sweeps - nu, STEPS2);
+        const bool last = nu + steps == mo.n_sweeps;
+        hipLaunchKernelGGL(k_jacobi2, tiles, dim3(256), 0, s, g, th, xcur, xa, steps,
+                           resid_out ? resid_out + nu : nullptr, last ? xn : (const double*)nullptr, key);
+        xcur = xa;
+        std::swap(xa, xb);
+        nu += steps;
+    }
+    const long nint = (long)g.n[0] * g.n[1];
+    hipLaunchKernelGGL(k_disp2, dim3((unsigned)((nint + 255) / 256)), dim3(256), 0, s, g, xcur, xn, key, w.scal + 6,
+                       dtau_out, disp, xnext, status);
+    return hipGetLastError();
 }
 
 hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in, const double* JU,
@@ -1598,12 +1945,11 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
     }
     // the monitor kernels carry only the variables they are asked for
     const int sigmode = ext ? 2 : (press ? 1 : 0);
-    if (use_phi) {
-        ES_DISPATCH_ND(ph, g, launch_schlieren, ph, g, mo, JU, J, w.th1, w.part + 6 * RED_BLOCKS, w.scal + 7,
-                       w.phi, nb, gi, s);
-        const hipError_t e0 = fill_ghosts(g, w.phi, 1, GH_PLAIN, s);
-        if (e0 != hipSuccess) return e0;
-    }
+    hipLaunchKernelGGL(k_mesh_begin, dim3(1), dim3(256), 0, s, w.scal, g.dim == 2 ? resid_out : nullptr, mo.n_sweeps);
+    if (use_phi)
+        ES_DISPATCH_ND(ph, g, launch_schlieren, ph, g, mo, JU, J, w.th1, w.scal + 7, w.phi, nb, gi, s);
+    if (g.dim == 2)
+        return redistribute2(ph, g, mo, sigmode, JU, J, xn, disp, w, dtau_out, resid_out, status, s, xnext);
     // monitor and its global maxima
     if (march) {
         auto* kern = ph.nspec == 1
@@ -1611,7 +1957,7 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
                          : (sigmode == 2 ? k_monitor_grad3<2, 2> : (sigmode == 1 ? k_monitor_grad3<2, 1> : k_monitor_grad3<2, 0>));
         hipLaunchKernelGGL(kern, jgrid, dim3(256), 0, s, ph, g, mo, JU, J, w.grad, w.part, jchunk);
     } else {
-        ES_DISPATCH_ND(ph, g, launch_monitor, ph, g, mo, sigmode, JU, J, w.grad, w.part, nb, s);
+        (ph.nspec == 1 ? launch_monitor<1> : launch_monitor<2>)(ph, g, mo, sigmode, JU, J, w.grad, w.part, nb, s);
     }
     for (int q = 0; q < (mo.form ? 2 * mo.nsig : mo.nsig); q++)
         hipLaunchKernelGGL(k_finish<RED_MAX>, dim3(1), dim3(256), 0, s, w.part + q * RED_BLOCKS,
@@ -1640,8 +1986,6 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
     for (int nu = 0; nu < mo.n_sweeps; nu++) {
         if (march)
             hipLaunchKernelGGL(k_jacobi3, jgrid, dim3(256), 0, s, g, th, xcur, xa, w.part, jchunk);
-        else if (g.dim == 2)
-            hipLaunchKernelGGL(k_jacobi<2>, dim3(nb), dim3(256), 0, s, g, th, xcur, xa, w.part, nzs, nys, nxs);
         else
             hipLaunchKernelGGL(k_jacobi<3>, dim3(nb), dim3(256), 0, s, g, th, xcur, xa, w.part, nzs, nys, nxs);
         if (march && (e = fill_ghosts(g, xa, g.dim, GH_MESH, s)) != hipSuccess) return e;
@@ -1652,10 +1996,7 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
         std::swap(xa, xb);
     }
     // limiter and displacement
-    if (g.dim == 2)
-        hipLaunchKernelGGL(k_limiter<2>, dim3(nb), dim3(256), 0, s, g, xcur, xn, w.part);
-    else
-        hipLaunchKernelGGL(k_limiter<3>, dim3(nb), dim3(256), 0, s, g, xcur, xn, w.part);
+    hipLaunchKernelGGL(k_limiter<3>, dim3(nb), dim3(256), 0, s, g, xcur, xn, w.part);
     hipLaunchKernelGGL(k_finish<RED_MIN>, dim3(1), dim3(256), 0, s, w.part, nb, w.scal + 6, 2, 0.0, status);
     hipLaunchKernelGGL(k_disp, dim3(gi), dim3(256), 0, s, g, xcur, xn, w.scal + 6, disp, xnext, nzs, nys, nxs);
     if (dtau_out && (e = copy(w.scal + 6, dtau_out, 1, s)) != hipSuccess) return e;
