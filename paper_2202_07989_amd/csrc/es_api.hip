@@ -189,6 +189,8 @@ int alloc_workspace(es_ctx* c)
     if (!rc) rc = dalloc(&c->mx, d * P);
     if (!rc) rc = dalloc(&c->reuse, 1);
     if (rc) return rc;
+    const int one = 1;   // the reuse flag (step_begin only clears it)
+    if (hipMemcpy(c->reuse, &one, sizeof(int), hipMemcpyHostToDevice) != hipSuccess) return ES_EHIP;
     if (fill_value(c->mesh.th0, P, 1.0, 0) != hipSuccess) return ES_EHIP;
     if (fill_value(c->mesh.th1, P, 1.0, 0) != hipSuccess) return ES_EHIP;
     if (fill_value(c->mx, d * P, std::numeric_limits<double>::quiet_NaN(), 0) != hipSuccess) return ES_EHIP;
@@ -392,14 +394,12 @@ int es_step(es_ctx* c, const es_monitor* m, double cfl, double dt_fixed, int mov
         if ((expr) != hipSuccess) return ES_EHIP;     \
     } while (0)
 
-    ES_TRY(fill_state(g, c->inflow, JU, J, nc, ph.nspec, s));
-    ES_TRY(fill_ghosts(g, x, d, GH_MESH, s));
-    // x^n is as a rule the previous step's c = 1 stage mesh, whose metrics
-    // that step left in jxx beside a copy mx of the mesh: a device-side
-    // comparison of x^n with mx (before the mesh step below overwrites mx)
-    // decides whether they are reused or formed afresh, so a caller may
-    // change x between steps
-    ES_TRY(same_values(x, c->mx, d * P, c->reuse, s));
+    // ghost layers of the state and of x.  x^n is as a rule the previous step's
+    // c = 1 stage mesh, whose metrics that step left in jxx beside a copy mx of
+    // the mesh: the same launch compares x^n with mx (before the mesh step below
+    // overwrites mx) and decides whether they are reused or formed afresh, so a
+    // caller may change x between steps
+    ES_TRY(step_begin(g, c->inflow, JU, J, x, c->mx, c->reuse, nc, ph.nspec, s));
     const double* disp = nullptr;
     if (move_mesh) {
         // the displacement, and in mx the c = 1 stage mesh x^{n+1} = x^n + disp
@@ -431,6 +431,11 @@ int es_step(es_ctx* c, const es_monitor* m, double cfl, double dt_fixed, int mov
     double* accs[3][2] = {{c->bufA, c->bufA + nc * P}, {c->bufB, c->bufB + nc * P}, {c->bufA, c->bufA + nc * P}};
     double* outs[3][2] = {{c->bufA, c->bufA + nc * P}, {c->bufB, c->bufB + nc * P}, {JU, J}};
     double* jxs[3] = {c->jxx, c->jxx, disp ? c->jxx2 : c->jxx};
+    // 2D stages write their own ghost images where a node's image needs no
+    // other node (3D ones are bound by their traffic and gain nothing from it)
+    int images = d == 2;
+    for (int k = 0; k < d; k++)
+        for (int q = 0; q < 2; q++) images = images && (g.bc[k][q] == BC_PERIODIC || g.bc[k][q] == BC_REFLECT);
     for (int st = 0; st < 3; st++) {
         // stage mesh x^n + c_s disp (stage 0 has it from the pass above).
         // The c = 1 stage mesh is x^{n+1}, formed once in mx by the mesh step;
@@ -441,17 +446,15 @@ int es_step(es_ctx* c, const es_monitor* m, double cfl, double dt_fixed, int mov
         } else if (disp && st == 2) {
             ES_TRY(metrics(ph, g, x, disp, Cs[st], dt, c->jxx2, c->jxt, 0, c->G, s));
         }
-        RkArgs rk{JU, J, dt, A[st], B[st], outs[st][0], outs[st][1], (disp && st == 0) ? dt : nullptr};
+        RkArgs rk{JU, J, dt, A[st], B[st], outs[st][0], outs[st][1], (disp && st == 0) ? dt : nullptr, images};
         ES_TRY(launch_rhs(ph, g, mixed, inU, inJ, jxs[st], disp ? c->jxt : nullptr, accs[st][0], accs[st][1],
                           &rk, c->status, s));
-        ES_TRY(fill_state(g, c->inflow, outs[st][0], outs[st][1], nc, ph.nspec, s));
+        if (!images) ES_TRY(fill_state(g, c->inflow, outs[st][0], outs[st][1], nc, ph.nspec, s));
         inU = outs[st][0];
         inJ = outs[st][1];
     }
-    // x^{n+1} with its ghost layers
-    if (disp) ES_TRY(copy(c->mx, x, d * P, s));
-    if (dt_dev) ES_TRY(copy(dt, dt_dev, 1, s));
-    if (dtau_dev) ES_TRY(copy(dtau, dtau_dev, 1, s));
+    // x^{n+1} with its ghost layers, and the scalars
+    ES_TRY(step_end(dt, dt_dev, dtau, dtau_dev, c->mx, x, disp ? d * P : 0, c->reuse, s));
 #undef ES_TRY
     return ES_OK;
 }

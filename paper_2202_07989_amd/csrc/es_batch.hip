@@ -58,8 +58,8 @@ k_stage2d_batched(Phys ph, const Geo* __restrict__ geos, const int4* __restrict_
                 // the node and its ghost images
                 const double o = ca * qn[i] + cb * (qs[i] + dt * L);
                 double* to = cc < NC ? JUo + cc * P : Jo;
-                const int gx = ox + ni, gy = oy + nj;
                 to[gn] = o;
+                const int gx = ox + ni, gy = oy + nj;
                 if (gx < ng || gx >= nx - ng || gy < ng || gy >= ny - ng) {
 #pragma unroll 1
                     for (int k = 0; k < 9; k++) {

@@ -48,6 +48,39 @@ __device__ __forceinline__ long dir_stride(const Geo& g, int k)
     return k == 0 ? 1L : (k == 1 ? (long)g.np[0] : (long)g.np[0] * g.np[1]);
 }
 
+// ghost position of interior coordinate i (0 .. n-1) of direction k on side sd
+// (-1 / 0 / +1; 0: i itself); false where it has none in the ng layers
+__device__ __forceinline__ bool image_pos(const Geo& g, int k, int i, int sd, int& pos)
+{
+    const int n = g.n[k];
+    if (sd == 0) {
+        pos = i;
+        return true;
+    }
+    const bool per = g.bc[k][sd > 0] == BC_PERIODIC;
+    pos = sd < 0 ? (per ? i - n : -1 - i) : (per ? i + n : 2 * n - 1 - i);
+    return sd < 0 ? pos >= -g.ng : pos < n + g.ng;
+}
+
+// calls f(side, padded index) for every ghost image of the D-dimensional
+// interior node (i0, i1, i2)
+template <int D, typename F>
+__device__ __forceinline__ void for_images(const Geo& g, int i0, int i1, int i2, F f)
+{
+    const int ng = g.ng;
+    if (i0 >= ng && i0 < g.n[0] - ng && i1 >= ng && i1 < g.n[1] - ng && (D == 2 || (i2 >= ng && i2 < g.n[2] - ng)))
+        return;
+#pragma unroll 1
+    for (int q = 0; q < (D == 3 ? 27 : 9); q++) {
+        const int side[3] = {q % 3 - 1, (q / 3) % 3 - 1, D == 3 ? q / 9 - 1 : 0};
+        int p0, p1, p2 = 0;
+        if (!side[0] && !side[1] && !side[2]) continue;
+        if (!image_pos(g, 0, i0, side[0], p0) || !image_pos(g, 1, i1, side[1], p1)) continue;
+        if (D == 3 && !image_pos(g, 2, i2, side[2], p2)) continue;
+        f(side, node_index(g, p0 + ng, p1 + ng, p2 + (D == 3 ? ng : 0)));
+    }
+}
+
 // --------------------------------------------------------------------------
 // reciprocal of a finite, normal, nonzero x: the hardware estimate refined
 // by Newton steps r <- r (2 - x r) (two in FP64, one in FP32), within about

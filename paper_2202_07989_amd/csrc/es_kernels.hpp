@@ -54,8 +54,14 @@ hipError_t fill_state(const Geo& g, const InflowStates& in, double* JU, double* 
                       hipStream_t s);
 hipError_t copy(const double* src, double* dst, long n, hipStream_t s);
 hipError_t fill_value(double* dst, long n, double v, hipStream_t s);
-// *flag = 1 if a and b hold the same n values, else 0 (device-side; NaN never matches)
-hipError_t same_values(const double* a, const double* b, long n, int* flag, hipStream_t s);
+// start of a time step: ghost layers of the state and of x; *same (set by
+// step_end and at creation) cleared unless x equals the kept mesh mx
+hipError_t step_begin(const Geo& g, const InflowStates& in, double* JU, double* J, double* x, const double* mx,
+                      int* same, int nc, int nspec, hipStream_t s);
+// its end: the scalars to the caller's (each may be null), n values of mx to x
+// (n = 0 on a fixed mesh), *same set
+hipError_t step_end(const double* dt, double* dt_out, const double* dtau, double* dtau_out, const double* mx, double* x,
+                    long n, int* same, hipStream_t s);
 // dst = src when *flag is 0
 hipError_t copy_unless(const double* src, double* dst, long n, const int* flag, hipStream_t s);
 hipError_t set_scalar(double* dst, double v, hipStream_t s);
@@ -91,6 +97,9 @@ struct RkArgs {
     // when set, jxt holds -sum_j disp_j J dxi_k/dx_j and the sweeps divide it
     // by this device scalar (the step's dt) as they stage it
     const double* tdiv = nullptr;
+    // 2D: also write the ghost images of every node (grids whose faces are
+    // periodic or reflecting)
+    int images = 0;
 };
 
 hipError_t launch_rhs(const Phys& ph, const Geo& g, int mixed, const double* JU, const double* J,

@@ -180,12 +180,21 @@ k_rhs_xy(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict
                 qn[i] = (isJ ? nJ : nU + cc * P)[gn];
             }
         },
-        [&](int i, int cc, long gn, int, int, double o) {
+        [&](int i, int cc, long gn, int ni, int nj, double o) {
             if constexpr (ACC) o = o + ac[i];
             if constexpr (MODE == MODE_RK) o = rk.a * qn[i] + rk.b * (qs[i] + dt * o);
             double* to = cc < NC ? (MODE == MODE_RK && rk.outU ? rk.outU : accU) + cc * P
                                  : (MODE == MODE_RK && rk.outJ ? rk.outJ : accJ);
             to[gn] = o;
+            if constexpr (D == 2 && MODE == MODE_RK) {
+                if (rk.images)   // J and J U wrapped or mirrored, momentum k negated across a wall of direction k
+                    for_images<2>(g, ox + ni, oy + nj, 0, [&](const int (&side)[3], long gi) {
+                        const int k = cc - N;
+                        const bool neg = k >= 0 && k < 2 && cc < NC && side[k == 1] != 0 &&
+                                         g.bc[k == 1][side[k == 1] > 0] == BC_REFLECT;
+                        to[gi] = neg ? -o : o;
+                    });
+            }
         });
     if (bad) atomicOr(status, bad);
 }
