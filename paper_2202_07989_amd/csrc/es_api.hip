@@ -178,7 +178,6 @@ int alloc_workspace(es_ctx* c)
     if (!rc) rc = dalloc(&c->mesh.xa, d * P);
     if (!rc) rc = dalloc(&c->mesh.xb, d * P);
     if (!rc) rc = dalloc(&c->mesh.phi, P);
-    if (!rc) rc = dalloc(&c->mesh.part, 8 * 2048);
     if (!rc) rc = dalloc(&c->mesh.scal, 16);
     if (!rc) rc = dalloc(&c->bufA, (nc + 1) * P);
     if (!rc) rc = dalloc(&c->bufB, (nc + 1) * P);
@@ -266,7 +265,7 @@ int es_destroy(es_ctx* c)
 {
     if (!c) return ES_EINVAL;
     void* bufs[] = {c->status, c->scal, c->part, c->G, c->mesh.grad, c->mesh.th0, c->mesh.th1,
-                    c->mesh.xa, c->mesh.xb, c->mesh.phi, c->mesh.part, c->mesh.scal, c->bufA,
+                    c->mesh.xa, c->mesh.xb, c->mesh.phi, c->mesh.scal, c->bufA,
                     c->bufB, c->jxx, c->jxt, c->disp, c->mx, c->jxx2, c->reuse};
     for (void* p : bufs)
         if (p) (void)hipFree(p);

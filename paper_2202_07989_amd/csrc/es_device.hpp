@@ -625,15 +625,14 @@ __device__ __forceinline__ double block_reduce(double v)
 // (x, y) tiles at the usual grids), so the in-plane neighbour rows that
 // adjacent tiles read from each other come from one L2 (the 3D metrics take
 // 8% less time).  Any grid size: the first nb % 8 XCDs take one tile more.
-__device__ __forceinline__ void xcd_tile(int& bx, int& by, int& bz)
+// (one block index everywhere: a grid's second and third extents stop at 65535)
+__device__ __forceinline__ void xcd_tile(unsigned gx, unsigned gy, int& bx, int& by, int& bz)
 {
-    const unsigned gx = gridDim.x, gy = gridDim.y, nb = gx * gy * gridDim.z;
-    const unsigned L = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-    const unsigned q = nb / 8, r = nb % 8, c = L % 8;
-    const unsigned T = c * q + (c < r ? c : r) + L / 8;
-    bx = (int)(T % gx);
-    by = (int)((T / gx) % gy);
-    bz = (int)(T / (gx * gy));
+    const unsigned L = blockIdx.x, q = gridDim.x / 8, r = gridDim.x % 8, c = L % 8;
+    const unsigned T = c * q + (c < r ? c : r) + L / 8, row = T / gx;
+    bx = (int)(T - row * gx);
+    by = (int)(row % gy);
+    bz = (int)(row / gy);
 }
 
 // Tile of this block for plane-tile kernels whose work differs from tile to
@@ -644,19 +643,13 @@ __device__ __forceinline__ void xcd_tile(int& bx, int& by, int& bz)
 // columns then stay with one XCD, 2.69).  What is left past the last multiple
 // of 8 keeps launch order.
 template <int D>
-__device__ __forceinline__ void xcd_plane(int& bx, int& by, int& bz)
+__device__ __forceinline__ void xcd_plane(unsigned gx, unsigned gy, int& bx, int& by, int& bz)
 {
-    const unsigned gx = gridDim.x, gy = gridDim.y, pl = D == 3 ? gx * gy : gx, npl = D == 3 ? gridDim.z : gy;
-    const unsigned L = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-    bx = (int)blockIdx.x;
-    by = (int)blockIdx.y;
-    bz = (int)blockIdx.z;
-    if (L < npl / 8 * 8 * pl) {
-        const unsigned i = L >> 3, p = i / pl, r = i - p * pl, q = p * 8 + (L & 7);
-        by = (int)(D == 3 ? r / gx : q);
-        bz = (int)(D == 3 ? q : 0);
-        bx = (int)(r % gx);
-    }
+    const unsigned L = blockIdx.x, pl = D == 3 ? gx * gy : gx, dealt = gridDim.x / pl / 8 * 8 * pl;
+    const unsigned i = L < dealt ? L >> 3 : L, p = i / pl, r = i - p * pl, q = L < dealt ? p * 8 + (L & 7) : p;
+    by = (int)(D == 3 ? r / gx : q);
+    bz = (int)(D == 3 ? q : 0);
+    bx = (int)(D == 3 ? r % gx : r);
 }
 
 }  // namespace es

@@ -445,7 +445,7 @@ k_metric_prod3(Geo g, Phys ph, const double* __restrict__ xn, const double* __re
     const int np0 = g.np[0], np1 = g.np[1], np2 = g.np[2];
     const int tx = threadIdx.x, ty = threadIdx.y;
     int bx, by, bz;
-    xcd_tile(bx, by, bz);
+    xcd_tile((np0 + MT - 1) / MT, (np1 + MT - 1) / MT, bx, by, bz);
     const int x0 = bx * MT, y0 = by * MT;
     const int x = x0 + tx, y = y0 + ty;
     const int zc0 = bz * zchunk, zc1 = min(zc0 + zchunk, np2);
@@ -531,7 +531,7 @@ k_metric3(Geo g, Phys ph, const double* __restrict__ disp, const double* __restr
     const long P = g.P;
     const int np0 = g.np[0], np1 = g.np[1];
     int bx, by, bz;
-    xcd_tile(bx, by, bz);
+    xcd_tile((g.n[0] + MX - 1) / MX, (g.n[1] + MY - 1) / MY, bx, by, bz);
     const int tx = threadIdx.x, ty = threadIdx.y;
     const int xt = g.ng + bx * MX, yt = g.ng + by * MY;
     const int x = xt + tx, y = yt + ty;
@@ -772,12 +772,12 @@ hipError_t metrics(const Phys& ph, const Geo& g, const double* xn, const double*
         const int bx1 = (g.np[0] + MT - 1) / MT, by1 = (g.np[1] + MT - 1) / MT;
         const int nc1 = std::max(1, std::min(g.np[2] / 32, (1024 + bx1 * by1 - 1) / (bx1 * by1)));
         const int zc1 = (g.np[2] + nc1 - 1) / nc1;
-        hipLaunchKernelGGL(k_metric_prod3, dim3(bx1, by1, (g.np[2] + zc1 - 1) / zc1), dim3(MT, MT), 0, s,
+        hipLaunchKernelGGL(k_metric_prod3, dim3(bx1 * by1 * ((g.np[2] + zc1 - 1) / zc1)), dim3(MT, MT), 0, s,
                            g, ph, xn, dx, cs, G, zc1, reuse);
         const int bx2 = (g.n[0] + MX - 1) / MX, by2 = (g.n[1] + MY - 1) / MY;
         const int nc2 = std::max(1, std::min(g.n[2] / 16, (4096 + bx2 * by2 - 1) / (bx2 * by2)));
         const int zc2 = (g.n[2] + nc2 - 1) / nc2;
-        hipLaunchKernelGGL(k_metric3, dim3(bx2, by2, (g.n[2] + zc2 - 1) / zc2), dim3(MX, MY), 0, s, g, ph,
+        hipLaunchKernelGGL(k_metric3, dim3(bx2 * by2 * ((g.n[2] + zc2 - 1) / zc2)), dim3(MX, MY), 0, s, g, ph,
                            disp, G, dt_dev, jxx, jxt, zc2, reuse);
         if (reuse && jxt)
             hipLaunchKernelGGL(k_vcl, dim3(grid_for(nint)), dim3(256), 0, s, g, disp, dt_dev, jxx, jxt, reuse);
@@ -1073,7 +1073,7 @@ hipError_t entropy_sum(const Phys& ph, const Geo& g, const double* JU, const dou
 // ---------------------------------------------------------------------------
 // mesh redistribution (Section 4)
 // ---------------------------------------------------------------------------
-// The 2D kernels keep a maximum or minimum over all blocks in a device scalar
+// The kernels keep a maximum or minimum over all blocks in a device scalar
 // that the call's first launch resets (order does not matter, so the result
 // is the two-pass reduction's): non-negative doubles compare like their bits.
 __device__ __forceinline__ void scalar_max(double* a, double v)
@@ -1105,8 +1105,7 @@ __global__ void k_mesh_begin(double* __restrict__ scal, double* __restrict__ res
 }
 
 // |grad_xi sigma| by second-order central differences, for each monitor
-// variable; per-block maxima into part[s * RED_BLOCKS + block].  The form
-// with a Laplacian term also writes |lap_xi sigma| (second-order central
+// variable, and its maximum.  The form with a Laplacian term also writes |lap_xi sigma| (second-order central
 // differences) as channel nsig + s.  Variables: 0 rho, 1 rho_1, 2 rho_2,
 // 3 p, 4 the speed |v| (the u of Example 5.9's monitor), 5 the schlieren
 // function of eq schlieren, read from its array (with ghost layers).
@@ -1146,64 +1145,22 @@ __device__ __forceinline__ double sigma_of(const Phys& ph, const double* JU, con
     return s.p;
 }
 
-template <int N, int D, int SIG>
-__global__ void k_monitor_grad(Phys ph, Geo g, MonitorP mo, const double* __restrict__ JU,
-                               const double* __restrict__ Jv, double* __restrict__ grad,
-                               double* __restrict__ part)
-{
-    const long P = g.P;
-    const long nint = n_interior(g);
-    double gm[MON_CH] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < nint; q += (long)gridDim.x * blockDim.x) {
-        int i0, i1, i2;
-        const long i = interior_node(g, q, i0, i1, i2);
-        for (int s = 0; s < mo.nsig; s++) {
-            double g2 = 0.0, lap = 0.0;
-            const double sc = mo.form ? sigma_of<N, D, SIG>(ph, JU, Jv, P, i, mo.sigma[s], mo.phi) : 0.0;
-#pragma unroll
-            for (int k = 0; k < D; k++) {
-                const long st = dir_stride(g, k);
-                const double sp = sigma_of<N, D, SIG>(ph, JU, Jv, P, i + st, mo.sigma[s], mo.phi);
-                const double sm = sigma_of<N, D, SIG>(ph, JU, Jv, P, i - st, mo.sigma[s], mo.phi);
-                const double dk = (sp - sm) / (2.0 * g.dxi[k]);
-                g2 += dk * dk;
-                lap += (sp - 2.0 * sc + sm) / (g.dxi[k] * g.dxi[k]);
-            }
-            const double gv = sqrt(g2);
-            grad[s * P + i] = gv;
-            gm[s] = fmax(gm[s], gv);
-            if (mo.form) {
-                grad[(mo.nsig + s) * P + i] = fabs(lap);
-                gm[mo.nsig + s] = fmax(gm[mo.nsig + s], fabs(lap));
-            }
-        }
-    }
-    const int nch = mo.form ? 2 * mo.nsig : mo.nsig;
-    for (int s = 0; s < MON_CH; s++) {
-        if (s >= nch) break;   // uniform across the block
-        const double r = block_reduce<RED_MAX>(gm[s]);
-        if (threadIdx.x == 0) part[s * RED_BLOCKS + blockIdx.x] = r;
-    }
-}
-
-// 3D monitor gradient walking z (the central differences of k_monitor_grad):
-// each thread owns one (x, y) column of a 64 x 4 block over a chunk of z
+// 3D monitor gradient walking z (second-order central differences): each thread owns one (x, y) column of a 64 x 4 block over a chunk of z
 // planes.  Sigma is evaluated once per node of each plane of the tile plus
 // a 1-node in-plane halo (corners excepted) into a two-plane LDS buffer, so
 // the in-plane neighbours and the plane above come from LDS and sigma at
 // z-1 from a register: 1.5 evaluations per node instead of 5.
-// Per-block maxima go to part[s * RED_BLOCKS + block] in block order.
 template <int N, int SIG>
 __global__ void __launch_bounds__(256)
 k_monitor_grad3(Phys ph, Geo g, MonitorP mo, const double* __restrict__ JU, const double* __restrict__ Jv,
-                double* __restrict__ grad, double* __restrict__ part, int zchunk)
+                double* __restrict__ grad, double* __restrict__ gmax, int zchunk)
 {
     constexpr int D = 3;
     __shared__ double Sg[2][6][66];
     const long P = g.P;
     const int np0 = g.np[0], np1 = g.np[1];
     int bx, by, bz;
-    xcd_tile(bx, by, bz);
+    xcd_tile((g.n[0] + 63) / 64, (g.n[1] + 3) / 4, bx, by, bz);
     const int lx = (int)(threadIdx.x & 63), ly = (int)(threadIdx.x >> 6);
     const int xt = g.ng + bx * 64, yt = g.ng + by * 4;
     const int x = xt + lx, y = yt + ly;
@@ -1249,7 +1206,7 @@ k_monitor_grad3(Phys ph, Geo g, MonitorP mo, const double* __restrict__ JU, cons
                     const double gv = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
                     grad[s * P + i] = gv;
                     mg = fmax(mg, gv);
-                    if (mo.form) {   // the same sum as k_monitor_grad: directions 0, 1, 2 in order
+                    if (mo.form) {   // directions 0, 1, 2 in order
                         double lap = (xp - 2.0 * s0 + xm) / (g.dxi[0] * g.dxi[0]);
                         lap += (yp - 2.0 * s0 + ym) / (g.dxi[1] * g.dxi[1]);
                         lap += (sp - 2.0 * s0 + sm) / (g.dxi[2] * g.dxi[2]);
@@ -1268,75 +1225,18 @@ k_monitor_grad3(Phys ph, Geo g, MonitorP mo, const double* __restrict__ JU, cons
             }
         }
     }
-    const long blk = ((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     const int nch = mo.form ? 2 * mo.nsig : mo.nsig;
 #pragma unroll
     for (int s = 0; s < MON_CH; s++) {
+        if (s >= nch) break;   // uniform
         const double r = block_reduce<RED_MAX>(gm[s]);
-        if (threadIdx.x == 0 && s < nch) part[s * RED_BLOCKS + blk] = r;
-    }
-}
-
-// 3D monitor filter walking z: the weights 2^-(|j|_1 + 3), j in {-1,0,1}^3,
-// are the product of (1/4, 1/2, 1/4) along each direction, so each plane
-// contributes its 9-point in-plane sum q(z') and out = q(z-1)/4 + q(z)/2 +
-// q(z+1)/4 from a 3-plane ring.  The in-plane sums read the plane of the
-// tile plus a 1-node halo staged in LDS.
-__global__ void __launch_bounds__(256)
-k_filter3(Geo g, const double* __restrict__ in, double* __restrict__ out, int zchunk)
-{
-    __shared__ double Fs[6][66];
-    const int np0 = g.np[0], np1 = g.np[1];
-    int bx, by, bz;
-    xcd_tile(bx, by, bz);
-    const int lx = (int)(threadIdx.x & 63), ly = (int)(threadIdx.x >> 6);
-    const int xt = g.ng + bx * 64, yt = g.ng + by * 4;
-    const int x = xt + lx, y = yt + ly;
-    const int zc0 = g.ng + bz * zchunk, zc1 = min(zc0 + zchunk, g.ng + g.n[2]);
-    if (zc0 >= zc1) return;   // uniform over the block
-    const bool inside = x < g.ng + g.n[0] && y < g.ng + g.n[1];
-    const long sz = (long)np0 * np1;
-    auto stage = [&](int zz) {
-        for (int q = threadIdx.x; q < 6 * 66; q += 256) {
-            const int hx = q % 66, hy = q / 66;
-            const int gx = xt - 1 + hx, gy = yt - 1 + hy;
-            if (gx < np0 && gy < np1) Fs[hy][hx] = in[((long)zz * np1 + gy) * np0 + gx];
-        }
-    };
-    auto plane = [&]() {   // in-plane (1/4, 1/2, 1/4) x (1/4, 1/2, 1/4) sum around the own node
-        const int hx = lx + 1, hy = ly + 1;
-        const double r0 = 0.25 * Fs[hy - 1][hx - 1] + 0.5 * Fs[hy - 1][hx] + 0.25 * Fs[hy - 1][hx + 1];
-        const double r1 = 0.25 * Fs[hy][hx - 1] + 0.5 * Fs[hy][hx] + 0.25 * Fs[hy][hx + 1];
-        const double r2 = 0.25 * Fs[hy + 1][hx - 1] + 0.5 * Fs[hy + 1][hx] + 0.25 * Fs[hy + 1][hx + 1];
-        return 0.25 * r0 + 0.5 * r1 + 0.25 * r2;
-    };
-    long i = ((long)zc0 * np1 + y) * np0 + x;
-    double qm = 0.0, q0 = 0.0;
-    stage(zc0 - 1);
-    __syncthreads();
-    if (inside) qm = plane();
-    __syncthreads();
-    stage(zc0);
-    __syncthreads();
-    if (inside) q0 = plane();
-    __syncthreads();
-    for (int z = zc0; z < zc1; z++, i += sz) {
-        stage(z + 1);
-        __syncthreads();
-        if (inside) {
-            const double qp = plane();
-            out[i] = 0.25 * qm + 0.5 * q0 + 0.25 * qp;
-            qm = q0;
-            q0 = qp;
-        }
-        __syncthreads();
+        if (threadIdx.x == 0) scalar_max(gmax + s, r);
     }
 }
 
 // the schlieren function of eq schlieren, Phi = exp(-Psi |grad rho| /
 // max |grad rho|), Psi = (psi_1 rho_1 + psi_2 rho_2) / rho: first
-// |grad_xi rho| (the monitor's central differences) with per-block maxima,
-// then Phi from the global maximum (1 where it is 0)
+// |grad_xi rho| (the monitor's central differences) and its maximum, then Phi from the global maximum (1 where it is 0)
 template <int N, int D>
 __global__ void k_rho_grad(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict__ Jv,
                            double* __restrict__ gr, double* __restrict__ gmax)
@@ -1420,54 +1320,13 @@ __global__ void k_theta(Geo g, MonitorP mo, const double* __restrict__ grad, con
     }
 }
 
-// low-pass filter: sum over j in {0,+-1}^d of (1/2)^(|j|_1 + d) Theta_{i+j}
-__device__ __forceinline__ double filter_node(const Geo& g, const double* in, long i)
+// the movement limiter's bound for one coordinate that moves from x0 to xm
+// between the neighbours lo and hi (1 if it does not move)
+__device__ __forceinline__ double limiter_bound(double xm, double x0, double lo, double hi)
 {
-    const long s0 = 1, s1 = g.np[0], s2 = (long)g.np[0] * g.np[1];
-    const int r2 = g.dim == 3 ? 1 : 0;
-    double s = 0.0;
-    for (int j2 = -r2; j2 <= r2; j2++)
-        for (int j1 = -1; j1 <= 1; j1++)
-            for (int j0 = -1; j0 <= 1; j0++) {
-                const int e = abs(j0) + abs(j1) + abs(j2) + g.dim;
-                s += ldexp(1.0, -e) * in[i + j0 * s0 + j1 * s1 + j2 * s2];
-            }
-    return s;
-}
-
-__global__ void k_filter(Geo g, const double* __restrict__ in, double* __restrict__ out, long nzs, long nys,
-                         long nxs)
-{
-    const long nint = n_interior(g);
-    for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < nint; q += (long)gridDim.x * blockDim.x) {
-        int i0, i1, i2;
-        const long i = interior_node(g, q, i0, i1, i2);
-        out[i] = filter_node(g, in, i);
-    }
-    for (long t = blockIdx.x * (long)blockDim.x + threadIdx.x; t < nzs + nys + nxs;
-         t += (long)gridDim.x * blockDim.x) {
-        int side[3];
-        long di;
-        const long si = shell_image(g, t, nzs, nys, side, di);
-        out[di] = filter_node(g, in, si);
-    }
-}
-
-// the movement limiter's bound at node i for the moved position xm (1 if none)
-template <int D>
-__device__ __forceinline__ double limiter_bound(const Geo& g, const double* __restrict__ xn, long i,
-                                                const double (&xm)[D])
-{
-    const long P = g.P;
-    double b = 1.0;
-#pragma unroll
-    for (int k = 0; k < D; k++) {
-        const long st = dir_stride(g, k);
-        const double x0 = xn[k * P + i], dx = xm[k] - x0;
-        if (dx < 0.0) b = fmin(b, -(x0 - xn[k * P + i - st]) / (2.0 * dx));
-        else if (dx > 0.0) b = fmin(b, (xn[k * P + i + st] - x0) / (2.0 * dx));
-    }
-    return b;
+    const double dx = xm - x0;
+    if (dx < 0.0) return -(x0 - lo) / (2.0 * dx);
+    return dx > 0.0 ? (hi - x0) / (2.0 * dx) : 1.0;
 }
 
 // ---------------------------------------------------------------------------
@@ -1475,12 +1334,23 @@ __device__ __forceinline__ double limiter_bound(const Geo& g, const double* __re
 // microseconds costs more than its work.  Each block owns a 32 x 16 tile and
 // takes several steps of the same kind in LDS on a halo that shrinks by one
 // node a step (the halo's updates are computed again by the neighbours);
-// nodes outside the grid are filled by the face rules and updated like
-// any other, which the updates commute with.  800 x 160, five-variable
+// nodes outside the grid are read through the face rules and updated like
+// any other, which the updates commute with, so no launch needs or writes the
+// ghost layers of Theta or of the moving mesh.  800 x 160, five-variable
 // monitor, 3 filter passes, 10 Jacobi sweeps: 8 launches instead of 29.
 // ---------------------------------------------------------------------------
 constexpr int TX2 = 32, TY2 = 16, STEPS2 = 5;
 constexpr int RX2 = TX2 + 2 * STEPS2, RY2 = TY2 + 2 * STEPS2;
+
+// the tiles of a 2D grid, one block index (a grid's second extent stops at
+// 65535), and the first node of this block's
+static dim3 tiles2(const Geo& g) { return dim3((unsigned)((g.n[0] + TX2 - 1) / TX2) * ((g.n[1] + TY2 - 1) / TY2)); }
+__device__ __forceinline__ void tile2(const Geo& g, int& ox, int& oy)
+{
+    const unsigned tx = (g.n[0] + TX2 - 1) / TX2, row = blockIdx.x / tx;
+    ox = (int)(blockIdx.x - row * tx) * TX2;
+    oy = (int)row * TY2;
+}
 
 // the monitor variables of a tile and its one-node halo, evaluated once per
 // node from one load of its state, then |grad| (and |lap|) at the tile's nodes
@@ -1494,7 +1364,8 @@ k_monitor2(Phys ph, Geo g, MonitorP mo, const double* __restrict__ JU, const dou
     __shared__ double Sg[NV][HY][HX];
     __shared__ double part[4][MON_CH];
     const long P = g.P;
-    const int ox = blockIdx.x * TX2, oy = blockIdx.y * TY2;
+    int ox, oy;
+    tile2(g, ox, oy);
     const double ih0 = 1.0 / (2.0 * g.dxi[0]), ih1 = 1.0 / (2.0 * g.dxi[1]);
     const double il0 = 1.0 / (g.dxi[0] * g.dxi[0]), il1 = 1.0 / (g.dxi[1] * g.dxi[1]);
     // (a monitor may name a variable more than once; NV of them fit at a time)
@@ -1596,7 +1467,8 @@ k_filter2(Geo g, MonitorP mo, const double* __restrict__ in, const double* __res
           double* __restrict__ out, int steps)
 {
     __shared__ double F[2][RY2][RX2];
-    const int ox = blockIdx.x * TX2, oy = blockIdx.y * TY2;
+    int ox, oy;
+    tile2(g, ox, oy);
     const Region2 R(threadIdx.x);
 #pragma unroll
     for (int r = 0; r < R2S; r++) {
@@ -1626,8 +1498,7 @@ k_filter2(Geo g, MonitorP mo, const double* __restrict__ in, const double* __res
     for (int r = 0; r < R2S; r++) {
         const int x = ox + R.x[r] - STEPS2, y = oy + R.y[r] - STEPS2;
         if (R.e[r] > 0 || x >= g.n[0] || y >= g.n[1]) continue;
-        const double v[1] = {F[steps & 1][R.y[r]][R.x[r]]};
-        put_images<2, 1, GH_PLAIN>(g, x, y, 0, v, out);
+        out[(long)(y + g.ng) * g.np[0] + (x + g.ng)] = F[steps & 1][R.y[r]][R.x[r]];
     }
 }
 
@@ -1643,7 +1514,8 @@ k_jacobi2(Geo g, const double* __restrict__ th, const double* __restrict__ xa, d
     __shared__ double Xs[2][2][RY2][RX2];   // buffer, component
     __shared__ double part[NT2 / 64];
     const long P = g.P;
-    const int ox = blockIdx.x * TX2, oy = blockIdx.y * TY2;
+    int ox, oy;
+    tile2(g, ox, oy);
     const Region2 R(threadIdx.x);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
@@ -1711,8 +1583,14 @@ k_jacobi2(Geo g, const double* __restrict__ th, const double* __restrict__ xa, d
         const int x = ox + R.x[r] - STEPS2, y = oy + R.y[r] - STEPS2;
         if (R.e[r] > 0 || x >= g.n[0] || y >= g.n[1]) continue;
         const double v[2] = {Xs[steps & 1][0][R.y[r]][R.x[r]], Xs[steps & 1][1][R.y[r]][R.x[r]]};
-        put_images<2, 2, GH_MESH>(g, x, y, 0, v, xb);
-        if (xn) b = fmin(b, limiter_bound<2>(g, xn, (long)(y + g.ng) * g.np[0] + (x + g.ng), v));
+        const long i = (long)(y + g.ng) * g.np[0] + (x + g.ng);
+        xb[i] = v[0];
+        xb[P + i] = v[1];
+        if (xn) {
+            const long n0 = g.np[0];
+            b = fmin(b, limiter_bound(v[0], xn[i], xn[i - 1], xn[i + 1]));
+            b = fmin(b, limiter_bound(v[1], xn[P + i], xn[P + i - n0], xn[P + i + n0]));
+        }
     }
     if (xn) {
         b = wave_min(b);
@@ -1720,229 +1598,15 @@ k_jacobi2(Geo g, const double* __restrict__ th, const double* __restrict__ xa, d
     }
 }
 
-// one Jacobi update of interior node i
+// disp = Delta_tau (x^[mu] - x_n), and with xnext also x_{n+1} = x_n + disp; 2D with
+// the ghost layers (each ghost node from its image node, as a ghost fill
+// gives it), which a fill follows up in 3D.  The limiter's key is decoded here: Delta_tau = min(1, bound) into
+// dtau and, when given, dtau_out
 template <int D>
-__device__ __forceinline__ void jacobi_node(const Geo& g, const double* th, const double* xa, long i, double* xn)
-{
-    // Theta_{k+-1/2} / dxi_k^2, and one reciprocal of the denominator the D
-    // coordinates share
-    const long P = g.P;
-    double tp[D], tm[D];
-    double den = 0.0;
-#pragma unroll
-    for (int k = 0; k < D; k++) {
-        const long st = dir_stride(g, k);
-        const double w2 = 1.0 / (g.dxi[k] * g.dxi[k]);
-        tp[k] = 0.5 * (th[i] + th[i + st]);
-        tm[k] = 0.5 * (th[i] + th[i - st]);
-        tp[k] *= w2;
-        tm[k] *= w2;
-        den += tp[k] + tm[k];
-    }
-    const double iden = rcp(den);
-#pragma unroll
-    for (int c = 0; c < D; c++) {
-        double num = 0.0;
-#pragma unroll
-        for (int k = 0; k < D; k++) {
-            const long st = dir_stride(g, k);
-            num += tp[k] * xa[c * P + i + st] + tm[k] * xa[c * P + i - st];
-        }
-        xn[c] = num * iden;
-    }
-}
-
-// one Jacobi sweep of the mesh equations, per-block max |x_new - x_old|,
-// with the ghost layers of its output in the same launch: a
-// ghost node takes the update of the interior node it wraps or mirrors to
-// (computed again, with the same arithmetic) under the mesh's ghost rule
-template <int D>
-__global__ void k_jacobi(Geo g, const double* __restrict__ th, const double* __restrict__ xa,
-                         double* __restrict__ xb, double* __restrict__ part, long nzs, long nys, long nxs)
-{
-    const long P = g.P;
-    const long nint = n_interior(g);
-    double r = 0.0;
-    for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < nint; q += (long)gridDim.x * blockDim.x) {
-        int i0, i1, i2;
-        const long i = interior_node(g, q, i0, i1, i2);
-        double xn[D];
-        jacobi_node<D>(g, th, xa, i, xn);
-#pragma unroll
-        for (int c = 0; c < D; c++) {
-            xb[c * P + i] = xn[c];
-            r = fmax(r, fabs(xn[c] - xa[c * P + i]));
-        }
-    }
-    const long total = nzs + nys + nxs;
-    for (long t = blockIdx.x * (long)blockDim.x + threadIdx.x; t < total; t += (long)gridDim.x * blockDim.x) {
-        int d[3];
-        shell_node(g, t, nzs, nys, d);
-        int sidx[3] = {d[0], d[1], d[2]}, side[3] = {0, 0, 0};
-        for (int k = 0; k < D; k++) sidx[k] = ghost_image(g, k, d[k], side[k]);
-        double xn[D];
-        jacobi_node<D>(g, th, xa, node_index(g, sidx[0], sidx[1], sidx[2]), xn);
-        const long di = node_index(g, d[0], d[1], d[2]);
-#pragma unroll
-        for (int c = 0; c < D; c++) xb[c * P + di] = ghost_value(g, GH_MESH, c, side, xn[c]);
-    }
-    r = block_reduce<RED_MAX>(r);
-    if (threadIdx.x == 0) part[blockIdx.x] = r;
-}
-
-// 3D Jacobi sweep (the arithmetic of k_jacobi<3>, term for term), walking
-// z: each thread owns one (x, y) column of a 64 x 4 block over a chunk of z
-// planes; theta and x at z-1 and z+1 come from a 3-plane ring in registers,
-// the in-plane neighbours from the plane's theta and x staged in LDS with a
-// 1-node halo (reading them from the caches instead took 323 against 259 us
-// at 256^3, with 106 registers and four waves per SIMD instead of eight).
-// Per-block residual maxima go to part[] in block order.
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8)))
-k_jacobi3(Geo g, const double* __restrict__ th, const double* __restrict__ xa, double* __restrict__ xb,
-          double* __restrict__ part, int zchunk)
-{
-    // the plane's theta and x of the tile plus a 1-node in-plane halo
-    __shared__ double Ts[6][66];
-    __shared__ double Xs[3][6][66];
-    const long P = g.P;
-    const int np0 = g.np[0], np1 = g.np[1];
-    int bx, by, bz;
-    xcd_tile(bx, by, bz);
-    const int lx = (int)(threadIdx.x & 63), ly = (int)(threadIdx.x >> 6);
-    const int xt = g.ng + bx * 64, yt = g.ng + by * 4;
-    const int x = xt + lx, y = yt + ly;
-    const int zc0 = g.ng + bz * zchunk, zc1 = min(zc0 + zchunk, g.ng + g.n[2]);
-    const bool in = x < g.ng + g.n[0] && y < g.ng + g.n[1];
-    const long sz = (long)np0 * np1;
-    double w2[3];
-#pragma unroll
-    for (int k = 0; k < 3; k++) w2[k] = 1.0 / (g.dxi[k] * g.dxi[k]);
-    double r = 0.0;
-    long i = ((long)zc0 * np1 + y) * np0 + x;
-    double tm1 = 0.0, t0 = 0.0, xm1[3] = {0.0, 0.0, 0.0}, x0[3] = {0.0, 0.0, 0.0};
-    if (in && zc0 < zc1) {
-        tm1 = th[i - sz];
-        t0 = th[i];
-#pragma unroll
-        for (int c = 0; c < 3; c++) {
-            xm1[c] = xa[c * P + i - sz];
-            x0[c] = xa[c * P + i];
-        }
-    }
-    for (int z = zc0; z < zc1; z++, i += sz) {
-        for (int q = threadIdx.x; q < 6 * 66; q += 256) {
-            const int hx = q % 66, hy = q / 66;
-            const int gx = xt - 1 + hx, gy = yt - 1 + hy;
-            if (gx < np0 && gy < np1) {
-                const long gi = ((long)z * np1 + gy) * np0 + gx;
-                Ts[hy][hx] = th[gi];
-#pragma unroll
-                for (int c = 0; c < 3; c++) Xs[c][hy][hx] = xa[c * P + gi];
-            }
-        }
-        __syncthreads();
-        if (in) {
-            const double tp1 = th[i + sz];
-            double xp1[3];
-#pragma unroll
-            for (int c = 0; c < 3; c++) xp1[c] = xa[c * P + i + sz];
-            const int hx = lx + 1, hy = ly + 1;
-            double tp[3], tm[3];
-            tp[0] = 0.5 * (t0 + Ts[hy][hx + 1]);
-            tm[0] = 0.5 * (t0 + Ts[hy][hx - 1]);
-            tp[1] = 0.5 * (t0 + Ts[hy + 1][hx]);
-            tm[1] = 0.5 * (t0 + Ts[hy - 1][hx]);
-            tp[2] = 0.5 * (t0 + tp1);
-            tm[2] = 0.5 * (t0 + tm1);
-            double den = 0.0;
-#pragma unroll
-            for (int k = 0; k < 3; k++) {
-                tp[k] *= w2[k];
-                tm[k] *= w2[k];
-                den += tp[k] + tm[k];
-            }
-            const double iden = rcp(den);
-#pragma unroll
-            for (int c = 0; c < 3; c++) {
-                double num = tp[0] * Xs[c][hy][hx + 1] + tm[0] * Xs[c][hy][hx - 1];
-                num += tp[1] * Xs[c][hy + 1][hx] + tm[1] * Xs[c][hy - 1][hx];
-                num += tp[2] * xp1[c] + tm[2] * xm1[c];
-                const double xn = num * iden;
-                xb[c * P + i] = xn;
-                r = fmax(r, fabs(xn - x0[c]));
-            }
-            tm1 = t0;
-            t0 = tp1;
-#pragma unroll
-            for (int c = 0; c < 3; c++) {
-                xm1[c] = x0[c];
-                x0[c] = xp1[c];
-            }
-        }
-        __syncthreads();
-    }
-    r = block_reduce<RED_MAX>(r);
-    if (threadIdx.x == 0) part[((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = r;
-}
-
-// movement limiter: per-block min of the bounds (1 if none)
-template <int D>
-__global__ void k_limiter(Geo g, const double* __restrict__ xmu, const double* __restrict__ xn,
-                          double* __restrict__ part)
-{
-    const long P = g.P;
-    const long nint = n_interior(g);
-    double b = 1.0;
-    for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < nint; q += (long)gridDim.x * blockDim.x) {
-        int i0, i1, i2;
-        const long i = interior_node(g, q, i0, i1, i2);
-        double xm[D];
-#pragma unroll
-        for (int k = 0; k < D; k++) xm[k] = xmu[k * P + i];
-        b = fmin(b, limiter_bound<D>(g, xn, i, xm));
-    }
-    b = block_reduce<RED_MIN>(b);
-    if (threadIdx.x == 0) part[blockIdx.x] = b;
-}
-
-// disp = Delta_tau (x^[mu] - x_n) with its ghost layers; with xnext, also
-// x_{n+1} = x_n + disp with the mesh's ghost layers (each ghost node from
-// the sum at its image node, as a ghost fill of x_{n+1} gives it)
 __global__ void k_disp(Geo g, const double* __restrict__ xmu, const double* __restrict__ xn,
-                       const double* __restrict__ dtau, double* __restrict__ disp, double* __restrict__ xnext,
-                       long nzs, long nys, long nxs)
-{
-    const long P = g.P;
-    const long nint = n_interior(g);
-    const double d = *dtau;
-    for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < nint; q += (long)gridDim.x * blockDim.x) {
-        int i0, i1, i2;
-        const long i = interior_node(g, q, i0, i1, i2);
-        for (int c = 0; c < g.dim; c++) {
-            const double v = d * (xmu[c * P + i] - xn[c * P + i]);
-            disp[c * P + i] = v;
-            if (xnext) xnext[c * P + i] = xn[c * P + i] + v;
-        }
-    }
-    for (long t = blockIdx.x * (long)blockDim.x + threadIdx.x; t < nzs + nys + nxs;
-         t += (long)gridDim.x * blockDim.x) {
-        int side[3];
-        long di;
-        const long si = shell_image(g, t, nzs, nys, side, di);
-        for (int c = 0; c < g.dim; c++) {
-            const double v = d * (xmu[c * P + si] - xn[c * P + si]);
-            disp[c * P + di] = ghost_value(g, GH_DISP, c, side, v);
-            if (xnext) xnext[c * P + di] = ghost_value(g, GH_MESH, c, side, xn[c * P + si] + v);
-        }
-    }
-}
-
-// the same in 2D, a node and its images a thread; the limiter's key is
-// decoded here (Delta_tau into dtau and, when given, dtau_out)
-__global__ void k_disp2(Geo g, const double* __restrict__ xmu, const double* __restrict__ xn,
-                        const unsigned long long* __restrict__ bound, double* __restrict__ dtau,
-                        double* __restrict__ dtau_out, double* __restrict__ disp, double* __restrict__ xnext,
-                        unsigned* __restrict__ status)
+                       const unsigned long long* __restrict__ bound, double* __restrict__ dtau,
+                       double* __restrict__ dtau_out, double* __restrict__ disp, double* __restrict__ xnext,
+                       unsigned* __restrict__ status)
 {
     const long P = g.P;
     const double d = fmin(1.0, order_value(*bound));
@@ -1955,15 +1619,280 @@ __global__ void k_disp2(Geo g, const double* __restrict__ xmu, const double* __r
     if (q >= n_interior(g)) return;
     int i0, i1, i2;
     const long i = interior_node(g, q, i0, i1, i2);
-    double v[2], w[2];
+    const int z = D == 3 ? i2 - g.ng : 0;
+    double v[D], w[D];
 #pragma unroll
-    for (int c = 0; c < 2; c++) {
+    for (int c = 0; c < D; c++) {
         const double x0 = xn[c * P + i];
         v[c] = d * (xmu[c * P + i] - x0);
         w[c] = x0 + v[c];
     }
-    put_images<2, 2, GH_DISP>(g, i0 - g.ng, i1 - g.ng, 0, v, disp);
-    if (xnext) put_images<2, 2, GH_MESH>(g, i0 - g.ng, i1 - g.ng, 0, w, xnext);
+    if constexpr (D == 3) {   // (the images a thread cost 108 us at 256^3, the fill 45)
+#pragma unroll
+        for (int c = 0; c < D; c++) {
+            disp[c * P + i] = v[c];
+            if (xnext) xnext[c * P + i] = w[c];
+        }
+    } else {
+        put_images<D, D, GH_DISP>(g, i0 - g.ng, i1 - g.ng, z, v, disp);
+        if (xnext) put_images<D, D, GH_MESH>(g, i0 - g.ng, i1 - g.ng, z, w, xnext);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// 3D: bound by HBM, so several filter passes or Jacobi sweeps walk z together.  A
+// block owns TX x TY columns over a chunk of z planes; every thread owns one
+// column of the tile plus a halo of S nodes.  Step s of plane z runs as soon as
+// step s - 1 has reached plane z + 1; the planes it needs along z are the
+// thread's own registers, those in the plane are in LDS (double-buffered, one
+// barrier a plane), and its halo is one node narrower.  Nodes outside the grid
+// are read through the face rules, as in 2D.  A launch then reads and writes a
+// field once for S steps: at 256^3 three filter passes take 258 us instead
+// of 3 x 97 us and two Jacobi sweeps 314 us instead of 2 x 307 us (each with the
+// ghost fill that they needed).
+// ---------------------------------------------------------------------------
+template <int TX, int TY, int S>
+struct Column3 {
+    static constexpr int HX = TX + 2 * S, HY = TY + 2 * S, HN = HX * HY, NT = (HN + 63) / 64 * 64;
+};
+
+// z chunks of nz planes for `cols` columns of blocks, two blocks a compute
+// unit: the number that leaves the shortest walk (rounds of blocks times planes
+// a block), each walk taking `extra` planes more than it writes
+static int z_chunk(int nz, long cols, int extra)
+{
+    long best = -1;
+    int chunk = nz;
+    for (int c = 1; c <= std::max(1, nz / 8); c++) {
+        const int zc = (nz + c - 1) / c;
+        const long walk = ((cols * ((nz + zc - 1) / zc) + 511) / 512) * (zc + extra);
+        if (best < 0 || walk < best) {
+            best = walk;
+            chunk = zc;
+        }
+    }
+    return chunk;
+}
+
+// S passes of the low-pass filter: the weights 2^-(|j|_1 + 3), j in {-1,0,1}^3, are
+// the product of (1/4, 1/2, 1/4) along each direction, so a pass is the
+// in-plane sum q of each plane and out = q(z-1)/4 + q(z)/2 + q(z+1)/4.  With
+// gmax, theta is formed from the monitor's gradients `in` first
+template <int TX, int TY, int S>
+__global__ void __launch_bounds__((Column3<TX, TY, S>::NT))
+k_filter3(Geo g, MonitorP mo, const double* __restrict__ in, const double* __restrict__ gmax,
+          double* __restrict__ out, int zchunk)
+{
+    constexpr int HX = Column3<TX, TY, S>::HX, HN = Column3<TX, TY, S>::HN;
+    __shared__ double F[S][2][HN];   // F[s]: the field after s passes, two planes
+    int bx, by, bz;
+    xcd_tile((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, bx, by, bz);
+    const int t = threadIdx.x, lx = t % HX, ly = t / HX;
+    const int gx = bx * TX + lx - S, gy = by * TY + ly - S;
+    const int e = t < HN ? max(max(S - lx, lx - (S + TX - 1)), max(max(S - ly, ly - (S + TY - 1)), 0)) : 1 << 20;
+    const int zc0 = bz * zchunk, zc1 = min(zc0 + zchunk, g.n[2]);
+    if (zc0 >= zc1) return;   // uniform over the block
+    double sg, off;
+    // (a column beyond a ragged tile's halo reads an image that no written node uses)
+    const int ix = mesh_image(g, 0, min(gx, g.n[0] + S), sg, off), iy = mesh_image(g, 1, min(gy, g.n[1] + S), sg, off);
+    const long col = (long)(iy + g.ng) * g.np[0] + (ix + g.ng), sz = (long)g.np[0] * g.np[1];
+    auto load = [&](int z) {
+        double s_, o_;
+        const long i = col + (mesh_image(g, 2, z, s_, o_) + g.ng) * sz;
+        return gmax ? theta_node(mo, in, gmax, g.P, i) : in[i];
+    };
+    double q[S][3];   // in-plane sums of the last three planes of F[s]
+#pragma unroll
+    for (int s = 0; s < S; s++) q[s][0] = q[s][1] = q[s][2] = 0.0;
+    // PF planes in flight (a plane a round trip to memory left the block waiting)
+    constexpr int PF = 2;
+    double next[PF];
+#pragma unroll
+    for (int u = 0; u < PF; u++) next[u] = load(min(zc0 - S + u, zc1 + S - 1));
+    // plane k enters F[0]; the sums of plane k - 1 - 2 s of F[s] and so plane
+    // k - 2 - 2 s of F[s + 1] follow
+    const int kend = zc1 + 2 * S;
+    for (int k0 = zc0 - S; k0 < kend; k0 += PF)
+#pragma unroll
+    for (int u = 0; u < PF; u++) {
+        const int k = k0 + u;
+        if (k >= kend) break;   // uniform
+        if (e <= S) F[0][k & 1][t] = next[u];
+        next[u] = load(min(k + PF, zc1 + S - 1));
+#pragma unroll
+        for (int s = 0; s < S; s++) {
+            const int zq = k - 1 - 2 * s, zo = zq - 1;
+            double v = 0.0;
+            if (e <= S - 1 - s) {
+                const double* A = F[s][zq & 1];
+                const double r0 = 0.25 * A[t - HX - 1] + 0.5 * A[t - HX] + 0.25 * A[t - HX + 1];
+                const double r1 = 0.25 * A[t - 1] + 0.5 * A[t] + 0.25 * A[t + 1];
+                const double r2 = 0.25 * A[t + HX - 1] + 0.5 * A[t + HX] + 0.25 * A[t + HX + 1];
+                q[s][0] = q[s][1];
+                q[s][1] = q[s][2];
+                q[s][2] = 0.25 * r0 + 0.5 * r1 + 0.25 * r2;
+                v = 0.25 * q[s][0] + 0.5 * q[s][1] + 0.25 * q[s][2];
+                if (s + 1 < S) F[s + 1][zo & 1][t] = v;
+                else if (zo >= zc0 && zo < zc1 && gx < g.n[0] && gy < g.n[1]) out[col + (zo + g.ng) * sz] = v;
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// S Jacobi sweeps of the mesh equations (1 or 2); resid: their residuals; LIM (the
+// last launch of a call): also the movement limiter's bound against x_n, whose
+// planes walk along, into the ordered key `bound`
+template <int TX, int TY, int S, bool LIM>
+__global__ void __launch_bounds__((Column3<TX, TY, S>::NT)) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_jacobi3(Geo g, const double* __restrict__ th, const double* __restrict__ xa, double* __restrict__ xb,
+          double* __restrict__ resid, const double* __restrict__ xn, unsigned long long* __restrict__ bound,
+          int zchunk)
+{
+    constexpr int HX = Column3<TX, TY, S>::HX, HN = Column3<TX, TY, S>::HN;
+    __shared__ double Ts[S + 1][HN];        // theta of the last planes
+    __shared__ double Xs[S][2][3][HN];      // x before step s, two planes
+    __shared__ double Ns[LIM ? S + 1 : 1][2][LIM ? HN : 1];   // x_n's first two components
+    const long P = g.P;
+    int bx, by, bz;
+    xcd_tile((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, bx, by, bz);
+    const int t = threadIdx.x, lx = t % HX, ly = t / HX;
+    const int gx = bx * TX + lx - S, gy = by * TY + ly - S;
+    const int e = t < HN ? max(max(S - lx, lx - (S + TX - 1)), max(max(S - ly, ly - (S + TY - 1)), 0)) : 1 << 20;
+    const bool own = e == 0 && gx < g.n[0] && gy < g.n[1];
+    const int zc0 = bz * zchunk, zc1 = min(zc0 + zchunk, g.n[2]);
+    if (zc0 >= zc1) return;   // uniform over the block
+    const long sz = (long)g.np[0] * g.np[1];
+    // (a column beyond a ragged tile's halo reads an image that no written node uses)
+    double s0, b0, s1, b1;
+    const int ix = mesh_image(g, 0, min(gx, g.n[0] + S), s0, b0), iy = mesh_image(g, 1, min(gy, g.n[1] + S), s1, b1);
+    const long col = (long)(iy + g.ng) * g.np[0] + (ix + g.ng);
+    double w2[3];
+#pragma unroll
+    for (int k = 0; k < 3; k++) w2[k] = 1.0 / (g.dxi[k] * g.dxi[k]);
+    double tr[S + 2];        // theta of the own column, planes k - S - 1 .. k
+    double xr[S][3][3];      // x before step s, the last three planes
+    double res[S];
+    double lim = 1.0;
+#pragma unroll
+    for (int s = 0; s < S; s++) {
+        res[s] = 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; c++) xr[s][c][0] = xr[s][c][1] = xr[s][c][2] = 0.0;
+    }
+#pragma unroll
+    for (int r = 0; r < S + 2; r++) tr[r] = 0.0;
+    double nr[LIM ? 3 : 1][S + 2];   // x_n of the own column, planes k - S - 1 .. k
+    // PF planes in flight
+    constexpr int PF = 2;
+    double tn[PF], pn[PF][3], nn[LIM ? PF : 1][3];
+    auto fetch = [&](int u, int z) {
+        double s2, b2;
+        const long i = col + (mesh_image(g, 2, min(z, zc1 + S - 1), s2, b2) + g.ng) * sz;
+        tn[u] = th[i];
+#pragma unroll
+        for (int c = 0; c < 3; c++) pn[u][c] = xa[c * P + i];
+        if constexpr (LIM)
+#pragma unroll
+            for (int c = 0; c < 3; c++) nn[u][c] = xn[c * P + i];
+    };
+#pragma unroll
+    for (int u = 0; u < PF; u++) fetch(u, zc0 - S + u);
+    // plane k enters; step s (0 .. S-1) runs at plane k - 1 - s
+    for (int k0 = zc0 - S; k0 < zc1 + S; k0 += PF)
+#pragma unroll
+    for (int u = 0; u < PF; u++) {
+        const int k = k0 + u;
+        if (k >= zc1 + S) break;   // uniform
+        if (e <= S) {
+            double s2, b2;
+            mesh_image(g, 2, k, s2, b2);
+            const double sc[3] = {s0, s1, s2}, bc[3] = {b0, b1, b2};
+#pragma unroll
+            for (int r = 0; r < S + 1; r++) tr[r] = tr[r + 1];
+            tr[S + 1] = tn[u];
+            Ts[(k + 3 * S + 3) % (S + 1)][t] = tn[u];
+#pragma unroll
+            for (int c = 0; c < 3; c++) {
+                const double x = fma(sc[c], pn[u][c], bc[c]);
+                xr[0][c][0] = xr[0][c][1];
+                xr[0][c][1] = xr[0][c][2];
+                xr[0][c][2] = x;
+                Xs[0][k & 1][c][t] = x;
+                if constexpr (LIM) {
+                    const double y = fma(sc[c], nn[u][c], bc[c]);
+#pragma unroll
+                    for (int r = 0; r < S + 1; r++) nr[c][r] = nr[c][r + 1];
+                    nr[c][S + 1] = y;
+                    if (c < 2) Ns[(k + 3 * S + 3) % (S + 1)][c][t] = y;
+                }
+            }
+        }
+        fetch(u, k + PF);
+#pragma unroll
+        for (int s = 0; s < S; s++) {
+            const int z = k - 1 - s;
+            if (e > S - 1 - s) continue;
+            const double* T = Ts[(z + 3 * S + 3) % (S + 1)];
+            const double t0 = tr[S - s];
+            double tp[3], tm[3];
+            tp[0] = 0.5 * (t0 + T[t + 1]);
+            tm[0] = 0.5 * (t0 + T[t - 1]);
+            tp[1] = 0.5 * (t0 + T[t + HX]);
+            tm[1] = 0.5 * (t0 + T[t - HX]);
+            tp[2] = 0.5 * (t0 + tr[S - s + 1]);
+            tm[2] = 0.5 * (t0 + tr[S - s - 1]);
+            double den = 0.0;
+#pragma unroll
+            for (int d = 0; d < 3; d++) {
+                tp[d] *= w2[d];
+                tm[d] *= w2[d];
+                den += tp[d] + tm[d];
+            }
+            const double iden = rcp(den);
+            double v[3];
+#pragma unroll
+            for (int c = 0; c < 3; c++) {
+                const double* A = Xs[s][z & 1][c];
+                double num = tp[0] * A[t + 1] + tm[0] * A[t - 1];
+                num += tp[1] * A[t + HX] + tm[1] * A[t - HX];
+                num += tp[2] * xr[s][c][2] + tm[2] * xr[s][c][0];
+                v[c] = num * iden;
+                if (own && z >= zc0 && z < zc1) res[s] = fmax(res[s], fabs(v[c] - xr[s][c][1]));
+            }
+            if (s + 1 < S) {
+#pragma unroll
+                for (int c = 0; c < 3; c++) {
+                    xr[s + 1 < S ? s + 1 : s][c][0] = xr[s + 1 < S ? s + 1 : s][c][1];
+                    xr[s + 1 < S ? s + 1 : s][c][1] = xr[s + 1 < S ? s + 1 : s][c][2];
+                    xr[s + 1 < S ? s + 1 : s][c][2] = v[c];
+                    Xs[s + 1 < S ? s + 1 : s][z & 1][c][t] = v[c];
+                }
+            } else if (own && z >= zc0 && z < zc1) {
+                const long i = col + (z + g.ng) * sz;
+#pragma unroll
+                for (int c = 0; c < 3; c++) xb[c * P + i] = v[c];
+                if constexpr (LIM) {   // plane z = k - S: x_n's own column at nr[.][1], its neighbours
+                    const double(*Nz)[HN] = Ns[(z + 3 * S + 3) % (S + 1)];
+                    const double lo[3] = {Nz[0][t - 1], Nz[1][t - HX], nr[2][0]};
+                    const double hi[3] = {Nz[0][t + 1], Nz[1][t + HX], nr[2][2]};
+#pragma unroll
+                    for (int c = 0; c < 3; c++) lim = fmin(lim, limiter_bound(v[c], nr[c][1], lo[c], hi[c]));
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (resid)
+#pragma unroll
+        for (int s = 0; s < S; s++) {
+            const double r = wave_max(res[s]);
+            if ((t & 63) == 0) scalar_max(resid + s, r);
+        }
+    if constexpr (LIM) {
+        lim = wave_min(lim);
+        if ((t & 63) == 0 && order_key(lim) < *(volatile unsigned long long*)bound) atomicMin(bound, order_key(lim));
+    }
 }
 
 // |grad rho| into gr, then the schlieren function
@@ -1975,8 +1904,7 @@ static void launch_schlieren(const Phys& ph, const Geo& g, const MonitorP& mo, c
     if constexpr (D == 2) {   // the monitor's gradient of one variable, the density
         MonitorP m{};
         m.nsig = 1;
-        hipLaunchKernelGGL((k_monitor2<N, 0>), dim3((g.n[0] + TX2 - 1) / TX2, (g.n[1] + TY2 - 1) / TY2), dim3(256),
-                           0, s, ph, g, m, JU, J, gr, gmax);
+        hipLaunchKernelGGL((k_monitor2<N, 0>), tiles2(g), dim3(256), 0, s, ph, g, m, JU, J, gr, gmax);
     } else {
         hipLaunchKernelGGL((k_rho_grad<N, D>), dim3(nb), dim3(256), 0, s, ph, g, JU, J, gr, gmax);
     }
@@ -1984,52 +1912,14 @@ static void launch_schlieren(const Phys& ph, const Geo& g, const MonitorP& mo, c
 }
 
 template <int N>
-static void launch_monitor(const Phys& ph, const Geo& g, const MonitorP& mo, int sigmode, const double* JU,
-                           const double* J, double* grad, double* part, int nb, hipStream_t s)
+static auto monitor2_kernel(int sigmode)
 {
-    if (sigmode == 2)
-        hipLaunchKernelGGL((k_monitor_grad<N, 3, 2>), dim3(nb), dim3(256), 0, s, ph, g, mo, JU, J, grad, part);
-    else if (sigmode == 1)
-        hipLaunchKernelGGL((k_monitor_grad<N, 3, 1>), dim3(nb), dim3(256), 0, s, ph, g, mo, JU, J, grad, part);
-    else
-        hipLaunchKernelGGL((k_monitor_grad<N, 3, 0>), dim3(nb), dim3(256), 0, s, ph, g, mo, JU, J, grad, part);
+    return sigmode == 2 ? k_monitor2<N, 2> : (sigmode == 1 ? k_monitor2<N, 1> : k_monitor2<N, 0>);
 }
-
-// the launches of the 2D kernels after the schlieren function
-static hipError_t redistribute2(const Phys& ph, const Geo& g, const MonitorP& mo, int sigmode, const double* JU,
-                                const double* J, const double* xn, double* disp, MeshWork& w, double* dtau_out,
-                                double* resid_out, unsigned* status, hipStream_t s, double* xnext)
+template <int N>
+static auto monitor3_kernel(int sigmode)
 {
-    const dim3 tiles((g.n[0] + TX2 - 1) / TX2, (g.n[1] + TY2 - 1) / TY2);
-    if (tiles.y > 65535) return hipErrorInvalidConfiguration;
-    auto* mon = ph.nspec == 1 ? (sigmode == 2 ? k_monitor2<1, 2> : (sigmode == 1 ? k_monitor2<1, 1> : k_monitor2<1, 0>))
-                              : (sigmode == 2 ? k_monitor2<2, 2> : (sigmode == 1 ? k_monitor2<2, 1> : k_monitor2<2, 0>));
-    hipLaunchKernelGGL(mon, tiles, dim3(256), 0, s, ph, g, mo, JU, J, w.grad, w.scal);
-    // (no filter pass: theta alone)
-    double *th = w.th0, *th2 = w.th1;
-    for (int left = mo.n_smooth, first = 1; first || left > 0; first = 0) {
-        const int steps = std::min(left, STEPS2);
-        hipLaunchKernelGGL(k_filter2, tiles, dim3(NT2), 0, s, g, mo, first ? w.grad : th,
-                           first ? w.scal : (const double*)nullptr, th2, steps);
-        std::swap(th, th2);
-        left -= steps;
-    }
-    const double* xcur = xn;
-    double *xa = w.xa, *xb = w.xb;
-    unsigned long long* key = reinterpret_cast<unsigned long long*>(w.scal + 8);
-    for (int nu = 0; nu < mo.n_sweeps;) {
-        const int steps = std::min(mo.n_sweeps - nu, STEPS2);
-        const bool last = nu + steps == mo.n_sweeps;
-        hipLaunchKernelGGL(k_jacobi2, tiles, dim3(NT2), 0, s, g, th, xcur, xa, steps,
-                           resid_out ? resid_out + nu : nullptr, last ? xn : (const double*)nullptr, key);
-        xcur = xa;
-        std::swap(xa, xb);
-        nu += steps;
-    }
-    const long nint = (long)g.n[0] * g.n[1];
-    hipLaunchKernelGGL(k_disp2, dim3((unsigned)((nint + 255) / 256)), dim3(256), 0, s, g, xcur, xn, key, w.scal + 6,
-                       dtau_out, disp, xnext, status);
-    return hipGetLastError();
+    return sigmode == 2 ? k_monitor_grad3<N, 2> : (sigmode == 1 ? k_monitor_grad3<N, 1> : k_monitor_grad3<N, 0>);
 }
 
 hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in, const double* JU,
@@ -2039,18 +1929,8 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
 {
     MonitorP mo = mo_in;
     mo.phi = w.phi;
-    const long P = g.P;
-    const long nint = (long)g.n[0] * g.n[1] * (g.dim == 3 ? g.n[2] : 1);
-    const int nb = red_grid(nint);
-    const int gi = grid_for(nint);
-    // 3D kernels walk z over 64 x 4 columns, in z chunks so that the blocks
-    // (one reduction partial each) stay within the partial buffer
-    const int jx = (g.n[0] + 63) / 64, jy = (g.n[1] + 3) / 4;
-    const int jz = std::max(1, std::min(g.n[2], RED_BLOCKS / (jx * jy)));
-    const int jchunk = (g.n[2] + jz - 1) / jz;
-    const dim3 jgrid(jx, jy, (g.n[2] + jchunk - 1) / jchunk);
-    const int jblocks = jx * jy * (int)jgrid.z;
-    const bool march = g.dim == 3 && jblocks <= RED_BLOCKS;
+    const bool d3 = g.dim == 3;
+    const long nint = (long)g.n[0] * g.n[1] * (d3 ? g.n[2] : 1);
     // the schlieren function first when the monitor uses it (th1 holds
     // |grad rho| until the filter overwrites it)
     bool use_phi = false, ext = false, press = false;
@@ -2061,61 +1941,75 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
     }
     // the monitor kernels carry only the variables they are asked for
     const int sigmode = ext ? 2 : (press ? 1 : 0);
-    hipLaunchKernelGGL(k_mesh_begin, dim3(1), dim3(256), 0, s, w.scal, g.dim == 2 ? resid_out : nullptr, mo.n_sweeps);
+    hipLaunchKernelGGL(k_mesh_begin, dim3(1), dim3(256), 0, s, w.scal, resid_out, mo.n_sweeps);
     if (use_phi)
-        ES_DISPATCH_ND(ph, g, launch_schlieren, ph, g, mo, JU, J, w.th1, w.scal + 7, w.phi, nb, gi, s);
-    if (g.dim == 2)
-        return redistribute2(ph, g, mo, sigmode, JU, J, xn, disp, w, dtau_out, resid_out, status, s, xnext);
-    // monitor and its global maxima
-    if (march) {
-        auto* kern = ph.nspec == 1
-                         ? (sigmode == 2 ? k_monitor_grad3<1, 2> : (sigmode == 1 ? k_monitor_grad3<1, 1> : k_monitor_grad3<1, 0>))
-                         : (sigmode == 2 ? k_monitor_grad3<2, 2> : (sigmode == 1 ? k_monitor_grad3<2, 1> : k_monitor_grad3<2, 0>));
-        hipLaunchKernelGGL(kern, jgrid, dim3(256), 0, s, ph, g, mo, JU, J, w.grad, w.part, jchunk);
+        ES_DISPATCH_ND(ph, g, launch_schlieren, ph, g, mo, JU, J, w.th1, w.scal + 7, w.phi, red_grid(nint),
+                       grid_for(nint), s);
+    // monitor and its global maxima (3D: z chunks of 64 x 4 columns, about 2048 blocks)
+    if (d3) {
+        const int jx = (g.n[0] + 63) / 64, jy = (g.n[1] + 3) / 4;
+        const int jz = std::max(1, std::min(g.n[2], 2048 / (jx * jy))), zc = (g.n[2] + jz - 1) / jz;
+        hipLaunchKernelGGL(ph.nspec == 1 ? monitor3_kernel<1>(sigmode) : monitor3_kernel<2>(sigmode),
+                           dim3(jx * jy * ((g.n[2] + zc - 1) / zc)), dim3(256), 0, s, ph, g, mo, JU, J, w.grad, w.scal, zc);
     } else {
-        (ph.nspec == 1 ? launch_monitor<1> : launch_monitor<2>)(ph, g, mo, sigmode, JU, J, w.grad, w.part, nb, s);
+        hipLaunchKernelGGL(ph.nspec == 1 ? monitor2_kernel<1>(sigmode) : monitor2_kernel<2>(sigmode), tiles2(g), dim3(256),
+                           0, s, ph, g, mo, JU, J, w.grad, w.scal);
     }
-    for (int q = 0; q < (mo.form ? 2 * mo.nsig : mo.nsig); q++)
-        hipLaunchKernelGGL(k_finish<RED_MAX>, dim3(1), dim3(256), 0, s, w.part + q * RED_BLOCKS,
-                           march ? jblocks : nb, w.scal + q, 0, 0.0, status);
-    // theta, the filter passes that are not z-marching, the Jacobi sweeps
-    // that are not and the displacement write their own ghost layers
-    long nzs, nys, nxs;
-    shell_sizes(g, nzs, nys, nxs);
-    hipError_t e = hipSuccess;
-    hipLaunchKernelGGL(k_theta, dim3(gi), dim3(256), 0, s, g, mo, w.grad, w.scal, w.th0, nzs, nys, nxs);
-    double* th = w.th0;
-    double* th2 = w.th1;
-    for (int q = 0; q < mo.n_smooth; q++) {
-        if (march) {
-            hipLaunchKernelGGL(k_filter3, jgrid, dim3(256), 0, s, g, th, th2, jchunk);
-            if ((e = fill_ghosts(g, th2, 1, GH_PLAIN, s)) != hipSuccess) return e;
+    // 3D launches over z chunks of tiles
+    auto march = [&](auto kern, int tx, int ty, int nt, int extra, auto... args) {
+        const int gx = (g.n[0] + tx - 1) / tx, gy = (g.n[1] + ty - 1) / ty;
+        const int zc = z_chunk(g.n[2], (long)gx * gy, extra);
+        hipLaunchKernelGGL(kern, dim3(gx * gy * ((g.n[2] + zc - 1) / zc)), dim3(nt), 0, s, g, args..., zc);
+    };
+    // theta and the filter passes (none: theta alone)
+    double *th = w.th0, *th2 = w.th1;
+    for (int left = mo.n_smooth, first = 1; first || left > 0; first = 0) {
+        const int steps = std::min(left, d3 ? 3 : STEPS2);
+        const double* in = first ? w.grad : th;
+        const double* gmax = first ? w.scal : nullptr;
+        if (!d3) {
+            hipLaunchKernelGGL(k_filter2, tiles2(g), dim3(NT2), 0, s, g, mo, in, gmax, th2, steps);
+        } else if (steps == 0) {
+            long nzs, nys, nxs;
+            shell_sizes(g, nzs, nys, nxs);
+            hipLaunchKernelGGL(k_theta, dim3(grid_for(nint)), dim3(256), 0, s, g, mo, in, gmax, th2, nzs, nys, nxs);
         } else {
-            hipLaunchKernelGGL(k_filter, dim3(gi), dim3(256), 0, s, g, th, th2, nzs, nys, nxs);
+            if (steps == 1) march(k_filter3<32, 12, 1>, 32, 12, Column3<32, 12, 1>::NT, 3, mo, in, gmax, th2);
+            else if (steps == 2) march(k_filter3<32, 12, 2>, 32, 12, Column3<32, 12, 2>::NT, 6, mo, in, gmax, th2);
+            else march(k_filter3<32, 12, 3>, 32, 12, Column3<32, 12, 3>::NT, 9, mo, in, gmax, th2);
         }
         std::swap(th, th2);
+        left -= steps;
     }
-    // Jacobi sweeps: the first reads x_n itself, then xa and xb alternate
+    // Jacobi sweeps: the first launch reads x_n itself, then xa and xb alternate;
+    // the last one takes the limiter's bound
     const double* xcur = xn;
-    double* xa = w.xa;
-    double* xb = w.xb;
-    for (int nu = 0; nu < mo.n_sweeps; nu++) {
-        if (march)
-            hipLaunchKernelGGL(k_jacobi3, jgrid, dim3(256), 0, s, g, th, xcur, xa, w.part, jchunk);
-        else
-            hipLaunchKernelGGL(k_jacobi<3>, dim3(nb), dim3(256), 0, s, g, th, xcur, xa, w.part, nzs, nys, nxs);
-        if (march && (e = fill_ghosts(g, xa, g.dim, GH_MESH, s)) != hipSuccess) return e;
-        if (resid_out)
-            hipLaunchKernelGGL(k_finish<RED_MAX>, dim3(1), dim3(256), 0, s, w.part, march ? jblocks : nb,
-                               resid_out + nu, 0, 0.0, status);
+    double *xa = w.xa, *xb = w.xb;
+    unsigned long long* key = reinterpret_cast<unsigned long long*>(w.scal + 8);
+    for (int nu = 0; nu < mo.n_sweeps;) {
+        const int steps = std::min(mo.n_sweeps - nu, d3 ? 2 : STEPS2);
+        const double* xl = nu + steps == mo.n_sweeps ? xn : nullptr;
+        double* res = resid_out ? resid_out + nu : nullptr;
+        if (!d3) {
+            hipLaunchKernelGGL(k_jacobi2, tiles2(g), dim3(NT2), 0, s, g, th, xcur, xa, steps, res, xl, key);
+        } else {
+            // (blocks of 512 threads)
+            if (steps == 1 && xl) march(k_jacobi3<30, 14, 1, true>, 30, 14, 512, 2, th, xcur, xa, res, xl, key);
+            else if (steps == 1) march(k_jacobi3<30, 14, 1, false>, 30, 14, 512, 2, th, xcur, xa, res, xl, key);
+            else if (xl) march(k_jacobi3<28, 12, 2, true>, 28, 12, 512, 4, th, xcur, xa, res, xl, key);
+            else march(k_jacobi3<28, 12, 2, false>, 28, 12, 512, 4, th, xcur, xa, res, xl, key);
+        }
         xcur = xa;
         std::swap(xa, xb);
+        nu += steps;
     }
-    // limiter and displacement
-    hipLaunchKernelGGL(k_limiter<3>, dim3(nb), dim3(256), 0, s, g, xcur, xn, w.part);
-    hipLaunchKernelGGL(k_finish<RED_MIN>, dim3(1), dim3(256), 0, s, w.part, nb, w.scal + 6, 2, 0.0, status);
-    hipLaunchKernelGGL(k_disp, dim3(gi), dim3(256), 0, s, g, xcur, xn, w.scal + 6, disp, xnext, nzs, nys, nxs);
-    if (dtau_out && (e = copy(w.scal + 6, dtau_out, 1, s)) != hipSuccess) return e;
+    const dim3 nodes((unsigned)((nint + 255) / 256));
+    if (d3) {
+        hipLaunchKernelGGL(k_disp<3>, nodes, dim3(256), 0, s, g, xcur, xn, key, w.scal + 6, dtau_out, disp, xnext, status);
+        const hipError_t e = hipGetLastError();
+        return e != hipSuccess ? e : fill_ghosts2(g, disp, 3, GH_DISP, xnext, 3, GH_MESH, s);
+    }
+    hipLaunchKernelGGL(k_disp<2>, nodes, dim3(256), 0, s, g, xcur, xn, key, w.scal + 6, dtau_out, disp, xnext, status);
     return hipGetLastError();
 }
 

@@ -30,9 +30,8 @@ struct MeshWork {
     double* xa;     // dim * P
     double* xb;     // dim * P
     double* phi;    // P: the schlieren function
-    double* part;   // 8 * 2048 partials
     double* scal;   // 16 scalars: monitor maxima [0..5], Delta_tau [6], max |grad rho| [7],
-                    // the 2D limiter's ordered key [8]
+                    // the limiter's ordered key [8]
 };
 
 struct RkArgs;

@@ -160,7 +160,7 @@ k_rhs_xy(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict
     __shared__ double My[D + 1][NN];
     const long P = g.P;
     int bx, by, bz;
-    xcd_plane<D>(bx, by, bz);
+    xcd_plane<D>((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, bx, by, bz);
     const int ox = bx * TX, oy = by * TY;
     const PlaneIn in{JU, Jv, jxx, jxt, rk.tdiv ? 1.0 / *rk.tdiv : 1.0, P, g.ng, g.np[0], g.np[1], g.n[0], g.n[1]};
     // padded index of patch node (0, 0), at interior (ox - 3, oy - 3) of plane bz
@@ -225,12 +225,9 @@ static hipError_t launch_xy(const Phys& ph, const Geo& g, const double* JU, cons
 {
     constexpr int TX = 16, TY = 15;
     const long gx = (g.n[0] + TX - 1) / TX, gy = (g.n[1] + TY - 1) / TY, gz = D == 3 ? g.n[2] : 1;
-    if (g.ng < 3 || gx * gy * gz > 0x7fffffffL || gz > 65535) return hipErrorInvalidConfiguration;
-    // (one block index: a grid's second extent stops at 65535)
-    const dim3 grid = gy <= 65535 ? dim3((unsigned)gx, (unsigned)gy, (unsigned)gz) : dim3(0);
-    if (!grid.x) return hipErrorInvalidConfiguration;
+    if (g.ng < 3 || gx * gy * gz > 0x7fffffffL) return hipErrorInvalidConfiguration;
     // two field groups in the FP32 dissipation keep that launch at 90 registers
-    hipLaunchKernelGGL((k_rhs_xy<N, D, TX, TY, MODE, R, RC, 2>), grid, dim3(512), 0, s, ph, g, JU, J, jxx, jxt,
+    hipLaunchKernelGGL((k_rhs_xy<N, D, TX, TY, MODE, R, RC, 2>), dim3((unsigned)(gx * gy * gz)), dim3(512), 0, s, ph, g, JU, J, jxx, jxt,
                        accU, accJ, rk, status);
     return hipGetLastError();
 }
