@@ -24,7 +24,6 @@ struct es_ctx {
     unsigned* status = nullptr;   // device status word
     double* scal = nullptr;       // 16 device scalars: [0] lambda [1] dt [2..] scratch
     double* part = nullptr;       // 4 x 2048 reduction partials
-    double* G = nullptr;          // 3D metric pass-1 buffer (9 P)
     MeshWork mesh{};
     double *bufA = nullptr, *bufB = nullptr;
     double *jxx = nullptr, *jxt = nullptr, *disp = nullptr;
@@ -170,9 +169,7 @@ int dalloc(T** p, size_t count)
 int alloc_workspace(es_ctx* c)
 {
     const size_t P = c->geo.P, d = c->geo.dim, nc = c->ph.nc;
-    int rc = ES_OK;
-    if (c->geo.dim == 3) rc = dalloc(&c->G, 9 * P);
-    if (!rc) rc = dalloc(&c->mesh.grad, MON_CH * P);
+    int rc = dalloc(&c->mesh.grad, MON_CH * P);
     if (!rc) rc = dalloc(&c->mesh.th0, P);
     if (!rc) rc = dalloc(&c->mesh.th1, P);
     if (!rc) rc = dalloc(&c->mesh.xa, d * P);
@@ -264,7 +261,7 @@ int es_create(const es_grid* g, es_ctx** out)
 int es_destroy(es_ctx* c)
 {
     if (!c) return ES_EINVAL;
-    void* bufs[] = {c->status, c->scal, c->part, c->G, c->mesh.grad, c->mesh.th0, c->mesh.th1,
+    void* bufs[] = {c->status, c->scal, c->part, c->mesh.grad, c->mesh.th0, c->mesh.th1,
                     c->mesh.xa, c->mesh.xb, c->mesh.phi, c->mesh.scal, c->bufA,
                     c->bufB, c->jxx, c->jxt, c->disp, c->mx, c->jxx2, c->reuse};
     for (void* p : bufs)
@@ -301,7 +298,7 @@ int es_metrics(es_ctx* c, const double* x_n, const double* disp, double c_s, con
     if (!vcl_only && !x_n) return ES_EINVAL;
     if (vcl_only && !jxi_t) return ES_EINVAL;
     if (!std::isfinite(c_s)) return ES_EINVAL;
-    return hip_rc(metrics(c->ph, c->geo, x_n, disp, c_s, dt_dev, jxi_x, jxi_t, vcl_only, c->G, S(stream)));
+    return hip_rc(metrics(c->ph, c->geo, x_n, disp, c_s, dt_dev, jxi_x, jxi_t, vcl_only, S(stream)));
 }
 
 int es_jacobian(es_ctx* c, const double* x, const double* jxi_x, double* J, void* stream)
@@ -414,7 +411,7 @@ int es_step(es_ctx* c, const es_monitor* m, double cfl, double dt_fixed, int mov
     // mesh the same pass leaves -sum_j disp_j J dxi_k/dx_j in jxt (divided by
     // the device scalar 1); stage 0's sweeps divide it by dt once dt exists
     ES_TRY(metrics(ph, g, x, disp, 0.0, disp ? c->scal + 5 : nullptr, c->jxx, disp ? c->jxt : nullptr, 0,
-                   c->G, s, c->reuse));
+                   s, c->reuse));
     // a fixed mesh keeps these metrics for the steps that follow
     if (!disp) ES_TRY(copy_unless(x, c->mx, d * P, c->reuse, s));
     if (dt_fixed > 0.0) ES_TRY(set_scalar(dt, dt_fixed, s));
@@ -441,9 +438,9 @@ int es_step(es_ctx* c, const es_monitor* m, double cfl, double dt_fixed, int mov
         // its metrics stay in jxx for the next step, and the c = 1/2 stage's
         // go to jxx2
         if (disp && st == 1) {
-            ES_TRY(metrics(ph, g, c->mx, disp, 0.0, dt, c->jxx, c->jxt, 0, c->G, s));
+            ES_TRY(metrics(ph, g, c->mx, disp, 0.0, dt, c->jxx, c->jxt, 0, s));
         } else if (disp && st == 2) {
-            ES_TRY(metrics(ph, g, x, disp, Cs[st], dt, c->jxx2, c->jxt, 0, c->G, s));
+            ES_TRY(metrics(ph, g, x, disp, Cs[st], dt, c->jxx2, c->jxt, 0, s));
         }
         RkArgs rk{JU, J, dt, A[st], B[st], outs[st][0], outs[st][1], (disp && st == 0) ? dt : nullptr, images};
         ES_TRY(launch_rhs(ph, g, mixed, inU, inJ, jxs[st], disp ? c->jxt : nullptr, accs[st][0], accs[st][1],

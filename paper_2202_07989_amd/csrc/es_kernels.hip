@@ -407,25 +407,47 @@ __device__ __forceinline__ double xs_at(const double* xn, const double* disp, do
     return v;
 }
 
-// 3D metrics in two z-marching passes.  Pass 1 forms the products
+// z chunks of nz planes for `cols` columns of blocks, `slots` blocks at a time:
+// the number that leaves the shortest walk (rounds of blocks times planes a
+// block), each walk taking `extra` planes more than it writes
+static int z_chunk(int nz, long cols, int extra, int slots)
+{
+    long best = -1;
+    int chunk = nz;
+    for (int c = 1; c <= std::max(1, nz / 8); c++) {
+        const int zc = (nz + c - 1) / c;
+        const long walk = ((cols * ((nz + zc - 1) / zc) + slots - 1) / slots) * (zc + extra);
+        if (best < 0 || walk < best) {
+            best = walk;
+            chunk = zc;
+        }
+    }
+    return chunk;
+}
+
+// 3D metrics in one walk along z.  The products
 //   Pr[a][j] = delta_a[xs_p] xs_q,  (p, q) = (j+1, j+2) mod 3,
-// at every node interior along a; pass 2 differences them,
+// are differenced again,
 //   J dxi_k/dx_j = (delta_b[Pr[a][j]] - delta_a[Pr[b][j]]) / (dxi_a dxi_b),  (k, a, b) cyclic.
 // delta is the 2w-order central difference 1/2 sum_m alpha_m (f_{+m} - f_{-m})
-// (alpha_m = 0 for m > w).  Each thread walks one (x, y) column up a chunk of
-// z planes, and z-differences come from a 7-plane ring in registers (each
-// value is loaded once).
-//   Pass 1 (16 x 16 columns) stages the stage mesh xs = x + c_s disp of the
-//   current plane with a 3-node halo in LDS for the x/y-differences (two
-//   loads per value, each used by up to 13 nodes).
-//   Pass 2 (64 x 4 columns, so a wavefront reads 64 consecutive doubles of a
-//   row) stages the in-plane neighbours of the products of the current plane
-//   in LDS (Pr[2] along x and y, Pr[0] along y, Pr[1] along x, 3-node
-//   halos): 1011 us at 256^3 against 1195 us reading them from the caches.
-constexpr int MT = 16;
-constexpr int MH = MT + 6;
-constexpr int MX = 64, MY = 4;
-
+// (alpha_m = 0 for m > w).
+//   A block owns (HX - 6) x (HY - 6) columns over a chunk of z planes and forms
+// the products of these and of a 3-node halo around them, so they never go to
+// memory: at 256^3 the walk moves 2.7 GB (2.4 GB of x, disp and the metrics
+// themselves) where two passes with the nine products between them moved 7.2.
+// Differences along z come from 7 planes of the thread's own column in
+// registers: x, Pr[0] and Pr[1].  All three are 126 registers, two waves a SIMD,
+// so two threads share a column: the first holds x and Pr[1] and gives
+// Pr[2] and the metrics k = 0, the second holds Pr[0], brings x in and gives
+// k = 1 and 2.  Neighbours in the plane are in LDS, both x and the products
+// twice, so one barrier a plane is enough: products of plane k - 3 and x of
+// plane k + 1 are written while the metrics of plane k - 4 are formed.
+// x is loaded two planes ahead, and its wait comes before the plane's stores (behind
+// them, in order, it would drain them first).
+//   256^3, ghost fill included: 1153 us (two passes 1735 us).  Two barriers a
+// plane 1249, one thread a column (512 of them) 1276, 48 x 10 columns of those
+// 1537, 64 x 8 1610; stores without the non-temporal hint 200 us more.  Bound
+// by LDS and FP64 issue, whose bursts the barrier keeps apart.
 __device__ __forceinline__ double cdiff(const double* al, double p1, double m1, double p2, double m2,
                                         double p3, double m3)
 {
@@ -435,204 +457,152 @@ __device__ __forceinline__ double cdiff(const double* al, double p1, double m1, 
     return 0.5 * s;
 }
 
-__global__ void __launch_bounds__(MT * MT)
-k_metric_prod3(Geo g, Phys ph, const double* __restrict__ xn, const double* __restrict__ disp,
-               double cs, double* __restrict__ Pr, int zchunk, const int* __restrict__ reuse)
+template <int HX, int HY, bool MOVED>
+__global__ void __launch_bounds__(2 * HX * HY)
+k_metric3(Geo g, Phys ph, const double* __restrict__ xn, const double* __restrict__ dx, double cs,
+          const double* __restrict__ disp, const double* __restrict__ dt_dev, double* __restrict__ jxx,
+          double* __restrict__ jxt, int zchunk, const int* __restrict__ reuse)
 {
     if (reuse && *reuse) return;
-    __shared__ double T[3][MH][MH];
-    const long P = g.P;
-    const int np0 = g.np[0], np1 = g.np[1], np2 = g.np[2];
-    const int tx = threadIdx.x, ty = threadIdx.y;
-    int bx, by, bz;
-    xcd_tile((np0 + MT - 1) / MT, (np1 + MT - 1) / MT, bx, by, bz);
-    const int x0 = bx * MT, y0 = by * MT;
-    const int x = x0 + tx, y = y0 + ty;
-    const int zc0 = bz * zchunk, zc1 = min(zc0 + zchunk, np2);
-    const bool in = x < np0 && y < np1;
-    const bool xin = x >= g.ng && x < g.ng + g.n[0];
-    const bool yin = y >= g.ng && y < g.ng + g.n[1];
-    const double al[3] = {ph.alpha[0], ph.alpha[1], ph.alpha[2]};
-    double ring[3][7];
-#pragma unroll
-    for (int p = 0; p < 3; p++)
-#pragma unroll
-        for (int r = 0; r < 7; r++) ring[p][r] = 0.0;
-    const int zs = max(zc0 - 3, 0), ze = min(zc1 + 3, np2);
-    for (int zl = zs; zl < ze; zl++) {
-        for (int q = ty * MT + tx; q < MH * MH; q += MT * MT) {
-            const int hx = q % MH, hy = q / MH;
-            const int gx = x0 + hx - 3, gy = y0 + hy - 3;
-            if (gx >= 0 && gx < np0 && gy >= 0 && gy < np1) {
-                const long i = ((long)zl * np1 + gy) * np0 + gx;
-#pragma unroll
-                for (int p = 0; p < 3; p++) {
-                    double v = xn[p * P + i];
-                    if (disp) v += cs * disp[p * P + i];
-                    T[p][hy][hx] = v;
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int p = 0; p < 3; p++) {
-#pragma unroll
-            for (int r = 0; r < 6; r++) ring[p][r] = ring[p][r + 1];
-            ring[p][6] = in ? T[p][ty + 3][tx + 3] : 0.0;
-        }
-        if (in && zl >= zc0 && zl < zc1) {
-            const long i = ((long)zl * np1 + y) * np0 + x;
-            const int cx = tx + 3, cy = ty + 3;
-            if (xin) {
-                double d[3];
-#pragma unroll
-                for (int p = 0; p < 3; p++)
-                    d[p] = cdiff(al, T[p][cy][cx + 1], T[p][cy][cx - 1], T[p][cy][cx + 2],
-                                 T[p][cy][cx - 2], T[p][cy][cx + 3], T[p][cy][cx - 3]);
-#pragma unroll
-                for (int j = 0; j < 3; j++) Pr[(0 * 3 + j) * P + i] = d[(j + 1) % 3] * T[(j + 2) % 3][cy][cx];
-            }
-            if (yin) {
-                double d[3];
-#pragma unroll
-                for (int p = 0; p < 3; p++)
-                    d[p] = cdiff(al, T[p][cy + 1][cx], T[p][cy - 1][cx], T[p][cy + 2][cx],
-                                 T[p][cy - 2][cx], T[p][cy + 3][cx], T[p][cy - 3][cx]);
-#pragma unroll
-                for (int j = 0; j < 3; j++) Pr[(1 * 3 + j) * P + i] = d[(j + 1) % 3] * T[(j + 2) % 3][cy][cx];
-            }
-        }
-        const int zp = zl - 3;   // ring slot 3 holds plane zp
-        if (in && zp >= zc0 && zp < zc1 && zp >= g.ng && zp < g.ng + g.n[2]) {
-            const long i = ((long)zp * np1 + y) * np0 + x;
-            double d[3];
-#pragma unroll
-            for (int p = 0; p < 3; p++)
-                d[p] = cdiff(al, ring[p][4], ring[p][2], ring[p][5], ring[p][1], ring[p][6], ring[p][0]);
-#pragma unroll
-            for (int j = 0; j < 3; j++) Pr[(2 * 3 + j) * P + i] = d[(j + 1) % 3] * ring[(j + 2) % 3][3];
-        }
-        __syncthreads();
-    }
-}
-
-__global__ void __launch_bounds__(MX * MY) __attribute__((amdgpu_waves_per_eu(4, 8)))
-k_metric3(Geo g, Phys ph, const double* __restrict__ disp, const double* __restrict__ Pr,
-          const double* __restrict__ dt_dev, double* __restrict__ jxx, double* __restrict__ jxt,
-          int zchunk, const int* __restrict__ reuse)
-{
-    if (reuse && *reuse) return;
-    // the in-plane neighbours of plane z: Pr[2][j] along x and y, Pr[0][j]
-    // along y, Pr[1][j] along x (the tile plus a 3-node halo; the corners of
-    // the Pr[2] patch are never read)
-    __shared__ double L2[3][MY + 6][MX + 6];
-    __shared__ double L0[3][MY + 6][MX];
-    __shared__ double L1[3][MY][MX + 6];
+    constexpr int TX = HX - 6, TY = HY - 6, NT = HX * HY;
+    static_assert(NT % 64 == 0);
+    __shared__ double X[2][3][NT + 6];    // xs of a plane (node t at t + 3)
+    __shared__ double E[2][3][3][NT];     // Pr[a][j] of a plane
     const long P = g.P;
     const int np0 = g.np[0], np1 = g.np[1];
     int bx, by, bz;
-    xcd_tile((g.n[0] + MX - 1) / MX, (g.n[1] + MY - 1) / MY, bx, by, bz);
-    const int tx = threadIdx.x, ty = threadIdx.y;
-    const int xt = g.ng + bx * MX, yt = g.ng + by * MY;
-    const int x = xt + tx, y = yt + ty;
+    xcd_tile((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, bx, by, bz);
+    const bool first = __builtin_amdgcn_readfirstlane(threadIdx.x) < NT;
+    const int t = first ? threadIdx.x : threadIdx.x - NT, lx = t % HX, ly = t / HX;
+    const int gx = g.ng + bx * TX + lx - 3, gy = g.ng + by * TY + ly - 3;
     const int zc0 = g.ng + bz * zchunk, zc1 = min(zc0 + zchunk, g.ng + g.n[2]);
-    const bool in = x < g.ng + g.n[0] && y < g.ng + g.n[1];
+    if (zc0 >= zc1) return;   // uniform over the block
+    const bool row = ly >= 3 && ly < TY + 3;
+    const bool own = row && lx >= 3 && lx < TX + 3 && gx < g.ng + g.n[0] && gy < g.ng + g.n[1];
+    // (a column beyond a ragged tile's halo reads the last padded node, which
+    // no written node uses)
+    const long sz = (long)np0 * np1;
     const double dt = dt_dev ? *dt_dev : 0.0;
     const double idt = dt > 0.0 ? 1.0 / dt : 0.0;   // mesh velocity = disp / dt
+    const bool moving = jxt && disp && dt > 0.0;
+    const double* wsrc = moving ? disp : xn;   // (read in any case)
     const double al[3] = {ph.alpha[0], ph.alpha[1], ph.alpha[2]};
     const double s01 = g.idxi[0] * g.idxi[1], s12 = g.idxi[1] * g.idxi[2], s20 = g.idxi[2] * g.idxi[0];
-    const int t = tx + MX * ty;
-    double ring[6][7];   // Pr[0][j] (0..2) and Pr[1][j] (3..5) at the own node, planes zl-6..zl
-#pragma unroll
-    for (int c = 0; c < 6; c++)
-#pragma unroll
-        for (int r = 0; r < 7; r++) ring[c][r] = 0.0;
-    // the ring advances on every thread (a column beyond a ragged tile reads
-    // the last padded node instead): a shift under a branch would keep two
-    // copies of the ring live
-    const int xr = min(x, np0 - 1), yr = min(y, np1 - 1);
-    auto advance = [&](int zl) {   // ring slot r then holds plane zl - 6 + r
-        const long il = ((long)zl * np1 + yr) * np0 + xr;
-#pragma unroll
-        for (int c = 0; c < 6; c++) {
-#pragma unroll
-            for (int r = 0; r < 6; r++) ring[c][r] = ring[c][r + 1];
-            ring[c][6] = Pr[(long)c * P + il];
-        }
+    const unsigned cb = (unsigned)((min(gy, np1 - 1) * np0 + min(gx, np0 - 1)) * sizeof(double));
+    auto at = [&](auto* f, int c, int z) -> auto& {   // component c of the own column at plane z
+        using T = std::remove_reference_t<decltype(*f)>;
+        using B = std::conditional_t<std::is_const_v<T>, const char, char>;
+        return *reinterpret_cast<T*>(reinterpret_cast<B*>(f + (c * P + z * sz)) + cb);
     };
-    for (int zl = zc0 - 3; zl < zc0 + 3; zl++) advance(zl);
-    for (int z = zc0; z < zc1; z++) {
-        advance(z + 3);
-        const long pz = (long)z * np1;
-#pragma unroll 1
-        for (int q = t; q < (MY + 6) * (MX + 6); q += MX * MY) {
-            const int hx = q % (MX + 6), hy = q / (MX + 6);
-            const bool cx = hx >= 3 && hx < MX + 3, cy = hy >= 3 && hy < MY + 3;
-            const int gx = xt - 3 + hx, gy = yt - 3 + hy;
-            if (!(cx || cy) || gx >= np0 || gy >= np1) continue;
-            const long gi = (pz + gy) * np0 + gx;
+    // the waves of the two halves take different walks, each with the same
+    // barrier a plane
+    auto walk = [&](auto half) {
+        constexpr bool A = half == 0;
+        double pr[3][7], xr[A ? 3 : 1][7];   // planes k - 6 .. k of the own column: Pr[1] (A) or Pr[0]; xs
 #pragma unroll
-            for (int j = 0; j < 3; j++) L2[j][hy][hx] = Pr[(long)(6 + j) * P + gi];
-            if (cx) {
+        for (int j = 0; j < 3; j++)
 #pragma unroll
-                for (int j = 0; j < 3; j++) L0[j][hy][hx - 3] = Pr[(long)j * P + gi];
+            for (int r = 0; r < 7; r++) {
+                pr[j][r] = 0.0;
+                if constexpr (A) xr[j][r] = 0.0;
             }
-            if (cy) {
+        double w[3] = {0.0, 0.0, 0.0}, nx[3], nd[3];
+        auto fetch = [&](int z) {
 #pragma unroll
-                for (int j = 0; j < 3; j++) L1[j][hy - 3][hx] = Pr[(long)(3 + j) * P + gi];
+            for (int p = 0; p < 3; p++) {
+                nx[p] = at(xn, p, z);
+                if constexpr (MOVED) nd[p] = at(dx, p, z);
             }
+        };
+        auto stage = [&](int z) {   // plane z into X; the next one on its way
+#pragma unroll
+            for (int p = 0; p < 3; p++) {
+                if constexpr (MOVED) X[z & 1][p][t + 3] = nx[p] + cs * nd[p];
+                else X[z & 1][p][t + 3] = nx[p];
+            }
+            fetch(min(z + 1, zc1 + 2));
+        };
+        if constexpr (!A) {
+            fetch(zc0 - 3);
+            stage(zc0 - 3);
         }
         __syncthreads();
-        if (in) {
-            const long i = (pz + y) * np0 + x;
-            const int cx = tx + 3, cy = ty + 3;
-            // one j at a time: its three metrics are stored and folded into
-            // the time metrics at once (the sum over j in the same order)
-            double w[3] = {0.0, 0.0, 0.0};
-            if (jxt && disp && dt > 0.0)
+#pragma unroll 1
+        for (int k = zc0 - 3;; k++) {
+            // the metrics of plane z, whose products are in E since the last
+            // barrier.  Each half folds its metrics into its time metrics (the
+            // sum over j in the order of k_vcl)
+            const int z = k - 4;
+            if constexpr (!A)
+                if (k + 1 < zc1 + 3) stage(k + 1);
+            if (own && z >= zc0) {
+                double nt[2] = {0.0, 0.0};
 #pragma unroll
-                for (int j = 0; j < 3; j++) w[j] = disp[j * P + i] * idt;
-            double nt[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-            for (int j = 0; j < 3; j++) {
-                // each difference reads its six LDS values after a point that
-                // no LDS read moves across, so few of them are live beside
-                // the ring (four waves per SIMD without spills)
-                double M[3];
-                // k = 0 (a = 1, b = 2): delta_2 Pr[1][j] - delta_1 Pr[2][j]
-                const double* r1 = ring[3 + j];
-                const double t1 = cdiff(al, r1[4], r1[2], r1[5], r1[1], r1[6], r1[0]);
-                asm volatile("" ::: "memory");
-                const double t2 = cdiff(al, L2[j][cy + 1][cx], L2[j][cy - 1][cx], L2[j][cy + 2][cx],
-                                        L2[j][cy - 2][cx], L2[j][cy + 3][cx], L2[j][cy - 3][cx]);
-                M[0] = (t1 - t2) * s12;
-                // k = 1 (a = 2, b = 0): delta_0 Pr[2][j] - delta_2 Pr[0][j]
-                const double* r0 = ring[j];
-                asm volatile("" ::: "memory");
-                const double u1 = cdiff(al, L2[j][cy][cx + 1], L2[j][cy][cx - 1], L2[j][cy][cx + 2],
-                                        L2[j][cy][cx - 2], L2[j][cy][cx + 3], L2[j][cy][cx - 3]);
-                const double u2 = cdiff(al, r0[4], r0[2], r0[5], r0[1], r0[6], r0[0]);
-                M[1] = (u1 - u2) * s20;
-                // k = 2 (a = 0, b = 1): delta_1 Pr[0][j] - delta_0 Pr[1][j]
-                asm volatile("" ::: "memory");
-                const double v1 = cdiff(al, L0[j][cy + 1][tx], L0[j][cy - 1][tx], L0[j][cy + 2][tx],
-                                        L0[j][cy - 2][tx], L0[j][cy + 3][tx], L0[j][cy - 3][tx]);
-                asm volatile("" ::: "memory");
-                const double v2 = cdiff(al, L1[j][ty][cx + 1], L1[j][ty][cx - 1], L1[j][ty][cx + 2],
-                                        L1[j][ty][cx - 2], L1[j][ty][cx + 3], L1[j][ty][cx - 3]);
-                M[2] = (v1 - v2) * s01;
-#pragma unroll
-                for (int k = 0; k < 3; k++) {
-                    __builtin_nontemporal_store(M[k], &jxx[(k * 3 + j) * P + i]);
-                    nt[k] -= w[j] * M[k];
+                for (int j = 0; j < 3; j++) {
+                    const double v = moving ? w[j] * idt : 0.0;
+                    const double *e0 = &E[z & 1][0][j][t], *e1 = &E[z & 1][1][j][t], *e2 = &E[z & 1][2][j][t], *q = pr[j];
+                    if constexpr (A) {   // k = 0 (a = 1, b = 2): delta_2 Pr[1][j] - delta_1 Pr[2][j]
+                        const double M = (cdiff(al, q[4], q[2], q[5], q[1], q[6], q[0]) -
+                                          cdiff(al, e2[HX], e2[-HX], e2[2 * HX], e2[-2 * HX], e2[3 * HX], e2[-3 * HX])) * s12;
+                        __builtin_nontemporal_store(M, &at(jxx, j, z));
+                        nt[0] -= v * M;
+                    } else {
+                        // k = 1 (a = 2, b = 0): delta_0 Pr[2][j] - delta_2 Pr[0][j]
+                        const double M1 = (cdiff(al, e2[1], e2[-1], e2[2], e2[-2], e2[3], e2[-3]) -
+                                           cdiff(al, q[4], q[2], q[5], q[1], q[6], q[0])) * s20;
+                        // k = 2 (a = 0, b = 1): delta_1 Pr[0][j] - delta_0 Pr[1][j]
+                        const double M2 = (cdiff(al, e0[HX], e0[-HX], e0[2 * HX], e0[-2 * HX], e0[3 * HX], e0[-3 * HX]) -
+                                           cdiff(al, e1[1], e1[-1], e1[2], e1[-2], e1[3], e1[-3])) * s01;
+                        __builtin_nontemporal_store(M1, &at(jxx, 3 + j, z));
+                        __builtin_nontemporal_store(M2, &at(jxx, 6 + j, z));
+                        nt[0] -= v * M1;
+                        nt[1] -= v * M2;
+                    }
+                }
+                if (jxt) {
+                    __builtin_nontemporal_store(nt[0], &at(jxt, A ? 0 : 1, z));
+                    if constexpr (!A) __builtin_nontemporal_store(nt[1], &at(jxt, 2, z));
                 }
             }
-            if (jxt)
+            if (k == zc1 + 3) break;
+            // Pr[1] (rows within the halo) or Pr[0] (columns within the halo) of plane k
+            double d[3] = {0.0, 0.0, 0.0};
+            if (!A || row)
 #pragma unroll
-                for (int k = 0; k < 3; k++) __builtin_nontemporal_store(nt[k], &jxt[k * P + i]);
+                for (int p = 0; p < 3; p++) {
+                    constexpr int st = A ? HX : 1;
+                    const double* F = &X[k & 1][p][t + 3];
+                    d[p] = cdiff(al, F[st], F[-st], F[2 * st], F[-2 * st], F[3 * st], F[-3 * st]);
+                }
+            double v[3];
+#pragma unroll
+            for (int p = 0; p < 3; p++) v[p] = X[k & 1][p][t + 3];
+            // and the products of plane k - 3
+#pragma unroll
+            for (int j = 0; j < 3; j++) {
+#pragma unroll
+                for (int r = 0; r < 6; r++) {
+                    pr[j][r] = pr[j][r + 1];
+                    if constexpr (A) xr[j][r] = xr[j][r + 1];
+                }
+                pr[j][6] = d[(j + 1) % 3] * v[(j + 2) % 3];
+                if constexpr (A) xr[j][6] = v[j];
+                E[(k + 1) & 1][A][j][t] = pr[j][3];
+            }
+            if constexpr (A) {
+#pragma unroll
+                for (int j = 0; j < 3; j++) {
+                    const double* q = xr[(j + 1) % 3];
+                    E[(k + 1) & 1][2][j][t] = cdiff(al, q[4], q[2], q[5], q[1], q[6], q[0]) * xr[(j + 2) % 3][3];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 3; j++) w[j] = at(wsrc, j, max(k - 3, zc0));
+            __syncthreads();
         }
-        __syncthreads();   // the next plane overwrites the patch
-    }
+    };
+    if (first) walk(std::integral_constant<int, 0>{});
+    else walk(std::integral_constant<int, 1>{});
 }
 
 // 2D: J dxi_1/dx = (delta_2 x_2, -delta_2 x_1)/dxi_2, J dxi_2/dx = (-delta_1 x_2, delta_1 x_1)/dxi_1,
@@ -751,7 +721,7 @@ hipError_t jacobian(const Phys& ph, const Geo& g, const double* x, const double*
 }
 
 hipError_t metrics(const Phys& ph, const Geo& g, const double* xn, const double* disp, double cs,
-                   const double* dt_dev, double* jxx, double* jxt, int vcl_only, double* G,
+                   const double* dt_dev, double* jxx, double* jxt, int vcl_only,
                    hipStream_t s, const int* reuse)
 {
     const long nint = (long)g.n[0] * g.n[1] * (g.dim == 3 ? g.n[2] : 1);
@@ -767,18 +737,11 @@ hipError_t metrics(const Phys& ph, const Geo& g, const double* xn, const double*
                            dt_dev, jxx, jxt, reuse);
         return hipGetLastError();
     } else {
-        // z chunks: enough blocks to fill the chip, chunks long against the
-        // 6-plane ring start-up
-        const int bx1 = (g.np[0] + MT - 1) / MT, by1 = (g.np[1] + MT - 1) / MT;
-        const int nc1 = std::max(1, std::min(g.np[2] / 32, (1024 + bx1 * by1 - 1) / (bx1 * by1)));
-        const int zc1 = (g.np[2] + nc1 - 1) / nc1;
-        hipLaunchKernelGGL(k_metric_prod3, dim3(bx1 * by1 * ((g.np[2] + zc1 - 1) / zc1)), dim3(MT, MT), 0, s,
-                           g, ph, xn, dx, cs, G, zc1, reuse);
-        const int bx2 = (g.n[0] + MX - 1) / MX, by2 = (g.n[1] + MY - 1) / MY;
-        const int nc2 = std::max(1, std::min(g.n[2] / 16, (4096 + bx2 * by2 - 1) / (bx2 * by2)));
-        const int zc2 = (g.n[2] + nc2 - 1) / nc2;
-        hipLaunchKernelGGL(k_metric3, dim3(bx2 * by2 * ((g.n[2] + zc2 - 1) / zc2)), dim3(MX, MY), 0, s, g, ph,
-                           disp, G, dt_dev, jxx, jxt, zc2, reuse);
+        constexpr int HX = 32, HY = 16;   // one block a compute unit
+        const int gx = (g.n[0] + HX - 7) / (HX - 6), gy = (g.n[1] + HY - 7) / (HY - 6);
+        const int zc = z_chunk(g.n[2], (long)gx * gy, 6, 256);
+        hipLaunchKernelGGL((dx ? k_metric3<HX, HY, true> : k_metric3<HX, HY, false>), dim3(gx * gy * ((g.n[2] + zc - 1) / zc)), dim3(2 * HX * HY), 0, s, g, ph,
+                           xn, dx, cs, disp, dt_dev, jxx, jxt, zc, reuse);
         if (reuse && jxt)
             hipLaunchKernelGGL(k_vcl, dim3(grid_for(nint)), dim3(256), 0, s, g, disp, dt_dev, jxx, jxt, reuse);
     }
@@ -1656,24 +1619,6 @@ struct Column3 {
     static constexpr int HX = TX + 2 * S, HY = TY + 2 * S, HN = HX * HY, NT = (HN + 63) / 64 * 64;
 };
 
-// z chunks of nz planes for `cols` columns of blocks, two blocks a compute
-// unit: the number that leaves the shortest walk (rounds of blocks times planes
-// a block), each walk taking `extra` planes more than it writes
-static int z_chunk(int nz, long cols, int extra)
-{
-    long best = -1;
-    int chunk = nz;
-    for (int c = 1; c <= std::max(1, nz / 8); c++) {
-        const int zc = (nz + c - 1) / c;
-        const long walk = ((cols * ((nz + zc - 1) / zc) + 511) / 512) * (zc + extra);
-        if (best < 0 || walk < best) {
-            best = walk;
-            chunk = zc;
-        }
-    }
-    return chunk;
-}
-
 // S passes of the low-pass filter: the weights 2^-(|j|_1 + 3), j in {-1,0,1}^3, are
 // the product of (1/4, 1/2, 1/4) along each direction, so a pass is the
 // in-plane sum q of each plane and out = q(z-1)/4 + q(z)/2 + q(z+1)/4.  With
@@ -1958,7 +1903,7 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
     // 3D launches over z chunks of tiles
     auto march = [&](auto kern, int tx, int ty, int nt, int extra, auto... args) {
         const int gx = (g.n[0] + tx - 1) / tx, gy = (g.n[1] + ty - 1) / ty;
-        const int zc = z_chunk(g.n[2], (long)gx * gy, extra);
+        const int zc = z_chunk(g.n[2], (long)gx * gy, extra, 512);
         hipLaunchKernelGGL(kern, dim3(gx * gy * ((g.n[2] + zc - 1) / zc)), dim3(nt), 0, s, g, args..., zc);
     };
     // theta and the filter passes (none: theta alone)

@@ -69,7 +69,7 @@ hipError_t jacobian(const Phys& ph, const Geo& g, const double* x, const double*
 // mesh velocity disp / dt.  With reuse set on the device, jxx already holds
 // the metrics of this mesh (ghost layers included) and only jxt is formed.
 hipError_t metrics(const Phys& ph, const Geo& g, const double* xn, const double* disp, double cs,
-                   const double* dt_dev, double* jxx, double* jxt, int vcl_only, double* G,
+                   const double* dt_dev, double* jxx, double* jxt, int vcl_only,
                    hipStream_t s, const int* reuse = nullptr);
 hipError_t wavespeed(const Phys& ph, const Geo& g, const double* JU, const double* J, const double* jxx,
                      double cfl, double* part, double* out2, unsigned* status, hipStream_t s);

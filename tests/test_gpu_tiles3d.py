@@ -1,4 +1,4 @@
-"""3D mesh step at the edges of its tiles: filter passes (32 x 12 columns, up to
+"""3D mesh step and metrics at the edges of their tiles: filter passes (32 x 12 columns, up to
 three a launch) and Jacobi sweeps (28 x 12 columns two a launch, 30 x 14 one),
 over one and several z chunks, on grids around the tile sizes and smaller than a
 halo, with every kind of face, against the oracle at the FP64 parity bar."""
@@ -54,3 +54,41 @@ def test_mesh_step(faces, n, smooth, sweeps):
             assert abs(float(host(gt)[0]) - tau) <= TOL_FP64
         if sweeps:
             assert np.abs(host(gr) - resid).max() <= TOL_FP64 * h
+
+
+@pytest.mark.parametrize("faces", list(FACES))
+@pytest.mark.parametrize("n", [(3, 3, 3), (26, 10, 9), (27, 11, 20), (25, 9, 40), (53, 21, 8)])
+@pytest.mark.parametrize("w", [1, 2, 3])
+def test_metrics(faces, n, w):
+    """Columns (26 x 10 a block) and z chunks of the metrics, with and without a
+    displacement and the time metrics, ghost layers included."""
+    say(f"[metric tiles 3D] {faces} {n} w={w}")
+    bc = FACES[faces]
+    sp = I.make_spec(3, 2, n, w=w, bc=bc, wall=[(0.0, 1.0)] * 3 if bc else None, **STIFF)
+    if faces == "mixed":
+        sp["inflow"] = {(2, 1): [1.0, 0.5, -0.3, 0.1, 0.2, 400.0]}
+    o = oracle.Oracle(sp)
+    rng = np.random.default_rng(5)
+    x, disp = I.zeros(sp, 3), I.zeros(sp, 3)
+    Iin = I.interior(sp)
+    for k, xi in enumerate(I.xi_nodes(sp)):
+        x[k][Iin[1:]] = xi + 0.2 * sp["dxi"][k] * rng.uniform(-1, 1, size=xi.shape)
+        disp[k][Iin[1:]] = 0.1 * sp["dxi"][k] * rng.uniform(-1, 1, size=xi.shape)
+    o.fill_ghosts_x(x)
+    o.fill_ghosts_kind(disp, 3, 2)
+    # a product is of size dxi and carries about 4 roundings; its differences over
+    # dxi^2 then carry 16 eps / dxi, on either side
+    tol = 32 * np.finfo(float).eps / min(sp["dxi"])
+    from paper_2202_07989_amd import es
+    ctx = es.Context(sp)
+    dt = torch.tensor([0.01], dtype=torch.float64, device="cuda")
+    for d, cs, t in ((disp, 0.5, True), (disp, 0.0, True), (None, 0.0, True), (disp, 1.0, False)):
+        jx, jt = o.metrics(x, d, c_s=cs, dt=0.01)
+        gx = torch.full_like(dev(jx), float("nan"))
+        gt = torch.full_like(dev(jt), float("nan"))
+        ctx.es_metrics(dev(x), None if d is None else dev(d), cs, dt, gx, gt if t else None)
+        assert np.abs(host(gx) - jx).max() <= tol * np.abs(jx).max(), (cs, t)
+        if t:
+            assert np.abs(host(gt) - jt).max() <= tol * np.abs(jx).max() * 10 * max(sp["dxi"]), cs
+        else:
+            assert torch.isnan(gt).all()
