@@ -409,15 +409,18 @@ __device__ __forceinline__ double xs_at(const double* xn, const double* disp, do
 
 // z chunks of nz planes for `cols` columns of blocks, `slots` blocks at a time:
 // the number that leaves the shortest walk (rounds of blocks times planes a
-// block), each walk taking `extra` planes more than it writes
+// block), each walk taking `extra` planes more than it writes.  A multiple of
+// 8, where each XCD walks whole chunks and so finds its tiles' neighbours in its
+// own L2, may be a tenth longer (two Jacobi sweeps at 256^3: 8 chunks 280 us, 2
+// chunks 306)
 static int z_chunk(int nz, long cols, int extra, int slots)
 {
-    long best = -1;
+    double best = -1.0;
     int chunk = nz;
     for (int c = 1; c <= std::max(1, nz / 8); c++) {
-        const int zc = (nz + c - 1) / c;
-        const long walk = ((cols * ((nz + zc - 1) / zc) + slots - 1) / slots) * (zc + extra);
-        if (best < 0 || walk < best) {
+        const int zc = (nz + c - 1) / c, n = (nz + zc - 1) / zc;
+        const double walk = (double)((cols * n + slots - 1) / slots) * (zc + extra) * (n % 8 == 0 ? 0.9 : 1.0);
+        if (best < 0.0 || walk < best) {
             best = walk;
             chunk = zc;
         }
@@ -1283,13 +1286,46 @@ __global__ void k_theta(Geo g, MonitorP mo, const double* __restrict__ grad, con
     }
 }
 
-// the movement limiter's bound for one coordinate that moves from x0 to xm
-// between the neighbours lo and hi (1 if it does not move)
-__device__ __forceinline__ double limiter_bound(double xm, double x0, double lo, double hi)
+// the value of the lane below or above this one in the wave (0 past its ends); every
+// lane of the wave has to take part
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double v)
 {
-    const double dx = xm - x0;
-    if (dx < 0.0) return -(x0 - lo) / (2.0 * dx);
-    return dx > 0.0 ? (hi - x0) / (2.0 * dx) : 1.0;
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, true);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+__device__ __forceinline__ double lane_below(double v) { return lane_shift<0x138>(v); }   // wave shift right by one
+__device__ __forceinline__ double lane_above(double v) { return lane_shift<0x130>(v); }   // wave shift left by one
+
+// a double of the `bytes` at base, both the same for the whole wave; a store at or
+// past the end is dropped.  A marching kernel stores through it without a
+// branch: behind a branch the compiler does not know how many stores follow a
+// load, and its wait for a load of two planes ago also drains the last plane's
+__device__ __forceinline__ double buffer_load(const double* base, unsigned bytes, unsigned at)
+{
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(base), 0, bytes, 0x00027000);
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, 0));
+}
+template <bool NT>
+__device__ __forceinline__ void buffer_store(double* base, unsigned bytes, unsigned at, double v)
+{
+    using U2 = __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned;
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00027000);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r, at, 0, NT ? 2 : 0);
+}
+constexpr unsigned DROPPED = 0xfffffff8u;
+
+// lim lowered to the movement limiter's bound for one coordinate that moves
+// from x0 to xm between the neighbours lo and hi (1 if it does not move).  The
+// quotient is taken only where a product says that it may be below lim, which at
+// 1 is where a node moves half a spacing
+__device__ __forceinline__ double limit(double lim, double xm, double x0, double lo, double hi)
+{
+    const double dx = xm - x0, n = (dx < 0.0 ? lo : hi) - x0, d = 2.0 * dx;
+    const bool may = dx != 0.0 && !((dx < 0.0 ? -n : n) > lim * fabs(d) * (1.0 + 1e-15));
+    return may ? fmin(lim, n / d) : lim;
 }
 
 // ---------------------------------------------------------------------------
@@ -1551,8 +1587,8 @@ k_jacobi2(Geo g, const double* __restrict__ th, const double* __restrict__ xa, d
         xb[P + i] = v[1];
         if (xn) {
             const long n0 = g.np[0];
-            b = fmin(b, limiter_bound(v[0], xn[i], xn[i - 1], xn[i + 1]));
-            b = fmin(b, limiter_bound(v[1], xn[P + i], xn[P + i - n0], xn[P + i + n0]));
+            b = limit(b, v[0], xn[i], xn[i - 1], xn[i + 1]);
+            b = limit(b, v[1], xn[P + i], xn[P + i - n0], xn[P + i + n0]);
         }
     }
     if (xn) {
@@ -1610,8 +1646,8 @@ __global__ void k_disp(Geo g, const double* __restrict__ xmu, const double* __re
 // thread's own registers, those in the plane are in LDS (double-buffered, one
 // barrier a plane), and its halo is one node narrower.  Nodes outside the grid
 // are read through the face rules, as in 2D.  A launch then reads and writes a
-// field once for S steps: at 256^3 three filter passes take 258 us instead
-// of 3 x 97 us and two Jacobi sweeps 314 us instead of 2 x 307 us (each with the
+// field once for S steps: at 256^3 three filter passes take 172 us instead
+// of 3 x 97 us and two Jacobi sweeps 300 us instead of 2 x 307 us (each with the
 // ghost fill that they needed).
 // ---------------------------------------------------------------------------
 template <int TX, int TY, int S>
@@ -1621,7 +1657,9 @@ struct Column3 {
 
 // S passes of the low-pass filter: the weights 2^-(|j|_1 + 3), j in {-1,0,1}^3, are
 // the product of (1/4, 1/2, 1/4) along each direction, so a pass is the
-// in-plane sum q of each plane and out = q(z-1)/4 + q(z)/2 + q(z+1)/4.  With
+// in-plane sum q of each plane and out = q(z-1)/4 + q(z)/2 + q(z+1)/4.  The sum
+// along x comes from the neighbouring lanes (a wave is two rows), which leaves two
+// LDS reads a pass instead of nine: 172 instead of 260 us for three.  With
 // gmax, theta is formed from the monitor's gradients `in` first
 template <int TX, int TY, int S>
 __global__ void __launch_bounds__((Column3<TX, TY, S>::NT))
@@ -1629,12 +1667,13 @@ k_filter3(Geo g, MonitorP mo, const double* __restrict__ in, const double* __res
           double* __restrict__ out, int zchunk)
 {
     constexpr int HX = Column3<TX, TY, S>::HX, HN = Column3<TX, TY, S>::HN;
-    __shared__ double F[S][2][HN];   // F[s]: the field after s passes, two planes
+    static_assert(HX == 32 && HN % 64 == 0, "lanes of a row are neighbours");
+    __shared__ double R[S][2][HN + 2 * HX];   // sums along x of the field after s passes, two planes
     int bx, by, bz;
     xcd_tile((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, bx, by, bz);
     const int t = threadIdx.x, lx = t % HX, ly = t / HX;
     const int gx = bx * TX + lx - S, gy = by * TY + ly - S;
-    const int e = t < HN ? max(max(S - lx, lx - (S + TX - 1)), max(max(S - ly, ly - (S + TY - 1)), 0)) : 1 << 20;
+    const bool own = lx >= S && lx < S + TX && ly >= S && ly < S + TY && gx < g.n[0] && gy < g.n[1];
     const int zc0 = bz * zchunk, zc1 = min(zc0 + zchunk, g.n[2]);
     if (zc0 >= zc1) return;   // uniform over the block
     double sg, off;
@@ -1646,43 +1685,55 @@ k_filter3(Geo g, MonitorP mo, const double* __restrict__ in, const double* __res
         const long i = col + (mesh_image(g, 2, z, s_, o_) + g.ng) * sz;
         return gmax ? theta_node(mo, in, gmax, g.P, i) : in[i];
     };
-    double q[S][3];   // in-plane sums of the last three planes of F[s]
+    const int row = __builtin_amdgcn_readfirstlane(ly);   // the wave's rows: this one and the next
+    double q[S][3];   // in-plane sums of the last three planes after s passes
+    double rx[S];     // the own sum along x of the last plane
 #pragma unroll
-    for (int s = 0; s < S; s++) q[s][0] = q[s][1] = q[s][2] = 0.0;
+    for (int s = 0; s < S; s++) q[s][0] = q[s][1] = q[s][2] = rx[s] = 0.0;
     // PF planes in flight (a plane a round trip to memory left the block waiting)
     constexpr int PF = 2;
     double next[PF];
+    const unsigned plane = (unsigned)(sz * sizeof(double)), ob = own ? (unsigned)(col * sizeof(double)) : DROPPED;
+    auto store = [&](int z, double v) {   // (a plane below the chunk: dropped)
+        buffer_store<false>(out + (max(z, zc0) + g.ng) * sz, z >= zc0 ? plane : 0u, ob, v);
+    };
 #pragma unroll
-    for (int u = 0; u < PF; u++) next[u] = load(min(zc0 - S + u, zc1 + S - 1));
-    // plane k enters F[0]; the sums of plane k - 1 - 2 s of F[s] and so plane
-    // k - 2 - 2 s of F[s + 1] follow
+    for (int u = 0; u < PF; u++) {   // (with the store that a step has)
+        next[u] = load(min(zc0 - S + u, zc1 + S - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        store(zc0 - 1 - u, 0.0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // plane k enters; the field after s passes has reached plane k - 2 s
     const int kend = zc1 + 2 * S;
-    for (int k0 = zc0 - S; k0 < kend; k0 += PF)
+    int k0 = zc0 - S;
+    do {   // (entered without a test, past which the first loads would sink)
 #pragma unroll
-    for (int u = 0; u < PF; u++) {
-        const int k = k0 + u;
-        if (k >= kend) break;   // uniform
-        if (e <= S) F[0][k & 1][t] = next[u];
-        next[u] = load(min(k + PF, zc1 + S - 1));
+        for (int u = 0; u < PF; u++) {
+            const int k = k0 + u;
+            if (k >= kend) break;   // uniform
+            auto enter = [&](int s, double v) {
+                rx[s] = 0.25 * lane_below(v) + 0.5 * v + 0.25 * lane_above(v);
+                R[s][k & 1][HX + t] = rx[s];
+            };
+            double vo = 0.0;
 #pragma unroll
-        for (int s = 0; s < S; s++) {
-            const int zq = k - 1 - 2 * s, zo = zq - 1;
-            double v = 0.0;
-            if (e <= S - 1 - s) {
-                const double* A = F[s][zq & 1];
-                const double r0 = 0.25 * A[t - HX - 1] + 0.5 * A[t - HX] + 0.25 * A[t - HX + 1];
-                const double r1 = 0.25 * A[t - 1] + 0.5 * A[t] + 0.25 * A[t + 1];
-                const double r2 = 0.25 * A[t + HX - 1] + 0.5 * A[t + HX] + 0.25 * A[t + HX + 1];
+            for (int s = S - 1; s >= 0; s--) {
+                if (row + 1 < s + 1 || row > TY + 2 * S - 2 - s) continue;   // halo used up
+                const double* A = &R[s][~k & 1][HX + t];
                 q[s][0] = q[s][1];
                 q[s][1] = q[s][2];
-                q[s][2] = 0.25 * r0 + 0.5 * r1 + 0.25 * r2;
-                v = 0.25 * q[s][0] + 0.5 * q[s][1] + 0.25 * q[s][2];
-                if (s + 1 < S) F[s + 1][zo & 1][t] = v;
-                else if (zo >= zc0 && zo < zc1 && gx < g.n[0] && gy < g.n[1]) out[col + (zo + g.ng) * sz] = v;
+                q[s][2] = 0.25 * A[-HX] + 0.5 * rx[s] + 0.25 * A[HX];
+                const double v = 0.25 * q[s][0] + 0.5 * q[s][1] + 0.25 * q[s][2];
+                if (s + 1 < S) enter(s + 1, v);
+                else vo = v;
             }
+            store(k - 2 * S, vo);
+            enter(0, next[u]);
+            next[u] = load(min(k + PF, zc1 + S - 1));
+            __syncthreads();
         }
-        __syncthreads();
-    }
+    } while ((k0 += PF) < kend);
 }
 
 // S Jacobi sweeps of the mesh equations (1 or 2); resid: their residuals; LIM (the
@@ -1695,26 +1746,29 @@ k_jacobi3(Geo g, const double* __restrict__ th, const double* __restrict__ xa, d
           int zchunk)
 {
     constexpr int HX = Column3<TX, TY, S>::HX, HN = Column3<TX, TY, S>::HN;
-    __shared__ double Ts[S + 1][HN];        // theta of the last planes
-    __shared__ double Xs[S][2][3][HN];      // x before step s, two planes
-    __shared__ double Ns[LIM ? S + 1 : 1][2][LIM ? HN : 1];   // x_n's first two components
+    static_assert(HX == 32 && HN % 64 == 0, "lanes of a row are neighbours");
+    constexpr int HP = HN + 2 * HX;         // (a row on either side, read and not used)
+    __shared__ double Ts[S + 1][HP];        // theta of the last planes
+    __shared__ double Xs[S][2][3][HP];      // x before step s, two planes
+    __shared__ double Ns[LIM ? S + 1 : 1][LIM ? HP : 1];   // x_n's second component
     const long P = g.P;
     int bx, by, bz;
     xcd_tile((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, bx, by, bz);
     const int t = threadIdx.x, lx = t % HX, ly = t / HX;
     const int gx = bx * TX + lx - S, gy = by * TY + ly - S;
-    const int e = t < HN ? max(max(S - lx, lx - (S + TX - 1)), max(max(S - ly, ly - (S + TY - 1)), 0)) : 1 << 20;
-    const bool own = e == 0 && gx < g.n[0] && gy < g.n[1];
+    const bool own = lx >= S && lx < S + TX && ly >= S && ly < S + TY && gx < g.n[0] && gy < g.n[1];
+    const int row = __builtin_amdgcn_readfirstlane(ly);   // the wave's rows: this one and the next
     const int zc0 = bz * zchunk, zc1 = min(zc0 + zchunk, g.n[2]);
     if (zc0 >= zc1) return;   // uniform over the block
     const long sz = (long)g.np[0] * g.np[1];
     // (a column beyond a ragged tile's halo reads an image that no written node uses)
     double s0, b0, s1, b1;
     const int ix = mesh_image(g, 0, min(gx, g.n[0] + S), s0, b0), iy = mesh_image(g, 1, min(gy, g.n[1] + S), s1, b1);
-    const long col = (long)(iy + g.ng) * g.np[0] + (ix + g.ng);
-    double w2[3];
+    const unsigned cb = ((unsigned)(iy + g.ng) * g.np[0] + (ix + g.ng)) * (unsigned)sizeof(double);
+    const unsigned ob = own ? cb : DROPPED, plane = (unsigned)(sz * sizeof(double));
+    double h2[3];
 #pragma unroll
-    for (int k = 0; k < 3; k++) w2[k] = 1.0 / (g.dxi[k] * g.dxi[k]);
+    for (int k = 0; k < 3; k++) h2[k] = 0.5 / (g.dxi[k] * g.dxi[k]);
     double tr[S + 2];        // theta of the own column, planes k - S - 1 .. k
     double xr[S][3][3];      // x before step s, the last three planes
     double res[S];
@@ -1733,101 +1787,117 @@ k_jacobi3(Geo g, const double* __restrict__ th, const double* __restrict__ xa, d
     double tn[PF], pn[PF][3], nn[LIM ? PF : 1][3];
     auto fetch = [&](int u, int z) {
         double s2, b2;
-        const long i = col + (mesh_image(g, 2, min(z, zc1 + S - 1), s2, b2) + g.ng) * sz;
-        tn[u] = th[i];
+        const long i = (mesh_image(g, 2, min(z, zc1 + S - 1), s2, b2) + g.ng) * sz;
+        tn[u] = buffer_load(th + i, plane, cb);
 #pragma unroll
-        for (int c = 0; c < 3; c++) pn[u][c] = xa[c * P + i];
+        for (int c = 0; c < 3; c++) pn[u][c] = buffer_load(xa + c * P + i, plane, cb);
         if constexpr (LIM)
 #pragma unroll
-            for (int c = 0; c < 3; c++) nn[u][c] = xn[c * P + i];
+            for (int c = 0; c < 3; c++) nn[u][c] = buffer_load(xn + c * P + i, plane, cb);
+    };
+    auto store = [&](int z, const double (&v)[3]) {   // (a plane outside the chunk: dropped)
+        const bool on = z >= zc0 && z < zc1;
+#pragma unroll
+        for (int c = 0; c < 3; c++)
+            buffer_store<false>(xb + c * P + ((on ? z : zc0) + g.ng) * sz, on ? plane : 0u, ob, v[c]);
     };
 #pragma unroll
-    for (int u = 0; u < PF; u++) fetch(u, zc0 - S + u);
+    for (int u = 0; u < PF; u++) {   // (with the stores that a step has)
+        fetch(u, zc0 - S + u);
+        __builtin_amdgcn_sched_barrier(0);
+        store(zc0 - 1 - u, {0.0, 0.0, 0.0});
+        __builtin_amdgcn_sched_barrier(0);
+    }
     // plane k enters; step s (0 .. S-1) runs at plane k - 1 - s
-    for (int k0 = zc0 - S; k0 < zc1 + S; k0 += PF)
+    int k0 = zc0 - S;
+    do {   // (entered without a test, past which the first loads would sink)
 #pragma unroll
-    for (int u = 0; u < PF; u++) {
-        const int k = k0 + u;
-        if (k >= zc1 + S) break;   // uniform
-        if (e <= S) {
+        for (int u = 0; u < PF; u++) {
+            const int k = k0 + u;
+            if (k >= zc1 + S) break;   // uniform
             double s2, b2;
             mesh_image(g, 2, k, s2, b2);
             const double sc[3] = {s0, s1, s2}, bc[3] = {b0, b1, b2};
 #pragma unroll
             for (int r = 0; r < S + 1; r++) tr[r] = tr[r + 1];
-            tr[S + 1] = tn[u];
-            Ts[(k + 3 * S + 3) % (S + 1)][t] = tn[u];
+            double t1 = tn[u];
+            asm volatile("" : "+v"(t1));   // (a copy: a load into the register of a ring's value is moved, and so waited for, at once)
+            tr[S + 1] = t1;
+            Ts[(k + 3 * S + 3) % (S + 1)][HX + t] = t1;
 #pragma unroll
             for (int c = 0; c < 3; c++) {
                 const double x = fma(sc[c], pn[u][c], bc[c]);
                 xr[0][c][0] = xr[0][c][1];
                 xr[0][c][1] = xr[0][c][2];
                 xr[0][c][2] = x;
-                Xs[0][k & 1][c][t] = x;
+                Xs[0][k & 1][c][HX + t] = x;
                 if constexpr (LIM) {
                     const double y = fma(sc[c], nn[u][c], bc[c]);
 #pragma unroll
                     for (int r = 0; r < S + 1; r++) nr[c][r] = nr[c][r + 1];
                     nr[c][S + 1] = y;
-                    if (c < 2) Ns[(k + 3 * S + 3) % (S + 1)][c][t] = y;
+                    if (c == 1) Ns[(k + 3 * S + 3) % (S + 1)][HX + t] = y;
                 }
             }
-        }
-        fetch(u, k + PF);
+            fetch(u, k + PF);
+            double v[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-        for (int s = 0; s < S; s++) {
-            const int z = k - 1 - s;
-            if (e > S - 1 - s) continue;
-            const double* T = Ts[(z + 3 * S + 3) % (S + 1)];
-            const double t0 = tr[S - s];
-            double tp[3], tm[3];
-            tp[0] = 0.5 * (t0 + T[t + 1]);
-            tm[0] = 0.5 * (t0 + T[t - 1]);
-            tp[1] = 0.5 * (t0 + T[t + HX]);
-            tm[1] = 0.5 * (t0 + T[t - HX]);
-            tp[2] = 0.5 * (t0 + tr[S - s + 1]);
-            tm[2] = 0.5 * (t0 + tr[S - s - 1]);
-            double den = 0.0;
-#pragma unroll
-            for (int d = 0; d < 3; d++) {
-                tp[d] *= w2[d];
-                tm[d] *= w2[d];
-                den += tp[d] + tm[d];
-            }
-            const double iden = rcp(den);
-            double v[3];
-#pragma unroll
-            for (int c = 0; c < 3; c++) {
-                const double* A = Xs[s][z & 1][c];
-                double num = tp[0] * A[t + 1] + tm[0] * A[t - 1];
-                num += tp[1] * A[t + HX] + tm[1] * A[t - HX];
-                num += tp[2] * xr[s][c][2] + tm[2] * xr[s][c][0];
-                v[c] = num * iden;
-                if (own && z >= zc0 && z < zc1) res[s] = fmax(res[s], fabs(v[c] - xr[s][c][1]));
-            }
-            if (s + 1 < S) {
+            for (int s = 0; s < S; s++) {
+                const int z = k - 1 - s;
+                if (row + 1 < s + 1 || row > TY + 2 * S - 2 - s) continue;   // halo used up
+                const double* T = &Ts[(z + 3 * S + 3) % (S + 1)][HX + t];
+                const double t0 = tr[S - s];
+                double tp[3], tm[3];
+                tp[0] = h2[0] * (t0 + T[1]);
+                tm[0] = h2[0] * (t0 + T[-1]);
+                tp[1] = h2[1] * (t0 + T[HX]);
+                tm[1] = h2[1] * (t0 + T[-HX]);
+                tp[2] = h2[2] * (t0 + tr[S - s + 1]);
+                tm[2] = h2[2] * (t0 + tr[S - s - 1]);
+                const double iden = rcp(((tp[0] + tm[0]) + (tp[1] + tm[1])) + (tp[2] + tm[2]));
+                double r = res[s];
 #pragma unroll
                 for (int c = 0; c < 3; c++) {
-                    xr[s + 1 < S ? s + 1 : s][c][0] = xr[s + 1 < S ? s + 1 : s][c][1];
-                    xr[s + 1 < S ? s + 1 : s][c][1] = xr[s + 1 < S ? s + 1 : s][c][2];
-                    xr[s + 1 < S ? s + 1 : s][c][2] = v[c];
-                    Xs[s + 1 < S ? s + 1 : s][z & 1][c][t] = v[c];
+                    const double* A = &Xs[s][z & 1][c][HX + t];
+                    double num = tp[0] * A[1];
+                    num = fma(tm[0], A[-1], num);
+                    num = fma(tp[1], A[HX], num);
+                    num = fma(tm[1], A[-HX], num);
+                    num = fma(tp[2], xr[s][c][2], num);
+                    num = fma(tm[2], xr[s][c][0], num);
+                    v[c] = num * iden;
+                    r = fmax(r, fabs(v[c] - xr[s][c][1]));
                 }
-            } else if (own && z >= zc0 && z < zc1) {
-                const long i = col + (z + g.ng) * sz;
+                res[s] = own && z >= zc0 && z < zc1 ? r : res[s];
+                if (s + 1 < S) {
 #pragma unroll
-                for (int c = 0; c < 3; c++) xb[c * P + i] = v[c];
-                if constexpr (LIM) {   // plane z = k - S: x_n's own column at nr[.][1], its neighbours
-                    const double(*Nz)[HN] = Ns[(z + 3 * S + 3) % (S + 1)];
-                    const double lo[3] = {Nz[0][t - 1], Nz[1][t - HX], nr[2][0]};
-                    const double hi[3] = {Nz[0][t + 1], Nz[1][t + HX], nr[2][2]};
+                    for (int c = 0; c < 3; c++) {
+                        xr[s + 1 < S ? s + 1 : s][c][0] = xr[s + 1 < S ? s + 1 : s][c][1];
+                        xr[s + 1 < S ? s + 1 : s][c][1] = xr[s + 1 < S ? s + 1 : s][c][2];
+                        xr[s + 1 < S ? s + 1 : s][c][2] = v[c];
+                        Xs[s + 1 < S ? s + 1 : s][z & 1][c][HX + t] = v[c];
+                    }
+                } else {
+                    double lo[3], hi[3];
+                    if constexpr (LIM) {   // plane z = k - S: x_n's own column at nr[.][1], its neighbours
+                        const double* A = &Ns[(z + 3 * S + 3) % (S + 1)][HX + t];
+                        lo[0] = lane_below(nr[0][1]);
+                        hi[0] = lane_above(nr[0][1]);
+                        lo[1] = A[-HX];
+                        hi[1] = A[HX];
+                        lo[2] = nr[2][0];
+                        hi[2] = nr[2][2];
+                    }
+                    if constexpr (LIM)
+                        if (own && z >= zc0 && z < zc1)
 #pragma unroll
-                    for (int c = 0; c < 3; c++) lim = fmin(lim, limiter_bound(v[c], nr[c][1], lo[c], hi[c]));
+                            for (int c = 0; c < 3; c++) lim = limit(lim, v[c], nr[c][1], lo[c], hi[c]);
                 }
             }
+            store(k - S, v);
+            __syncthreads();
         }
-        __syncthreads();
-    }
+    } while ((k0 += PF) < zc1 + S);
     if (resid)
 #pragma unroll
         for (int s = 0; s < S; s++) {
@@ -1919,9 +1989,9 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
             shell_sizes(g, nzs, nys, nxs);
             hipLaunchKernelGGL(k_theta, dim3(grid_for(nint)), dim3(256), 0, s, g, mo, in, gmax, th2, nzs, nys, nxs);
         } else {
-            if (steps == 1) march(k_filter3<32, 12, 1>, 32, 12, Column3<32, 12, 1>::NT, 3, mo, in, gmax, th2);
-            else if (steps == 2) march(k_filter3<32, 12, 2>, 32, 12, Column3<32, 12, 2>::NT, 6, mo, in, gmax, th2);
-            else march(k_filter3<32, 12, 3>, 32, 12, Column3<32, 12, 3>::NT, 9, mo, in, gmax, th2);
+            if (steps == 1) march(k_filter3<30, 20, 1>, 30, 20, 704, 3, mo, in, gmax, th2);
+            else if (steps == 2) march(k_filter3<28, 18, 2>, 28, 18, 704, 6, mo, in, gmax, th2);
+            else march(k_filter3<26, 16, 3>, 26, 16, 704, 9, mo, in, gmax, th2);
         }
         std::swap(th, th2);
         left -= steps;
