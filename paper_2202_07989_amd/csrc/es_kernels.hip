@@ -436,7 +436,7 @@ static int z_chunk(int nz, long cols, int extra, int slots)
 // (alpha_m = 0 for m > w).
 //   A block owns (HX - 6) x (HY - 6) columns over a chunk of z planes and forms
 // the products of these and of a 3-node halo around them, so they never go to
-// memory: at 256^3 the walk moves 2.7 GB (2.4 GB of x, disp and the metrics
+// memory: at 256^3 the walk moves 3.4 GB (2.4 GB of x, disp and the metrics
 // themselves) where two passes with the nine products between them moved 7.2.
 // Differences along z come from 7 planes of the thread's own column in
 // registers: x, Pr[0] and Pr[1].  All three are 126 registers, two waves a SIMD,
@@ -613,7 +613,8 @@ k_metric3(Geo g, Phys ph, const double* __restrict__ xn, const double* __restric
 // already (ghost layers included) and only the time metrics are formed.
 // (One pass: the separate grid-stride passes over the nodes and the ghost shell,
 // with divisions and the time metrics and ghost fill of kept metrics in
-// launches of their own, took 12.3 + 4.1 + 4.8 us at 350 x 150.)
+// launches of their own, took 12.3 + 4.1 + 4.8 us at 350 x 150; now 6.9 on
+// average.)
 __global__ void k_metric2(Geo g, Phys ph, const double* __restrict__ xn,
                           const double* __restrict__ disp, double cs, const double* __restrict__ dt_dev,
                           double* __restrict__ jxx, double* __restrict__ jxt, const int* __restrict__ reuse)
@@ -626,6 +627,11 @@ __global__ void k_metric2(Geo g, Phys ph, const double* __restrict__ xn,
     const double dt = dt_dev ? *dt_dev : 0.0;
     int i0, i1, i2;
     const long i = interior_node(g, q, i0, i1, i2);
+    double w[2] = {0.0, 0.0};   // the displacement, ahead of the stores
+    if (jxt && disp && dt > 0.0) {
+        w[0] = disp[i];
+        w[1] = disp[P + i];
+    }
     double M[4];
     if (kept) {
 #pragma unroll
@@ -633,22 +639,28 @@ __global__ void k_metric2(Geo g, Phys ph, const double* __restrict__ xn,
     } else {
         const double al[3] = {ph.alpha[0], ph.alpha[1], ph.alpha[2]};   // 0 beyond w
         const bool moved = disp && cs != 0.0;
+        // all loads first (one behind a branch is waited for on the spot)
+        auto node = [&](int a, int p, int m) {   // +1 +2 +3 -1 -2 -3 along a, component p
+            return p * P + i + (m < 3 ? m + 1 : 2 - m) * (a == 0 ? 1L : g.np[0]);
+        };
+        double f[2][2][6];
+#pragma unroll
+        for (int q = 0; q < 24; q++) f[q / 12][q / 6 % 2][q % 6] = xn[node(q / 12, q / 6 % 2, q % 6)];
+        if (moved) {
+            double e[2][2][6];
+#pragma unroll
+            for (int q = 0; q < 24; q++) e[q / 12][q / 6 % 2][q % 6] = disp[node(q / 12, q / 6 % 2, q % 6)];
+#pragma unroll
+            for (int q = 0; q < 24; q++) f[q / 12][q / 6 % 2][q % 6] += cs * e[q / 12][q / 6 % 2][q % 6];
+        }
         double d[2][2];   // d[a][p] = delta_a[x_p]
 #pragma unroll
-        for (int a = 0; a < 2; a++) {
-            const long st = a == 0 ? 1 : g.np[0];
+        for (int a = 0; a < 2; a++)
 #pragma unroll
             for (int p = 0; p < 2; p++) {
-                double f[6];
-#pragma unroll
-                for (int m = 0; m < 6; m++) {
-                    const long j = p * P + i + (m < 3 ? m + 1 : 2 - m) * st;   // +1 +2 +3 -1 -2 -3
-                    f[m] = xn[j];
-                    if (moved) f[m] += cs * disp[j];
-                }
-                d[a][p] = cdiff(al, f[0], f[3], f[1], f[4], f[2], f[5]);
+                const double* h = f[a][p];
+                d[a][p] = cdiff(al, h[0], h[3], h[1], h[4], h[2], h[5]);
             }
-        }
         M[0] = d[1][1] * g.idxi[1];
         M[1] = -d[1][0] * g.idxi[1];
         M[2] = -d[0][1] * g.idxi[0];
@@ -662,7 +674,7 @@ __global__ void k_metric2(Geo g, Phys ph, const double* __restrict__ xn,
 #pragma unroll
             for (int k = 0; k < 2; k++)
 #pragma unroll
-                for (int j = 0; j < 2; j++) nt[k] -= (disp[j * P + i] * idt) * M[k * 2 + j];
+                for (int j = 0; j < 2; j++) nt[k] -= (w[j] * idt) * M[k * 2 + j];
         put_images<2, 2, GH_JXT>(g, i0 - g.ng, i1 - g.ng, 0, nt, jxt);
     }
 }
@@ -1251,20 +1263,42 @@ __global__ void k_schlieren(Phys ph, Geo g, MonitorP mo, const double* __restric
     }
 }
 
+// channels of a monitor's gradients that theta is formed from (0 without gmax: the
+// field is theta already), and a node's, all loaded before the first is used (a
+// load behind the arithmetic of the one before is a round trip each)
+__device__ __forceinline__ int theta_channels(const MonitorP& mo, const double* gmax)
+{
+    return !gmax ? 1 : (mo.form ? 2 * mo.nsig : mo.nsig);
+}
+__device__ __forceinline__ void theta_load(double (&raw)[MON_CH], const double* in, int nch, long P, long i)
+{
+#pragma unroll
+    for (int c = 0; c < MON_CH; c++)
+        if (c < nch) raw[c] = in[c * P + i];
+}
+__device__ __forceinline__ double theta_of(const MonitorP& mo, const double* gmax, const double (&raw)[MON_CH])
+{
+    if (!gmax) return raw[0];
+    double th = 1.0;
+#pragma unroll
+    for (int s = 0; s < MON_CH; s++) {
+        if (s >= mo.nsig) break;
+        const double G = gmax[s];
+        if (G > 0.0) {
+            const double r = raw[s] / G;
+            th += mo.form ? mo.alpha[s] * r : mo.alpha[s] * r * r;
+        }
+        if (s < 2 && mo.form && gmax[mo.nsig + s] > 0.0)   // (at most two variables)
+            th += mo.beta[s] * ((mo.nsig == 1 ? raw[1] : raw[2 + s]) / gmax[mo.nsig + s]);
+    }
+    return sqrt(th);
+}
 __device__ __forceinline__ double theta_node(const MonitorP& mo, const double* grad, const double* gmax, long P,
                                              long i)
 {
-    double th = 1.0;
-    for (int s = 0; s < mo.nsig; s++) {
-        const double G = gmax[s];
-        if (G > 0.0) {
-            const double r = grad[s * P + i] / G;
-            th += mo.form ? mo.alpha[s] * r : mo.alpha[s] * r * r;
-        }
-        if (mo.form && gmax[mo.nsig + s] > 0.0)
-            th += mo.beta[s] * (grad[(mo.nsig + s) * P + i] / gmax[mo.nsig + s]);
-    }
-    return sqrt(th);
+    double raw[MON_CH];
+    theta_load(raw, grad, theta_channels(mo, gmax), P, i);
+    return theta_of(mo, gmax, raw);
 }
 
 __global__ void k_theta(Geo g, MonitorP mo, const double* __restrict__ grad, const double* __restrict__ gmax,
@@ -1336,7 +1370,8 @@ __device__ __forceinline__ double limit(double lim, double xm, double x0, double
 // nodes outside the grid are read through the face rules and updated like
 // any other, which the updates commute with, so no launch needs or writes the
 // ghost layers of Theta or of the moving mesh.  800 x 160, five-variable
-// monitor, 3 filter passes, 10 Jacobi sweeps: 8 launches instead of 29.
+// monitor, 3 filter passes, 10 Jacobi sweeps: 8 launches instead of 29, 54
+// instead of 137 us.  A launch's loads are all issued before the first is used.
 // ---------------------------------------------------------------------------
 constexpr int TX2 = 32, TY2 = 16, STEPS2 = 5;
 constexpr int RX2 = TX2 + 2 * STEPS2, RY2 = TY2 + 2 * STEPS2;
@@ -1469,15 +1504,20 @@ k_filter2(Geo g, MonitorP mo, const double* __restrict__ in, const double* __res
     int ox, oy;
     tile2(g, ox, oy);
     const Region2 R(threadIdx.x);
+    // every load of the thread's nodes before the first is used
+    const int nch = theta_channels(mo, gmax);
+    double raw[R2S][MON_CH];
 #pragma unroll
     for (int r = 0; r < R2S; r++) {
-        if (R.e[r] > steps) continue;
         double sg, off;
-        const int ix = mesh_image(g, 0, ox + R.x[r] - STEPS2, sg, off);
-        const int iy = mesh_image(g, 1, oy + R.y[r] - STEPS2, sg, off);
-        const long i = (long)(iy + g.ng) * g.np[0] + (ix + g.ng);
-        F[0][R.y[r]][R.x[r]] = gmax ? theta_node(mo, in, gmax, g.P, i) : in[i];
+        const bool on = R.e[r] <= steps;
+        const int ix = on ? mesh_image(g, 0, ox + R.x[r] - STEPS2, sg, off) : 0;
+        const int iy = on ? mesh_image(g, 1, oy + R.y[r] - STEPS2, sg, off) : 0;
+        theta_load(raw[r], in, nch, g.P, (long)(iy + g.ng) * g.np[0] + (ix + g.ng));
     }
+#pragma unroll
+    for (int r = 0; r < R2S; r++)
+        if (R.e[r] <= steps) F[0][R.y[r]][R.x[r]] = theta_of(mo, gmax, raw[r]);
     __syncthreads();
     for (int p = 1; p <= steps; p++) {
         const double (*A)[RX2] = F[(p - 1) & 1];
@@ -1517,16 +1557,24 @@ k_jacobi2(Geo g, const double* __restrict__ th, const double* __restrict__ xa, d
     tile2(g, ox, oy);
     const Region2 R(threadIdx.x);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    // every load of the thread's nodes before the first is used
+    double t0[R2S], x0[R2S], x1[R2S], sg[R2S][2], of[R2S][2];
+#pragma unroll
+    for (int r = 0; r < R2S; r++) {
+        const bool on = R.e[r] <= steps;
+        const int ix = on ? mesh_image(g, 0, ox + R.x[r] - STEPS2, sg[r][0], of[r][0]) : 0;
+        const int iy = on ? mesh_image(g, 1, oy + R.y[r] - STEPS2, sg[r][1], of[r][1]) : 0;
+        const long i = (long)(iy + g.ng) * g.np[0] + (ix + g.ng);
+        t0[r] = th[i];
+        x0[r] = xa[i];
+        x1[r] = xa[P + i];
+    }
 #pragma unroll
     for (int r = 0; r < R2S; r++) {
         if (R.e[r] > steps) continue;
-        const int x = R.x[r], y = R.y[r];
-        double s0, b0, s1, b1;
-        const int ix = mesh_image(g, 0, ox + x - STEPS2, s0, b0), iy = mesh_image(g, 1, oy + y - STEPS2, s1, b1);
-        const long i = (long)(iy + g.ng) * g.np[0] + (ix + g.ng);
-        Ts[y][x] = th[i];
-        Xs[0][0][y][x] = fma(s0, xa[i], b0);
-        Xs[0][1][y][x] = fma(s1, xa[P + i], b1);
+        Ts[R.y[r]][R.x[r]] = t0[r];
+        Xs[0][0][R.y[r]][R.x[r]] = fma(sg[r][0], x0[r], of[r][0]);
+        Xs[0][1][R.y[r]][R.x[r]] = fma(sg[r][1], x1[r], of[r][1]);
     }
     __syncthreads();
     const double w0 = 1.0 / (g.dxi[0] * g.dxi[0]), w1 = 1.0 / (g.dxi[1] * g.dxi[1]);
@@ -1577,19 +1625,35 @@ k_jacobi2(Geo g, const double* __restrict__ th, const double* __restrict__ xa, d
         }
     }
     double b = 1.0;
+    bool own[R2S];
+    long at[R2S];
+    double nb[R2S][6];   // x_n there and on either side
 #pragma unroll
     for (int r = 0; r < R2S; r++) {
         const int x = ox + R.x[r] - STEPS2, y = oy + R.y[r] - STEPS2;
-        if (R.e[r] > 0 || x >= g.n[0] || y >= g.n[1]) continue;
-        const double v[2] = {Xs[steps & 1][0][R.y[r]][R.x[r]], Xs[steps & 1][1][R.y[r]][R.x[r]]};
-        const long i = (long)(y + g.ng) * g.np[0] + (x + g.ng);
-        xb[i] = v[0];
-        xb[P + i] = v[1];
+        own[r] = R.e[r] == 0 && x < g.n[0] && y < g.n[1];
+        at[r] = own[r] ? (long)(y + g.ng) * g.np[0] + (x + g.ng) : (long)g.ng * g.np[0] + g.ng;
         if (xn) {
+            const double *p = xn + at[r], *q = xn + P + at[r];
             const long n0 = g.np[0];
-            b = limit(b, v[0], xn[i], xn[i - 1], xn[i + 1]);
-            b = limit(b, v[1], xn[P + i], xn[P + i - n0], xn[P + i + n0]);
+            nb[r][0] = p[0];
+            nb[r][1] = p[-1];
+            nb[r][2] = p[1];
+            nb[r][3] = q[0];
+            nb[r][4] = q[-n0];
+            nb[r][5] = q[n0];
         }
+    }
+#pragma unroll
+    for (int r = 0; r < R2S; r++) {
+        if (!own[r]) continue;
+        const double v[2] = {Xs[steps & 1][0][R.y[r]][R.x[r]], Xs[steps & 1][1][R.y[r]][R.x[r]]};
+        if (xn) {
+            b = limit(b, v[0], nb[r][0], nb[r][1], nb[r][2]);
+            b = limit(b, v[1], nb[r][3], nb[r][4], nb[r][5]);
+        }
+        xb[at[r]] = v[0];
+        xb[P + at[r]] = v[1];
     }
     if (xn) {
         b = wave_min(b);
@@ -1639,8 +1703,10 @@ __global__ void k_disp(Geo g, const double* __restrict__ xmu, const double* __re
 }
 
 // ---------------------------------------------------------------------------
-// 3D: bound by HBM, so several filter passes or Jacobi sweeps walk z together.  A
-// block owns TX x TY columns over a chunk of z planes; every thread owns one
+// 3D: bound by HBM (two Jacobi sweeps move 1.33 GB at 4.4 TB/s), so several filter
+// passes or Jacobi sweeps walk z together; three sweeps leave one block a
+// compute unit and half of its columns halo, 3 + 2 sweeps took 73 us more than
+// 2 + 2 + 1.  A block owns TX x TY columns over a chunk of z planes; every thread owns one
 // column of the tile plus a halo of S nodes.  Step s of plane z runs as soon as
 // step s - 1 has reached plane z + 1; the planes it needs along z are the
 // thread's own registers, those in the plane are in LDS (double-buffered, one
@@ -1680,26 +1746,26 @@ k_filter3(Geo g, MonitorP mo, const double* __restrict__ in, const double* __res
     // (a column beyond a ragged tile's halo reads an image that no written node uses)
     const int ix = mesh_image(g, 0, min(gx, g.n[0] + S), sg, off), iy = mesh_image(g, 1, min(gy, g.n[1] + S), sg, off);
     const long col = (long)(iy + g.ng) * g.np[0] + (ix + g.ng), sz = (long)g.np[0] * g.np[1];
-    auto load = [&](int z) {
+    // PF planes in flight (a plane a round trip to memory left the block waiting)
+    constexpr int PF = 2;
+    const int nch = theta_channels(mo, gmax);
+    double next[PF][MON_CH];
+    auto load = [&](int u, int z) {
         double s_, o_;
-        const long i = col + (mesh_image(g, 2, z, s_, o_) + g.ng) * sz;
-        return gmax ? theta_node(mo, in, gmax, g.P, i) : in[i];
+        theta_load(next[u], in, nch, g.P, col + (mesh_image(g, 2, min(z, zc1 + S - 1), s_, o_) + g.ng) * sz);
     };
     const int row = __builtin_amdgcn_readfirstlane(ly);   // the wave's rows: this one and the next
     double q[S][3];   // in-plane sums of the last three planes after s passes
     double rx[S];     // the own sum along x of the last plane
 #pragma unroll
     for (int s = 0; s < S; s++) q[s][0] = q[s][1] = q[s][2] = rx[s] = 0.0;
-    // PF planes in flight (a plane a round trip to memory left the block waiting)
-    constexpr int PF = 2;
-    double next[PF];
     const unsigned plane = (unsigned)(sz * sizeof(double)), ob = own ? (unsigned)(col * sizeof(double)) : DROPPED;
     auto store = [&](int z, double v) {   // (a plane below the chunk: dropped)
         buffer_store<false>(out + (max(z, zc0) + g.ng) * sz, z >= zc0 ? plane : 0u, ob, v);
     };
 #pragma unroll
     for (int u = 0; u < PF; u++) {   // (with the store that a step has)
-        next[u] = load(min(zc0 - S + u, zc1 + S - 1));
+        load(u, zc0 - S + u);
         __builtin_amdgcn_sched_barrier(0);
         store(zc0 - 1 - u, 0.0);
         __builtin_amdgcn_sched_barrier(0);
@@ -1729,8 +1795,8 @@ k_filter3(Geo g, MonitorP mo, const double* __restrict__ in, const double* __res
                 else vo = v;
             }
             store(k - 2 * S, vo);
-            enter(0, next[u]);
-            next[u] = load(min(k + PF, zc1 + S - 1));
+            enter(0, theta_of(mo, gmax, next[u]));
+            load(u, k + PF);
             __syncthreads();
         }
     } while ((k0 += PF) < kend);
