@@ -147,7 +147,7 @@ typedef struct es_ctx es_ctx;
 /* Create a context for one grid on the current device: validates g, then
  * allocates and initialises the whole workspace of the context (status word,
  * reduction scratch, the metric, mesh and stage buffers of es_step and the
- * kept-metrics copy): 67 P doubles in 3D with two species (9.6 GB at
+ * kept-metrics copy): 56 P doubles in 3D with two species (8.1 GB at
  * 256^3).  This is the only call that allocates or synchronises the
  * device; every other call only launches work on its stream, so it may be
  * captured in a graph from its first use.  Owns only its workspace;

@@ -164,8 +164,7 @@ int dalloc(T** p, size_t count)
 }
 
 // the whole workspace of a context, allocated once by es_create and
-// initialised there (Theta's ghost layers read as 1 before the first fill,
-// and the kept mesh holds NaN, which no mesh equals)
+// initialised there (the kept mesh holds NaN, which no mesh equals)
 int alloc_workspace(es_ctx* c)
 {
     const size_t P = c->geo.P, d = c->geo.dim, nc = c->ph.nc;
@@ -187,8 +186,6 @@ int alloc_workspace(es_ctx* c)
     if (rc) return rc;
     const int one = 1;   // the reuse flag (step_begin only clears it)
     if (hipMemcpy(c->reuse, &one, sizeof(int), hipMemcpyHostToDevice) != hipSuccess) return ES_EHIP;
-    if (fill_value(c->mesh.th0, P, 1.0, 0) != hipSuccess) return ES_EHIP;
-    if (fill_value(c->mesh.th1, P, 1.0, 0) != hipSuccess) return ES_EHIP;
     if (fill_value(c->mx, d * P, std::numeric_limits<double>::quiet_NaN(), 0) != hipSuccess) return ES_EHIP;
     return hipDeviceSynchronize() == hipSuccess ? ES_OK : ES_EHIP;
 }

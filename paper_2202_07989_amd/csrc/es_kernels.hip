@@ -142,22 +142,6 @@ __device__ __forceinline__ int mesh_image(const Geo& g, int k, int i, double& sg
     return i;
 }
 
-// The grid-stride kernels of this file that produce a field also write its ghost
-// layers when given the shell sizes (nzs + nys + nxs > 0): a ghost node
-// takes the value of the interior node it wraps or mirrors to, computed again
-// with the same arithmetic, under the field's ghost rule.  That saves the
-// separate fill launch.
-__device__ __forceinline__ long shell_image(const Geo& g, long t, long nzs, long nys, int side[3], long& di)
-{
-    int d[3];
-    shell_node(g, t, nzs, nys, d);
-    int sidx[3] = {d[0], d[1], d[2]};
-    side[0] = side[1] = side[2] = 0;
-    for (int k = 0; k < g.dim; k++) sidx[k] = ghost_image(g, k, d[k], side[k]);
-    di = node_index(g, d[0], d[1], d[2]);
-    return node_index(g, sidx[0], sidx[1], sidx[2]);
-}
-
 // interior node q (0 .. nint-1) -> padded index
 // (32-bit index arithmetic, as in shell_node)
 __device__ __forceinline__ long interior_node(const Geo& g, long q, int& i0, int& i1, int& i2)
@@ -399,14 +383,6 @@ hipError_t set_scalar(double* dst, double v, hipStream_t s)
 // ---------------------------------------------------------------------------
 // GCL metrics (eq SCLCoeff, eq VCLCoeff).  Stage mesh xs = x_n + c_s disp.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double xs_at(const double* xn, const double* disp, double cs, long P, int p,
-                                        long i)
-{
-    double v = xn[p * P + i];
-    if (disp && cs != 0.0) v += cs * disp[p * P + i];
-    return v;
-}
-
 // z chunks of nz planes for `cols` columns of blocks, `slots` blocks at a time:
 // the number that leaves the shortest walk (rounds of blocks times planes a
 // block), each walk taking `extra` planes more than it writes.  A multiple of
@@ -1302,21 +1278,13 @@ __device__ __forceinline__ double theta_node(const MonitorP& mo, const double* g
 }
 
 __global__ void k_theta(Geo g, MonitorP mo, const double* __restrict__ grad, const double* __restrict__ gmax,
-                        double* __restrict__ theta, long nzs, long nys, long nxs)
+                        double* __restrict__ theta)
 {
-    const long P = g.P;
     const long nint = n_interior(g);
     for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < nint; q += (long)gridDim.x * blockDim.x) {
         int i0, i1, i2;
         const long i = interior_node(g, q, i0, i1, i2);
-        theta[i] = theta_node(mo, grad, gmax, P, i);
-    }
-    for (long t = blockIdx.x * (long)blockDim.x + threadIdx.x; t < nzs + nys + nxs;
-         t += (long)gridDim.x * blockDim.x) {
-        int side[3];
-        long di;
-        const long si = shell_image(g, t, nzs, nys, side, di);
-        theta[di] = theta_node(mo, grad, gmax, P, si);
+        theta[i] = theta_node(mo, grad, gmax, g.P, i);
     }
 }
 
@@ -1712,7 +1680,7 @@ __global__ void k_disp(Geo g, const double* __restrict__ xmu, const double* __re
 // thread's own registers, those in the plane are in LDS (double-buffered, one
 // barrier a plane), and its halo is one node narrower.  Nodes outside the grid
 // are read through the face rules, as in 2D.  A launch then reads and writes a
-// field once for S steps: at 256^3 three filter passes take 172 us instead
+// field once for S steps: at 256^3 three filter passes take 123 us instead
 // of 3 x 97 us and two Jacobi sweeps 300 us instead of 2 x 307 us (each with the
 // ghost fill that they needed).
 // ---------------------------------------------------------------------------
@@ -1725,7 +1693,8 @@ struct Column3 {
 // the product of (1/4, 1/2, 1/4) along each direction, so a pass is the
 // in-plane sum q of each plane and out = q(z-1)/4 + q(z)/2 + q(z+1)/4.  The sum
 // along x comes from the neighbouring lanes (a wave is two rows), which leaves two
-// LDS reads a pass instead of nine: 172 instead of 260 us for three.  With
+// LDS reads a pass instead of nine: 172 instead of 260 us for three, and 123 with
+// the monitor channels prefetched.  With
 // gmax, theta is formed from the monitor's gradients `in` first
 template <int TX, int TY, int S>
 __global__ void __launch_bounds__((Column3<TX, TY, S>::NT))
@@ -2051,9 +2020,7 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
         if (!d3) {
             hipLaunchKernelGGL(k_filter2, tiles2(g), dim3(NT2), 0, s, g, mo, in, gmax, th2, steps);
         } else if (steps == 0) {
-            long nzs, nys, nxs;
-            shell_sizes(g, nzs, nys, nxs);
-            hipLaunchKernelGGL(k_theta, dim3(grid_for(nint)), dim3(256), 0, s, g, mo, in, gmax, th2, nzs, nys, nxs);
+            hipLaunchKernelGGL(k_theta, dim3(grid_for(nint)), dim3(256), 0, s, g, mo, in, gmax, th2);
         } else {
             if (steps == 1) march(k_filter3<30, 20, 1>, 30, 20, 704, 3, mo, in, gmax, th2);
             else if (steps == 2) march(k_filter3<28, 18, 2>, 28, 18, 704, 6, mo, in, gmax, th2);
