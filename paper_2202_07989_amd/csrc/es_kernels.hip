@@ -383,6 +383,23 @@ hipError_t set_scalar(double* dst, double v, hipStream_t s)
 // ---------------------------------------------------------------------------
 // GCL metrics (eq SCLCoeff, eq VCLCoeff).  Stage mesh xs = x_n + c_s disp.
 // ---------------------------------------------------------------------------
+// a double of the `bytes` at base, both the same for the whole wave; a store at or
+// past the end is dropped.  A marching kernel stores through it without a
+// branch: behind a branch the compiler does not know how many stores follow a
+// load, and its wait for a load of two planes ago also drains the last plane's
+__device__ __forceinline__ double buffer_load(const double* base, unsigned bytes, unsigned at)
+{
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(base), 0, bytes, 0x00027000);
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, 0));
+}
+__device__ __forceinline__ void buffer_store(double* base, unsigned bytes, unsigned at, double v)
+{
+    using U2 = __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned;
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00027000);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r, at, 0, 0);
+}
+constexpr unsigned DROPPED = 0xfffffff8u;
+
 // z chunks of nz planes for `cols` columns of blocks, `slots` blocks at a time:
 // the number that leaves the shortest walk (rounds of blocks times planes a
 // block), each walk taking `extra` planes more than it writes.  A multiple of
@@ -423,17 +440,20 @@ static int z_chunk(int nz, long cols, int extra, int slots)
 // plane k + 1 are written while the metrics of plane k - 4 are formed.
 // x is loaded two planes ahead, and its wait comes before the plane's stores (behind
 // them, in order, it would drain them first).
-//   256^3, ghost fill included: 1153 us (two passes 1735 us).  Two barriers a
-// plane 1249, one thread a column (512 of them) 1276, 48 x 10 columns of those
-// 1537, 64 x 8 1610; stores without the non-temporal hint 200 us more.  Bound
-// by LDS and FP64 issue, whose bursts the barrier keeps apart.
-__device__ __forceinline__ double cdiff(const double* al, double p1, double m1, double p2, double m2,
+//   256^3, ghost fill included: 1040 us (two passes 1735 us).  Seven planes are
+// unrolled, so that the rings stay in place (1153 us with the moves).  Bound by the
+// stores, rows of 26 doubles at any alignment: without them 723 us; with the
+// non-temporal hint, which keeps neighbouring tiles' parts of a line from meeting in
+// the L2, 1143.  Two barriers a plane took 1249 us, one thread a column (512 of
+// them) 1276, 48 x 10 columns of those 1537, 64 x 8 1610.
+// (with the halves of alpha: the factor 1/2 of each difference is exact)
+__device__ __forceinline__ double cdiff(const double* ah, double p1, double m1, double p2, double m2,
                                         double p3, double m3)
 {
-    double s = al[0] * (p1 - m1);
-    s += al[1] * (p2 - m2);
-    s += al[2] * (p3 - m3);
-    return 0.5 * s;
+    double s = ah[0] * (p1 - m1);
+    s += ah[1] * (p2 - m2);
+    s += ah[2] * (p3 - m3);
+    return s;
 }
 
 template <int HX, int HY, bool MOVED>
@@ -465,19 +485,18 @@ k_metric3(Geo g, Phys ph, const double* __restrict__ xn, const double* __restric
     const double idt = dt > 0.0 ? 1.0 / dt : 0.0;   // mesh velocity = disp / dt
     const bool moving = jxt && disp && dt > 0.0;
     const double* wsrc = moving ? disp : xn;   // (read in any case)
-    const double al[3] = {ph.alpha[0], ph.alpha[1], ph.alpha[2]};
+    const double ah[3] = {0.5 * ph.alpha[0], 0.5 * ph.alpha[1], 0.5 * ph.alpha[2]};
     const double s01 = g.idxi[0] * g.idxi[1], s12 = g.idxi[1] * g.idxi[2], s20 = g.idxi[2] * g.idxi[0];
     const unsigned cb = (unsigned)((min(gy, np1 - 1) * np0 + min(gx, np0 - 1)) * sizeof(double));
-    auto at = [&](auto* f, int c, int z) -> auto& {   // component c of the own column at plane z
-        using T = std::remove_reference_t<decltype(*f)>;
-        using B = std::conditional_t<std::is_const_v<T>, const char, char>;
-        return *reinterpret_cast<T*>(reinterpret_cast<B*>(f + (c * P + z * sz)) + cb);
-    };
+    const unsigned plane = (unsigned)(sz * sizeof(double));
+    auto load = [&](const double* f, int c, int z) { return buffer_load(f + (c * P + z * sz), plane, cb); };
+    auto store = [&](double* f, int c, int z, double v) { buffer_store(f + (c * P + z * sz), plane, cb, v); };
     // the waves of the two halves take different walks, each with the same
     // barrier a plane
     auto walk = [&](auto half) {
         constexpr bool A = half == 0;
-        double pr[3][7], xr[A ? 3 : 1][7];   // planes k - 6 .. k of the own column: Pr[1] (A) or Pr[0]; xs
+        // planes of the own column, plane zc0 - 3 + i in slot i % 7: Pr[1] (A) or Pr[0]; xs
+        double pr[3][7], xr[A ? 3 : 1][7];
 #pragma unroll
         for (int j = 0; j < 3; j++)
 #pragma unroll
@@ -489,8 +508,8 @@ k_metric3(Geo g, Phys ph, const double* __restrict__ xn, const double* __restric
         auto fetch = [&](int z) {
 #pragma unroll
             for (int p = 0; p < 3; p++) {
-                nx[p] = at(xn, p, z);
-                if constexpr (MOVED) nd[p] = at(dx, p, z);
+                nx[p] = load(xn, p, z);
+                if constexpr (MOVED) nd[p] = load(dx, p, z);
             }
         };
         auto stage = [&](int z) {   // plane z into X; the next one on its way
@@ -506,44 +525,50 @@ k_metric3(Geo g, Phys ph, const double* __restrict__ xn, const double* __restric
             stage(zc0 - 3);
         }
         __syncthreads();
-#pragma unroll 1
-        for (int k = zc0 - 3;; k++) {
+        // (seven planes a pass, so that no ring is moved)
+        for (int k0 = zc0 - 3;; k0 += 7)
+#pragma unroll
+        for (int u = 0; u < 7; u++) {
+            const int k = k0 + u;
             // the metrics of plane z, whose products are in E since the last
             // barrier.  Each half folds its metrics into its time metrics (the
             // sum over j in the order of k_vcl)
             const int z = k - 4;
             if constexpr (!A)
                 if (k + 1 < zc1 + 3) stage(k + 1);
+            // difference along z of a ring at plane z, its last plane in slot u - 1
+            auto zdiff = [&](const double (&q)[7], int u) {
+                return cdiff(ah, q[(u + 4) % 7], q[(u + 2) % 7], q[(u + 5) % 7], q[(u + 1) % 7], q[(u + 6) % 7], q[u % 7]);
+            };
             if (own && z >= zc0) {
                 double nt[2] = {0.0, 0.0};
 #pragma unroll
                 for (int j = 0; j < 3; j++) {
                     const double v = moving ? w[j] * idt : 0.0;
-                    const double *e0 = &E[z & 1][0][j][t], *e1 = &E[z & 1][1][j][t], *e2 = &E[z & 1][2][j][t], *q = pr[j];
+                    const double *e0 = &E[z & 1][0][j][t], *e1 = &E[z & 1][1][j][t], *e2 = &E[z & 1][2][j][t];
+                    const double zd = zdiff(pr[j], u);
                     if constexpr (A) {   // k = 0 (a = 1, b = 2): delta_2 Pr[1][j] - delta_1 Pr[2][j]
-                        const double M = (cdiff(al, q[4], q[2], q[5], q[1], q[6], q[0]) -
-                                          cdiff(al, e2[HX], e2[-HX], e2[2 * HX], e2[-2 * HX], e2[3 * HX], e2[-3 * HX])) * s12;
-                        __builtin_nontemporal_store(M, &at(jxx, j, z));
+                        const double M = (zd - cdiff(ah, e2[HX], e2[-HX], e2[2 * HX], e2[-2 * HX], e2[3 * HX], e2[-3 * HX])) * s12;
+                        store(jxx, j, z, M);
                         nt[0] -= v * M;
                     } else {
                         // k = 1 (a = 2, b = 0): delta_0 Pr[2][j] - delta_2 Pr[0][j]
-                        const double M1 = (cdiff(al, e2[1], e2[-1], e2[2], e2[-2], e2[3], e2[-3]) -
-                                           cdiff(al, q[4], q[2], q[5], q[1], q[6], q[0])) * s20;
+                        const double M1 = (cdiff(ah, e2[1], e2[-1], e2[2], e2[-2], e2[3], e2[-3]) - zd) * s20;
                         // k = 2 (a = 0, b = 1): delta_1 Pr[0][j] - delta_0 Pr[1][j]
-                        const double M2 = (cdiff(al, e0[HX], e0[-HX], e0[2 * HX], e0[-2 * HX], e0[3 * HX], e0[-3 * HX]) -
-                                           cdiff(al, e1[1], e1[-1], e1[2], e1[-2], e1[3], e1[-3])) * s01;
-                        __builtin_nontemporal_store(M1, &at(jxx, 3 + j, z));
-                        __builtin_nontemporal_store(M2, &at(jxx, 6 + j, z));
+                        const double M2 = (cdiff(ah, e0[HX], e0[-HX], e0[2 * HX], e0[-2 * HX], e0[3 * HX], e0[-3 * HX]) -
+                                           cdiff(ah, e1[1], e1[-1], e1[2], e1[-2], e1[3], e1[-3])) * s01;
+                        store(jxx, 3 + j, z, M1);
+                        store(jxx, 6 + j, z, M2);
                         nt[0] -= v * M1;
                         nt[1] -= v * M2;
                     }
                 }
                 if (jxt) {
-                    __builtin_nontemporal_store(nt[0], &at(jxt, A ? 0 : 1, z));
-                    if constexpr (!A) __builtin_nontemporal_store(nt[1], &at(jxt, 2, z));
+                    store(jxt, A ? 0 : 1, z, nt[0]);
+                    if constexpr (!A) store(jxt, 2, z, nt[1]);
                 }
             }
-            if (k == zc1 + 3) break;
+            if (k == zc1 + 3) return;
             // Pr[1] (rows within the halo) or Pr[0] (columns within the halo) of plane k
             double d[3] = {0.0, 0.0, 0.0};
             if (!A || row)
@@ -551,7 +576,7 @@ k_metric3(Geo g, Phys ph, const double* __restrict__ xn, const double* __restric
                 for (int p = 0; p < 3; p++) {
                     constexpr int st = A ? HX : 1;
                     const double* F = &X[k & 1][p][t + 3];
-                    d[p] = cdiff(al, F[st], F[-st], F[2 * st], F[-2 * st], F[3 * st], F[-3 * st]);
+                    d[p] = cdiff(ah, F[st], F[-st], F[2 * st], F[-2 * st], F[3 * st], F[-3 * st]);
                 }
             double v[3];
 #pragma unroll
@@ -559,24 +584,17 @@ k_metric3(Geo g, Phys ph, const double* __restrict__ xn, const double* __restric
             // and the products of plane k - 3
 #pragma unroll
             for (int j = 0; j < 3; j++) {
-#pragma unroll
-                for (int r = 0; r < 6; r++) {
-                    pr[j][r] = pr[j][r + 1];
-                    if constexpr (A) xr[j][r] = xr[j][r + 1];
-                }
-                pr[j][6] = d[(j + 1) % 3] * v[(j + 2) % 3];
-                if constexpr (A) xr[j][6] = v[j];
-                E[(k + 1) & 1][A][j][t] = pr[j][3];
+                pr[j][u] = d[(j + 1) % 3] * v[(j + 2) % 3];
+                if constexpr (A) xr[j][u] = v[j];
+                E[(k + 1) & 1][A][j][t] = pr[j][(u + 4) % 7];
             }
             if constexpr (A) {
 #pragma unroll
-                for (int j = 0; j < 3; j++) {
-                    const double* q = xr[(j + 1) % 3];
-                    E[(k + 1) & 1][2][j][t] = cdiff(al, q[4], q[2], q[5], q[1], q[6], q[0]) * xr[(j + 2) % 3][3];
-                }
+                for (int j = 0; j < 3; j++)
+                    E[(k + 1) & 1][2][j][t] = zdiff(xr[(j + 1) % 3], u + 1) * xr[(j + 2) % 3][(u + 4) % 7];
             }
 #pragma unroll
-            for (int j = 0; j < 3; j++) w[j] = at(wsrc, j, max(k - 3, zc0));
+            for (int j = 0; j < 3; j++) w[j] = load(wsrc, j, max(k - 3, zc0));
             __syncthreads();
         }
     };
@@ -613,7 +631,7 @@ __global__ void k_metric2(Geo g, Phys ph, const double* __restrict__ xn,
 #pragma unroll
         for (int c = 0; c < 4; c++) M[c] = jxx[c * P + i];
     } else {
-        const double al[3] = {ph.alpha[0], ph.alpha[1], ph.alpha[2]};   // 0 beyond w
+        const double ah[3] = {0.5 * ph.alpha[0], 0.5 * ph.alpha[1], 0.5 * ph.alpha[2]};   // 0 beyond w
         const bool moved = disp && cs != 0.0;
         // all loads first (one behind a branch is waited for on the spot)
         auto node = [&](int a, int p, int m) {   // +1 +2 +3 -1 -2 -3 along a, component p
@@ -635,7 +653,7 @@ __global__ void k_metric2(Geo g, Phys ph, const double* __restrict__ xn,
 #pragma unroll
             for (int p = 0; p < 2; p++) {
                 const double* h = f[a][p];
-                d[a][p] = cdiff(al, h[0], h[3], h[1], h[4], h[2], h[5]);
+                d[a][p] = cdiff(ah, h[0], h[3], h[1], h[4], h[2], h[5]);
             }
         M[0] = d[1][1] * g.idxi[1];
         M[1] = -d[1][0] * g.idxi[1];
@@ -1301,24 +1319,6 @@ __device__ __forceinline__ double lane_shift(double v)
 __device__ __forceinline__ double lane_below(double v) { return lane_shift<0x138>(v); }   // wave shift right by one
 __device__ __forceinline__ double lane_above(double v) { return lane_shift<0x130>(v); }   // wave shift left by one
 
-// a double of the `bytes` at base, both the same for the whole wave; a store at or
-// past the end is dropped.  A marching kernel stores through it without a
-// branch: behind a branch the compiler does not know how many stores follow a
-// load, and its wait for a load of two planes ago also drains the last plane's
-__device__ __forceinline__ double buffer_load(const double* base, unsigned bytes, unsigned at)
-{
-    const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(base), 0, bytes, 0x00027000);
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, 0));
-}
-template <bool NT>
-__device__ __forceinline__ void buffer_store(double* base, unsigned bytes, unsigned at, double v)
-{
-    using U2 = __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned;
-    const auto r = __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00027000);
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r, at, 0, NT ? 2 : 0);
-}
-constexpr unsigned DROPPED = 0xfffffff8u;
-
 // lim lowered to the movement limiter's bound for one coordinate that moves
 // from x0 to xm between the neighbours lo and hi (1 if it does not move).  The
 // quotient is taken only where a product says that it may be below lim, which at
@@ -1730,7 +1730,7 @@ k_filter3(Geo g, MonitorP mo, const double* __restrict__ in, const double* __res
     for (int s = 0; s < S; s++) q[s][0] = q[s][1] = q[s][2] = rx[s] = 0.0;
     const unsigned plane = (unsigned)(sz * sizeof(double)), ob = own ? (unsigned)(col * sizeof(double)) : DROPPED;
     auto store = [&](int z, double v) {   // (a plane below the chunk: dropped)
-        buffer_store<false>(out + (max(z, zc0) + g.ng) * sz, z >= zc0 ? plane : 0u, ob, v);
+        buffer_store(out + (max(z, zc0) + g.ng) * sz, z >= zc0 ? plane : 0u, ob, v);
     };
 #pragma unroll
     for (int u = 0; u < PF; u++) {   // (with the store that a step has)
@@ -1834,7 +1834,7 @@ k_jacobi3(Geo g, const double* __restrict__ th, const double* __restrict__ xa, d
         const bool on = z >= zc0 && z < zc1;
 #pragma unroll
         for (int c = 0; c < 3; c++)
-            buffer_store<false>(xb + c * P + ((on ? z : zc0) + g.ng) * sz, on ? plane : 0u, ob, v[c]);
+            buffer_store(xb + c * P + ((on ? z : zc0) + g.ng) * sz, on ? plane : 0u, ob, v[c]);
     };
 #pragma unroll
     for (int u = 0; u < PF; u++) {   // (with the stores that a step has)
