@@ -402,17 +402,21 @@ constexpr unsigned DROPPED = 0xfffffff8u;
 
 // z chunks of nz planes for `cols` columns of blocks, `slots` blocks at a time:
 // the number that leaves the shortest walk (rounds of blocks times planes a
-// block), each walk taking `extra` planes more than it writes.  A multiple of
-// 8, where each XCD walks whole chunks and so finds its tiles' neighbours in its
-// own L2, may be a tenth longer (two Jacobi sweeps at 256^3: 8 chunks 280 us, 2
-// chunks 306)
+// block), each walk taking `extra` planes more than it writes.  A block that has a
+// compute unit to itself walks faster, by a third at least (64^3 mesh step 100 us; with
+// the units doubled up for shorter chunks 111).  A multiple of 8, where each XCD
+// walks whole chunks and so finds its tiles' neighbours in its own L2, may be a
+// tenth longer (two Jacobi sweeps at 256^3: 8 chunks 280 us, 2 chunks 306)
 static int z_chunk(int nz, long cols, int extra, int slots)
 {
+    constexpr int UNITS = 256;
     double best = -1.0;
     int chunk = nz;
-    for (int c = 1; c <= std::max(1, nz / 8); c++) {
+    // (past four rounds a shorter chunk only adds its extra planes)
+    for (int c = 1; c <= std::max(1L, std::min((long)nz / 2, 4 * slots / cols + 8)); c++) {
         const int zc = (nz + c - 1) / c, n = (nz + zc - 1) / zc;
-        const double walk = (double)((cols * n + slots - 1) / slots) * (zc + extra) * (n % 8 == 0 ? 0.9 : 1.0);
+        const double rounds = slots > UNITS && cols * n <= UNITS ? 0.75 : (double)((cols * n + slots - 1) / slots);
+        const double walk = rounds * (zc + extra) * (n % 8 == 0 ? 0.9 : 1.0);
         if (best < 0.0 || walk < best) {
             best = walk;
             chunk = zc;
@@ -1117,92 +1121,84 @@ __device__ __forceinline__ double sigma_of(const Phys& ph, const double* JU, con
     return s.p;
 }
 
-// 3D monitor gradient walking z (second-order central differences): each thread owns one (x, y) column of a 64 x 4 block over a chunk of z
-// planes.  Sigma is evaluated once per node of each plane of the tile plus
-// a 1-node in-plane halo (corners excepted) into a two-plane LDS buffer, so
-// the in-plane neighbours and the plane above come from LDS and sigma at
-// z-1 from a register: 1.5 evaluations per node instead of 5.
+// the value of the lane below or above this one in the wave (0 past its ends); every
+// lane of the wave has to take part
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double v)
+{
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, true);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+__device__ __forceinline__ double lane_below(double v) { return lane_shift<0x138>(v); }   // wave shift right by one
+__device__ __forceinline__ double lane_above(double v) { return lane_shift<0x130>(v); }   // wave shift left by one
+
+// 3D monitor gradient walking z (second-order central differences): a block owns
+// 30 x 14 columns over a chunk of z planes, every thread a column of these and a
+// one-node halo (a row is 32 lanes).  A variable is evaluated once per node of
+// the patch, 1.2 times per owned node; its neighbours along x are the
+// neighbouring lanes', along y in LDS (two planes), along z the thread's own
+// (256^3, density: 170 us; 64 x 4 columns with all neighbours in LDS 205).
 template <int N, int SIG>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(512)
 k_monitor_grad3(Phys ph, Geo g, MonitorP mo, const double* __restrict__ JU, const double* __restrict__ Jv,
                 double* __restrict__ grad, double* __restrict__ gmax, int zchunk)
 {
-    constexpr int D = 3;
-    __shared__ double Sg[2][6][66];
+    constexpr int D = 3, TX = 30, TY = 14, HX = 32;
+    __shared__ double Sg[2][512 + 2 * HX];   // (a row on either side, read and not used)
     const long P = g.P;
     const int np0 = g.np[0], np1 = g.np[1];
     int bx, by, bz;
-    xcd_tile((g.n[0] + 63) / 64, (g.n[1] + 3) / 4, bx, by, bz);
-    const int lx = (int)(threadIdx.x & 63), ly = (int)(threadIdx.x >> 6);
-    const int xt = g.ng + bx * 64, yt = g.ng + by * 4;
-    const int x = xt + lx, y = yt + ly;
-    const int zc0 = g.ng + bz * zchunk, zc1 = min(zc0 + zchunk, g.ng + g.n[2]);
-    const bool in = x < g.ng + g.n[0] && y < g.ng + g.n[1];
-    const long sz = (long)np0 * np1;
+    xcd_tile((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, bx, by, bz);
+    const int t = threadIdx.x, lx = t % HX, ly = t / HX;
+    const int gx = bx * TX + lx - 1, gy = by * TY + ly - 1;
+    const bool own = lx >= 1 && lx <= TX && ly >= 1 && ly <= TY && gx < g.n[0] && gy < g.n[1];
+    const int zc0 = bz * zchunk, zc1 = min(zc0 + zchunk, g.n[2]);
+    // (a column beyond a ragged tile's halo reads the nearest one, which no written node uses)
+    const long sz = (long)np0 * np1, col = (long)(min(gy, g.n[1]) + g.ng) * np0 + min(gx, g.n[0]) + g.ng;
     double ih[3];
 #pragma unroll
     for (int k = 0; k < 3; k++) ih[k] = 1.0 / (2.0 * g.dxi[k]);
-    // sigma of channel sg at plane zz of the patch into buffer b
-    auto stage = [&](int b, int zz, int sg) {
-        for (int q = threadIdx.x; q < 6 * 66; q += 256) {
-            const int hx = q % 66, hy = q / 66;
-            const bool corner = (hx == 0 || hx == 65) && (hy == 0 || hy == 5);
-            const int gx = xt - 1 + hx, gy = yt - 1 + hy;
-            if (!corner && gx < np0 && gy < np1)
-                Sg[b][hy][hx] = sigma_of<N, D, SIG>(ph, JU, Jv, P, ((long)zz * np1 + gy) * np0 + gx, sg, mo.phi);
-        }
-    };
-    double gm[MON_CH] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (zc0 < zc1) {   // uniform over the block
-        for (int s = 0; s < mo.nsig; s++) {
-            const int sg = mo.sigma[s];
-            long i = ((long)zc0 * np1 + y) * np0 + x;
-            double sm = in ? sigma_of<N, D, SIG>(ph, JU, Jv, P, i - sz, sg, mo.phi) : 0.0;
-            double mg = 0.0, ml = 0.0;     // this channel's maxima over the column
-            int cur = 0;
-            stage(cur, zc0, sg);
-            for (int z = zc0; z < zc1; z++, i += sz) {
-                stage(cur ^ 1, z + 1, sg);
-                __syncthreads();
-                if (in) {
-                    const int hx = lx + 1, hy = ly + 1;
-                    const double s0 = Sg[cur][hy][hx];
-                    const double sp = Sg[cur ^ 1][hy][hx];
-                    const double xp = Sg[cur][hy][hx + 1];
-                    const double xm = Sg[cur][hy][hx - 1];
-                    const double yp = Sg[cur][hy + 1][hx];
-                    const double ym = Sg[cur][hy - 1][hx];
-                    const double d0 = (xp - xm) * ih[0];
-                    const double d1 = (yp - ym) * ih[1];
-                    const double d2 = (sp - sm) * ih[2];
-                    const double gv = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-                    grad[s * P + i] = gv;
-                    mg = fmax(mg, gv);
-                    if (mo.form) {   // directions 0, 1, 2 in order
-                        double lap = (xp - 2.0 * s0 + xm) / (g.dxi[0] * g.dxi[0]);
-                        lap += (yp - 2.0 * s0 + ym) / (g.dxi[1] * g.dxi[1]);
-                        lap += (sp - 2.0 * s0 + sm) / (g.dxi[2] * g.dxi[2]);
-                        grad[(mo.nsig + s) * P + i] = fabs(lap);
-                        ml = fmax(ml, fabs(lap));
-                    }
-                    sm = s0;
+    for (int s = 0; s < mo.nsig && zc0 < zc1; s++) {   // uniform over the block
+        const int sg = mo.sigma[s];
+        auto sigma = [&](int z) { return sigma_of<N, D, SIG>(ph, JU, Jv, P, col + (z + g.ng) * sz, sg, mo.phi); };
+        double sm = sigma(zc0 - 1), s0 = sigma(zc0);
+        double mg = 0.0, ml = 0.0;     // this channel's maxima over the column
+        Sg[zc0 & 1][HX + t] = s0;
+        __syncthreads();
+        for (int z = zc0; z < zc1; z++) {
+            const double sp = sigma(z + 1);
+            const double xp = lane_above(s0), xm = lane_below(s0);
+            const double* A = &Sg[z & 1][HX + t];
+            const double yp = A[HX], ym = A[-HX];
+            const double d0 = (xp - xm) * ih[0];
+            const double d1 = (yp - ym) * ih[1];
+            const double d2 = (sp - sm) * ih[2];
+            const double gv = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+            const long i = col + (z + g.ng) * sz;
+            if (own) {
+                grad[s * P + i] = gv;
+                mg = fmax(mg, gv);
+                if (mo.form) {   // directions 0, 1, 2 in order
+                    double lap = (xp - 2.0 * s0 + xm) / (g.dxi[0] * g.dxi[0]);
+                    lap += (yp - 2.0 * s0 + ym) / (g.dxi[1] * g.dxi[1]);
+                    lap += (sp - 2.0 * s0 + sm) / (g.dxi[2] * g.dxi[2]);
+                    grad[(mo.nsig + s) * P + i] = fabs(lap);
+                    ml = fmax(ml, fabs(lap));
                 }
-                __syncthreads();   // the next plane overwrites buffer cur
-                cur ^= 1;
             }
-#pragma unroll
-            for (int c = 0; c < MON_CH; c++) {
-                if (c == s) gm[c] = mg;
-                if (mo.form && c == mo.nsig + s) gm[c] = ml;
-            }
+            Sg[(z + 1) & 1][HX + t] = sp;
+            sm = s0;
+            s0 = sp;
+            __syncthreads();
         }
-    }
-    const int nch = mo.form ? 2 * mo.nsig : mo.nsig;
-#pragma unroll
-    for (int s = 0; s < MON_CH; s++) {
-        if (s >= nch) break;   // uniform
-        const double r = block_reduce<RED_MAX>(gm[s]);
-        if (threadIdx.x == 0) scalar_max(gmax + s, r);
+        mg = wave_max(mg);
+        if ((t & 63) == 0) scalar_max(gmax + s, mg);
+        if (mo.form) {
+            ml = wave_max(ml);
+            if ((t & 63) == 0) scalar_max(gmax + mo.nsig + s, ml);
+        }
     }
 }
 
@@ -1305,19 +1301,6 @@ __global__ void k_theta(Geo g, MonitorP mo, const double* __restrict__ grad, con
         theta[i] = theta_node(mo, grad, gmax, g.P, i);
     }
 }
-
-// the value of the lane below or above this one in the wave (0 past its ends); every
-// lane of the wave has to take part
-template <int CTRL>
-__device__ __forceinline__ double lane_shift(double v)
-{
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, true);
-    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
-}
-__device__ __forceinline__ double lane_below(double v) { return lane_shift<0x138>(v); }   // wave shift right by one
-__device__ __forceinline__ double lane_above(double v) { return lane_shift<0x130>(v); }   // wave shift left by one
 
 // lim lowered to the movement limiter's bound for one coordinate that moves
 // from x0 to xm between the neighbours lo and hi (1 if it does not move).  The
@@ -1995,12 +1978,11 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
     if (use_phi)
         ES_DISPATCH_ND(ph, g, launch_schlieren, ph, g, mo, JU, J, w.th1, w.scal + 7, w.phi, red_grid(nint),
                        grid_for(nint), s);
-    // monitor and its global maxima (3D: z chunks of 64 x 4 columns, about 2048 blocks)
+    // monitor and its global maxima (3D: three blocks a compute unit, two with the pressure)
     if (d3) {
-        const int jx = (g.n[0] + 63) / 64, jy = (g.n[1] + 3) / 4;
-        const int jz = std::max(1, std::min(g.n[2], 2048 / (jx * jy))), zc = (g.n[2] + jz - 1) / jz;
+        const int jx = (g.n[0] + 29) / 30, jy = (g.n[1] + 13) / 14, zc = z_chunk(g.n[2], (long)jx * jy, 2, sigmode ? 512 : 768);
         hipLaunchKernelGGL(ph.nspec == 1 ? monitor3_kernel<1>(sigmode) : monitor3_kernel<2>(sigmode),
-                           dim3(jx * jy * ((g.n[2] + zc - 1) / zc)), dim3(256), 0, s, ph, g, mo, JU, J, w.grad, w.scal, zc);
+                           dim3(jx * jy * ((g.n[2] + zc - 1) / zc)), dim3(512), 0, s, ph, g, mo, JU, J, w.grad, w.scal, zc);
     } else {
         hipLaunchKernelGGL(ph.nspec == 1 ? monitor2_kernel<1>(sigmode) : monitor2_kernel<2>(sigmode), tiles2(g), dim3(256),
                            0, s, ph, g, mo, JU, J, w.grad, w.scal);
