@@ -433,7 +433,7 @@ static int z_chunk(int nz, long cols, int extra, int slots)
 // (alpha_m = 0 for m > w).
 //   A block owns (HX - 6) x (HY - 6) columns over a chunk of z planes and forms
 // the products of these and of a 3-node halo around them, so they never go to
-// memory: at 256^3 the walk moves 3.4 GB (2.4 GB of x, disp and the metrics
+// memory: at 256^3 the walk moves 3.3 GB (2.4 GB of x, disp and the metrics
 // themselves) where two passes with the nine products between them moved 7.2.
 // Differences along z come from 7 planes of the thread's own column in
 // registers: x, Pr[0] and Pr[1].  All three are 126 registers, two waves a SIMD,
