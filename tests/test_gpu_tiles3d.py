@@ -1,7 +1,8 @@
-"""3D mesh step and metrics at the edges of their tiles: filter passes (32 x 12 columns, up to
-three a launch) and Jacobi sweeps (28 x 12 columns two a launch, 30 x 14 one),
-over one and several z chunks, on grids around the tile sizes and smaller than a
-halo, with every kind of face, against the oracle at the FP64 parity bar."""
+"""3D mesh step and metrics at the edges of their tiles: the monitor (30 x 14
+columns), filter passes (26 x 16 columns three a launch, 28 x 18 two, 30 x 20 one)
+and Jacobi sweeps (28 x 12 two a launch, 30 x 14 one), over one and several z
+chunks, on grids around the tile sizes and smaller than a halo, with every kind
+of face, against the oracle at the FP64 parity bar."""
 import numpy as np
 import pytest
 import torch
@@ -22,7 +23,8 @@ STIFF = dict(gamma=(3.0, 1.4), cv=(1.0, 1.0), pinf=(100.0, 0.0))
 
 
 @pytest.mark.parametrize("faces", list(FACES))
-@pytest.mark.parametrize("n", [(3, 3, 3), (28, 13, 5), (29, 12, 3), (31, 15, 17), (33, 11, 40), (5, 26, 9)])
+@pytest.mark.parametrize("n", [(3, 3, 3), (28, 13, 5), (29, 12, 3), (31, 15, 17), (33, 11, 40), (5, 26, 9),
+                               (27, 17, 6), (30, 20, 4), (61, 15, 7)])
 @pytest.mark.parametrize("smooth,sweeps", [(0, 0), (0, 1), (1, 2), (2, 3), (3, 4), (7, 5)])
 def test_mesh_step(faces, n, smooth, sweeps):
     say(f"[mesh tiles 3D] {faces} {n} smooth={smooth} sweeps={sweeps}")
