@@ -1052,6 +1052,9 @@ hipError_t entropy_sum(const Phys& ph, const Geo& g, const double* JU, const dou
 // The kernels keep a maximum or minimum over all blocks in a device scalar
 // that the call's first launch resets (order does not matter, so the result
 // is the two-pass reduction's): non-negative doubles compare like their bits.
+// One thread a block takes part: the atomics of one address follow one another,
+// and with one a wave the 64^3 monitor (480 blocks of eight) took 24.0 instead
+// of 9.3 us.
 __device__ __forceinline__ void scalar_max(double* a, double v)
 {
     if (v > *(volatile double*)a)
@@ -1067,6 +1070,12 @@ __device__ __forceinline__ unsigned long long order_key(double v)
 __device__ __forceinline__ double order_value(unsigned long long k)
 {
     return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
+}
+
+__device__ __forceinline__ void scalar_min(unsigned long long* key, double v)
+{
+    const unsigned long long k = order_key(v);
+    if (k < *(volatile unsigned long long*)key) atomicMin(key, k);
 }
 
 // scal: the maxima [0..7] to 0, the limiter's key [8] to that of 1; the
@@ -1147,6 +1156,7 @@ k_monitor_grad3(Phys ph, Geo g, MonitorP mo, const double* __restrict__ JU, cons
 {
     constexpr int D = 3, TX = 30, TY = 14, HX = 32;
     __shared__ double Sg[2][512 + 2 * HX];   // (a row on either side, read and not used)
+    __shared__ double part[8][MON_CH];       // the waves' maxima
     const long P = g.P;
     const int np0 = g.np[0], np1 = g.np[1];
     int bx, by, bz;
@@ -1155,12 +1165,13 @@ k_monitor_grad3(Phys ph, Geo g, MonitorP mo, const double* __restrict__ JU, cons
     const int gx = bx * TX + lx - 1, gy = by * TY + ly - 1;
     const bool own = lx >= 1 && lx <= TX && ly >= 1 && ly <= TY && gx < g.n[0] && gy < g.n[1];
     const int zc0 = bz * zchunk, zc1 = min(zc0 + zchunk, g.n[2]);
+    if (zc0 >= zc1) return;   // uniform over the block
     // (a column beyond a ragged tile's halo reads the nearest one, which no written node uses)
     const long sz = (long)np0 * np1, col = (long)(min(gy, g.n[1]) + g.ng) * np0 + min(gx, g.n[0]) + g.ng;
     double ih[3];
 #pragma unroll
     for (int k = 0; k < 3; k++) ih[k] = 1.0 / (2.0 * g.dxi[k]);
-    for (int s = 0; s < mo.nsig && zc0 < zc1; s++) {   // uniform over the block
+    for (int s = 0; s < mo.nsig; s++) {
         const int sg = mo.sigma[s];
         auto sigma = [&](int z) { return sigma_of<N, D, SIG>(ph, JU, Jv, P, col + (z + g.ng) * sz, sg, mo.phi); };
         double sm = sigma(zc0 - 1), s0 = sigma(zc0);
@@ -1194,11 +1205,17 @@ k_monitor_grad3(Phys ph, Geo g, MonitorP mo, const double* __restrict__ JU, cons
             __syncthreads();
         }
         mg = wave_max(mg);
-        if ((t & 63) == 0) scalar_max(gmax + s, mg);
-        if (mo.form) {
-            ml = wave_max(ml);
-            if ((t & 63) == 0) scalar_max(gmax + mo.nsig + s, ml);
+        if (mo.form) ml = wave_max(ml);
+        if ((t & 63) == 0) {
+            part[t >> 6][s] = mg;
+            if (mo.form) part[t >> 6][mo.nsig + s] = ml;
         }
+    }
+    __syncthreads();
+    if (t < (mo.form ? 2 * mo.nsig : mo.nsig)) {
+        double m = part[0][t];
+        for (int q = 1; q < 8; q++) m = fmax(m, part[q][t]);
+        scalar_max(gmax + t, m);
     }
 }
 
@@ -1608,7 +1625,12 @@ k_jacobi2(Geo g, const double* __restrict__ th, const double* __restrict__ xa, d
     }
     if (xn) {
         b = wave_min(b);
-        if (lane == 0 && order_key(b) < *(volatile unsigned long long*)bound) atomicMin(bound, order_key(b));
+        if (lane == 0) part[wid] = b;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int q = 1; q < NT2 / 64; q++) b = fmin(b, part[q]);
+            scalar_min(bound, b);
+        }
     }
 }
 
@@ -1769,6 +1791,7 @@ k_jacobi3(Geo g, const double* __restrict__ th, const double* __restrict__ xa, d
     __shared__ double Ts[S + 1][HP];        // theta of the last planes
     __shared__ double Xs[S][2][3][HP];      // x before step s, two planes
     __shared__ double Ns[LIM ? S + 1 : 1][LIM ? HP : 1];   // x_n's second component
+    __shared__ double part[S + LIM][HN / 64];   // the waves' maxima and minima
     const long P = g.P;
     int bx, by, bz;
     xcd_tile((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, bx, by, bz);
@@ -1916,15 +1939,25 @@ k_jacobi3(Geo g, const double* __restrict__ th, const double* __restrict__ xa, d
             __syncthreads();
         }
     } while ((k0 += PF) < zc1 + S);
-    if (resid)
+    if (!LIM && !resid) return;
 #pragma unroll
-        for (int s = 0; s < S; s++) {
-            const double r = wave_max(res[s]);
-            if ((t & 63) == 0) scalar_max(resid + s, r);
-        }
+    for (int s = 0; s < S; s++) {
+        const double r = wave_max(res[s]);
+        if ((t & 63) == 0) part[s][t >> 6] = r;
+    }
     if constexpr (LIM) {
         lim = wave_min(lim);
-        if ((t & 63) == 0 && order_key(lim) < *(volatile unsigned long long*)bound) atomicMin(bound, order_key(lim));
+        if ((t & 63) == 0) part[S][t >> 6] = lim;
+    }
+    __syncthreads();
+    if (resid && t < S) {
+        double r = part[t][0];
+        for (int q = 1; q < HN / 64; q++) r = fmax(r, part[t][q]);
+        scalar_max(resid + t, r);
+    }
+    if (LIM && t == S) {
+        for (int q = 0; q < HN / 64; q++) lim = fmin(lim, part[S][q]);
+        scalar_min(bound, lim);
     }
 }
 

@@ -1,0 +1,87 @@
+"""The maxima, residuals and the movement limiter's bound that the 3D mesh step
+folds over its blocks: monitors of several channels (the Laplacian form, the
+pressure alone, six variables) for one and two species on grids across the
+monitor's and the sweeps' tile edges, against the oracle at the FP64 parity bar;
+and the time of a small mesh step, which is what these folds cost."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2202_07989_amd import inputs as I
+from gpu_util import TOL_FP64, dev, host, say
+
+pytestmark = pytest.mark.gpu
+
+MONITORS = {
+    "laplacian": dict(sigma=[0, 3], alpha=[20.0, 3.0], beta=[10.0, 1.0], form=1),
+    "pressure": dict(sigma=[3], alpha=[40.0]),
+    "six": dict(sigma=[5, 4, 3, 1, 0, 3], alpha=[6.0, 5.0, 12.0, 12.0, 12.0, 3.0], psi=[12.0, 2.0]),
+}
+
+
+def state(nspec, n):
+    kw = dict(gamma=(3.0, 1.4), cv=(1.0, 1.0), pinf=(100.0, 0.0)) if nspec == 2 else dict(gamma=(1.4,), cv=(1.0,), pinf=(0.0,))
+    sp = I.make_spec(3, nspec, n, chi=I.CHI_SHOCK, **kw)
+    rho, v, p = I.random_state(sp, 3, noise=0.2, p_range=(50.0, 200.0))
+    rng = np.random.default_rng(3)
+    x = [np.broadcast_to(xi, rho[0].shape) + 0.2 * sp["dxi"][k] * rng.uniform(-1, 1, size=rho[0].shape)
+         for k, xi in enumerate(I.xi_nodes(sp))]
+    JU, J, xp = I.assemble(sp, I.conserved(sp, rho, v, p), np.ones_like(rho[0]), x)
+    o = oracle.Oracle(sp)
+    o.fill_ghosts_state(JU, J)
+    o.fill_ghosts_x(xp)
+    return sp, o, JU, J, xp
+
+
+@pytest.mark.parametrize("monitor", list(MONITORS))
+@pytest.mark.parametrize("nspec", [1, 2])
+@pytest.mark.parametrize("n", [(30, 14, 4), (31, 15, 17), (61, 29, 9), (9, 43, 33)])
+@pytest.mark.parametrize("smooth,sweeps", [(1, 2), (2, 3)])
+def test_folded_scalars(monitor, nspec, n, smooth, sweeps):
+    say(f"[mesh scalars] {monitor} N={nspec} {n} smooth={smooth} sweeps={sweeps}")
+    sp, o, JU, J, x = state(nspec, n)
+    mon = dict(MONITORS[monitor], n_smooth=smooth, n_sweeps=sweeps)
+    rc, disp, tau, resid = o.mesh_redistribute(mon, JU, J, x)
+    assert rc == 0
+    from paper_2202_07989_amd import es
+    ctx = es.Context(sp)
+    h = min(sp["dxi"])
+    gU, gJ, gx = dev(JU), dev(J), dev(x)
+    for want in (True, False):
+        gd = torch.full_like(gx, float("nan"))
+        gt = torch.full((1,), float("nan"), dtype=torch.float64, device="cuda")
+        gr = torch.full((sweeps,), float("nan"), dtype=torch.float64, device="cuda")
+        ctx.mesh_redistribute(mon, gU, gJ, gx, gd, gt, gr if want else None)
+        assert np.abs(host(gd) - disp).max() <= TOL_FP64 * h
+        assert abs(float(host(gt)[0]) - tau) <= TOL_FP64
+        if want:
+            assert np.abs(host(gr) - resid).max() <= TOL_FP64 * h
+
+
+def test_small_mesh_step_time():
+    """A mesh step without filter passes and sweeps is four launches and the monitor's
+    maximum.  Both grids are far from filling the device, so 64^3 may take little
+    longer than 32^3: 1.2 times, against 2.1 with an atomic maximum by every wave of
+    the monitor, all on one address."""
+    best = {}
+    for n in (32, 64):
+        sp, o, JU, J, x = state(2, (n, n, n))
+        mon = dict(sigma=[0], alpha=[100.0], n_smooth=0, n_sweeps=0)
+        from paper_2202_07989_amd import es
+        ctx = es.Context(sp)
+        gU, gJ, gx = dev(JU), dev(J), dev(x)
+        gd, gt = torch.empty_like(gx), torch.empty(1, dtype=torch.float64, device="cuda")
+        times = []
+        for rep in range(12):
+            torch.cuda.synchronize()
+            a = time.perf_counter()
+            for _ in range(100):
+                ctx.mesh_redistribute(mon, gU, gJ, gx, gd, gt)
+            torch.cuda.synchronize()
+            times.append((time.perf_counter() - a) / 100)
+        best[n] = min(times[2:])
+        say(f"[mesh scalars] {n}^3 {1e6 * best[n]:.1f} us")
+    assert best[64] <= 1.65 * best[32], best
