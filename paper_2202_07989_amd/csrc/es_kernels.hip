@@ -400,7 +400,11 @@ __device__ __forceinline__ void buffer_store(double* base, unsigned bytes, unsig
 }
 constexpr unsigned DROPPED = 0xfffffff8u;
 
-// z chunks of nz planes for `cols` columns of blocks, `slots` blocks at a time:
+// compute units of the device
+constexpr int UNITS = 256;
+
+// z chunks of nz planes for `cols` columns of blocks, `slots` blocks at a time (the
+// launch's resident blocks a compute unit times the units):
 // the number that leaves the shortest walk (rounds of blocks times planes a
 // block), each walk taking `extra` planes more than it writes.  A block that has a
 // compute unit to itself walks faster, by a third at least (64^3 mesh step 100 us; with
@@ -409,7 +413,6 @@ constexpr unsigned DROPPED = 0xfffffff8u;
 // tenth longer (two Jacobi sweeps at 256^3: 8 chunks 280 us, 2 chunks 306)
 static int z_chunk(int nz, long cols, int extra, int slots)
 {
-    constexpr int UNITS = 256;
     double best = -1.0;
     int chunk = nz;
     // (past four rounds a shorter chunk only adds its extra planes)
@@ -752,7 +755,7 @@ hipError_t metrics(const Phys& ph, const Geo& g, const double* xn, const double*
     } else {
         constexpr int HX = 32, HY = 16;   // one block a compute unit
         const int gx = (g.n[0] + HX - 7) / (HX - 6), gy = (g.n[1] + HY - 7) / (HY - 6);
-        const int zc = z_chunk(g.n[2], (long)gx * gy, 6, 256);
+        const int zc = z_chunk(g.n[2], (long)gx * gy, 6, UNITS);
         hipLaunchKernelGGL((dx ? k_metric3<HX, HY, true> : k_metric3<HX, HY, false>), dim3(gx * gy * ((g.n[2] + zc - 1) / zc)), dim3(2 * HX * HY), 0, s, g, ph,
                            xn, dx, cs, disp, dt_dev, jxx, jxt, zc, reuse);
         if (reuse && jxt)
@@ -1778,9 +1781,13 @@ k_filter3(Geo g, MonitorP mo, const double* __restrict__ in, const double* __res
 
 // S Jacobi sweeps of the mesh equations (1 or 2); resid: their residuals; LIM (the
 // last launch of a call): also the movement limiter's bound against x_n, whose
-// planes walk along, into the ordered key `bound`
+// planes walk along, into the ordered key `bound`.  Two blocks share a compute unit,
+// but for two sweeps with the limiter: 81 KB and 146 registers a thread.  Within 128
+// registers and 73 KB (no rows between the planes) 25 registers spill and ten sweeps
+// at 256^3 take 2473 us, as it is 2153, and with the last two sweeps in launches of
+// their own 2082, but six then take 1763 instead of 1555 and two 1087 instead of 938.
 template <int TX, int TY, int S, bool LIM>
-__global__ void __launch_bounds__((Column3<TX, TY, S>::NT)) __attribute__((amdgpu_waves_per_eu(4, 8)))
+__global__ void __launch_bounds__((Column3<TX, TY, S>::NT)) __attribute__((amdgpu_waves_per_eu(S == 2 && LIM ? 2 : 4, 8)))
 k_jacobi3(Geo g, const double* __restrict__ th, const double* __restrict__ xa, double* __restrict__ xb,
           double* __restrict__ resid, const double* __restrict__ xn, unsigned long long* __restrict__ bound,
           int zchunk)
@@ -2013,17 +2020,18 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
                        grid_for(nint), s);
     // monitor and its global maxima (3D: three blocks a compute unit, two with the pressure)
     if (d3) {
-        const int jx = (g.n[0] + 29) / 30, jy = (g.n[1] + 13) / 14, zc = z_chunk(g.n[2], (long)jx * jy, 2, sigmode ? 512 : 768);
+        const int jx = (g.n[0] + 29) / 30, jy = (g.n[1] + 13) / 14, zc = z_chunk(g.n[2], (long)jx * jy, 2, (sigmode ? 2 : 3) * UNITS);
         hipLaunchKernelGGL(ph.nspec == 1 ? monitor3_kernel<1>(sigmode) : monitor3_kernel<2>(sigmode),
                            dim3(jx * jy * ((g.n[2] + zc - 1) / zc)), dim3(512), 0, s, ph, g, mo, JU, J, w.grad, w.scal, zc);
     } else {
         hipLaunchKernelGGL(ph.nspec == 1 ? monitor2_kernel<1>(sigmode) : monitor2_kernel<2>(sigmode), tiles2(g), dim3(256),
                            0, s, ph, g, mo, JU, J, w.grad, w.scal);
     }
-    // 3D launches over z chunks of tiles
-    auto march = [&](auto kern, int tx, int ty, int nt, int extra, auto... args) {
+    // 3D launches over z chunks of tiles of nt threads, `blocks` of them resident on a
+    // compute unit
+    auto march = [&](auto kern, int tx, int ty, int nt, int extra, int blocks, auto... args) {
         const int gx = (g.n[0] + tx - 1) / tx, gy = (g.n[1] + ty - 1) / ty;
-        const int zc = z_chunk(g.n[2], (long)gx * gy, extra, 512);
+        const int zc = z_chunk(g.n[2], (long)gx * gy, extra, blocks * UNITS);
         hipLaunchKernelGGL(kern, dim3(gx * gy * ((g.n[2] + zc - 1) / zc)), dim3(nt), 0, s, g, args..., zc);
     };
     // theta and the filter passes (none: theta alone)
@@ -2037,9 +2045,9 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
         } else if (steps == 0) {
             hipLaunchKernelGGL(k_theta, dim3(grid_for(nint)), dim3(256), 0, s, g, mo, in, gmax, th2);
         } else {
-            if (steps == 1) march(k_filter3<30, 20, 1>, 30, 20, 704, 3, mo, in, gmax, th2);
-            else if (steps == 2) march(k_filter3<28, 18, 2>, 28, 18, 704, 6, mo, in, gmax, th2);
-            else march(k_filter3<26, 16, 3>, 26, 16, 704, 9, mo, in, gmax, th2);
+            if (steps == 1) march(k_filter3<30, 20, 1>, 30, 20, 704, 3, 2, mo, in, gmax, th2);
+            else if (steps == 2) march(k_filter3<28, 18, 2>, 28, 18, 704, 6, 2, mo, in, gmax, th2);
+            else march(k_filter3<26, 16, 3>, 26, 16, 704, 9, 2, mo, in, gmax, th2);
         }
         std::swap(th, th2);
         left -= steps;
@@ -2056,11 +2064,10 @@ hipError_t mesh_redistribute(const Phys& ph, const Geo& g, const MonitorP& mo_in
         if (!d3) {
             hipLaunchKernelGGL(k_jacobi2, tiles2(g), dim3(NT2), 0, s, g, th, xcur, xa, steps, res, xl, key);
         } else {
-            // (blocks of 512 threads)
-            if (steps == 1 && xl) march(k_jacobi3<30, 14, 1, true>, 30, 14, 512, 2, th, xcur, xa, res, xl, key);
-            else if (steps == 1) march(k_jacobi3<30, 14, 1, false>, 30, 14, 512, 2, th, xcur, xa, res, xl, key);
-            else if (xl) march(k_jacobi3<28, 12, 2, true>, 28, 12, 512, 4, th, xcur, xa, res, xl, key);
-            else march(k_jacobi3<28, 12, 2, false>, 28, 12, 512, 4, th, xcur, xa, res, xl, key);
+            if (steps == 1 && xl) march(k_jacobi3<30, 14, 1, true>, 30, 14, 512, 2, 2, th, xcur, xa, res, xl, key);
+            else if (steps == 1) march(k_jacobi3<30, 14, 1, false>, 30, 14, 512, 2, 2, th, xcur, xa, res, xl, key);
+            else if (xl) march(k_jacobi3<28, 12, 2, true>, 28, 12, 512, 4, 1, th, xcur, xa, res, xl, key);
+            else march(k_jacobi3<28, 12, 2, false>, 28, 12, 512, 4, 2, th, xcur, xa, res, xl, key);
         }
         xcur = xa;
         std::swap(xa, xb);
