@@ -46,7 +46,7 @@ k_stage2d_batched(Phys ph, const Geo* __restrict__ geos, const int4* __restrict_
         double qs[NH], qn[NH];
         bad |= xy_tile<N, D, TX, TY, NT, R, RC, 2>(
             ph, S, My, in, ox, oy, base, g.idxi[0], g.idxi[1], w,
-            [&](int i, int cc, bool, long gn) {
+            [&](int i, int cc, long gn) {
                 const bool isJ = cc == NC;
                 qs[i] = (isJ ? in.J : in.JU + cc * P)[gn];
                 // stage 0 has ca = 0: Q_s stands in for the state at t^n, which is not read

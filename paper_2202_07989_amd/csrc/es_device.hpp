@@ -19,7 +19,7 @@ struct Phys {
     double pinf_tot;
     double alpha[3];          // alpha_{w,m}
     double chi[3], eps;       // MR-WENO linear weights and epsilon
-    double wc[4];             // chi_2/6, chi_2/3, 11/60 - chi_2/6, 2/5 - chi_2/3 (mr5_jump64)
+    double wc[4];             // chi_2/6, chi_2/3, 11/60 - chi_2/6, 2/5 - chi_2/3 (mr5_side64)
     double r21;               // R_2 / R_1 (N = 2)
     double sr21, isr21;       // sqrt(R_2 / R_1) and its reciprocal
     double isa, ise;          // N = 1: 1/(2 Gamma R) and 1/(c_v Gamma), the scalings of R's columns
@@ -593,13 +593,12 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-enum RedOp { RED_MAX = 0, RED_MIN = 1, RED_SUM = 2 };
+enum RedOp { RED_MAX = 0, RED_SUM = 1 };
 
 template <int OP>
 __device__ __forceinline__ double red_combine(double a, double b)
 {
     if constexpr (OP == RED_MAX) return fmax(a, b);
-    else if constexpr (OP == RED_MIN) return fmin(a, b);
     else return a + b;
 }
 
@@ -610,7 +609,6 @@ __device__ __forceinline__ double block_reduce(double v)
     __shared__ double part[4];
     double w;
     if constexpr (OP == RED_MAX) w = wave_max(v);
-    else if constexpr (OP == RED_MIN) w = wave_min(v);
     else w = wave_sum(v);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     if (lane == 0) part[wid] = w;

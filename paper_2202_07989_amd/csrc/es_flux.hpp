@@ -842,10 +842,6 @@ __device__ __forceinline__ void dissipation64(const Phys& ph, const NodeTile<N, 
     Dout[NC - 1] = hs * En;
 }
 
-struct NoPre {
-    __device__ __forceinline__ void operator()() const {}
-};
-
 // two-point EC flux in the precision of the sweep
 template <int N, int D, int NN, typename R>
 __device__ __forceinline__ void two_point(const Phys& ph, const NodeTile<N, D, NN, R>& S, const double (*M)[NN],
@@ -877,18 +873,19 @@ __device__ __forceinline__ void two_point(const Phys& ph, const NodeTile<N, D, N
 // of slot s of line c, line_ok(c) whether line c exists; f_ok says that
 // this thread's interface (fi, fc) exists and its six nodes are loaded.
 // RC selects the reconstruction of the dissipation (0: multi-resolution
-// WENO, 1: classical WENO5).  With XALIAS, X overlays the node quantities of S (all but the metrics):
+// WENO, 1: classical WENO5).  X overlays the node quantities of S (all but the metrics):
 // every flux is then formed in registers first and X is written only after
 // a barrier that ends all node reads.  Every thread of the block must call
 // this (it holds barriers).
-// (MG: the dissipation's acoustic and species fields in one group or two;
-// two in FP64, where they keep the sweeps within fewer registers)
+// (MG: the FP32 dissipation's acoustic and species fields in one group or two;
+// the FP64 one takes them apart in any case)
 // interface_fluxes_m is the general form: the metrics M of the direction
 // are passed in, X rows are XS slots long, and the tile's TL and TC may be
 // run-time values (a block that sweeps two directions at once picks them per
 // wave), and pre() runs between the fluxes and the exchange (loads that the
-// caller wants in flight through the latter); interface_fluxes takes the tile's own metrics and fixed sizes.
-template <int N, int D, int NN, int XS, bool XALIAS, int RC, typename R, int MG, typename LI, typename XI,
+// caller wants in flight through the latter); interface_fluxes takes the tile's own metrics, fixed sizes and
+// one group.
+template <int N, int D, int NN, int XS, int RC, typename R, int MG, typename LI, typename XI,
           typename LOK, typename PRE>
 __device__ __forceinline__ void interface_fluxes_m(const Phys& ph, const NodeTile<N, D, NN, R>& S,
                                                    const double (*M)[NN], R (*X)[XS], LI lidx, XI xidx,
@@ -971,7 +968,7 @@ __device__ __forceinline__ void interface_fluxes_m(const Phys& ph, const NodeTil
         for (int cc = 0; cc < NC; cc++) Bh[cc] = am * Bh[cc];
     }
     pre();
-    if constexpr (XALIAS) __syncthreads();   // node reads end before X overwrites them
+    __syncthreads();   // node reads end before X overwrites them
     if (halo) {
 #pragma unroll
         for (int cc = 0; cc < NC; cc++) X[cc][xidx(hslot, hc)] = Bh[cc];
@@ -1013,15 +1010,13 @@ __device__ __forceinline__ void interface_fluxes_m(const Phys& ph, const NodeTil
     __syncthreads();
 }
 
-template <int N, int D, int NN, int TL, int TC, bool XALIAS, int RC, typename R,
-          int MG = (sizeof(R) == 8 ? 2 : 1), typename LI, typename XI, typename LOK, typename PRE = NoPre>
+template <int N, int D, int NN, int TL, int TC, int RC, typename R, typename LI, typename XI, typename LOK>
 __device__ __forceinline__ void interface_fluxes(const Phys& ph, const NodeTile<N, D, NN, R>& S,
                                                  R (*X)[(TL + 4) * TC], LI lidx, XI xidx,
-                                                 LOK line_ok, int fi, int fc, bool f_ok, int hid,
-                                                 PRE pre = PRE())
+                                                 LOK line_ok, int fi, int fc, bool f_ok, int hid)
 {
-    interface_fluxes_m<N, D, NN, (TL + 4) * TC, XALIAS, RC, R, MG>(ph, S, S.m, X, lidx, xidx, line_ok, fi, fc,
-                                                                  f_ok, hid, TL, TC, pre);
+    interface_fluxes_m<N, D, NN, (TL + 4) * TC, RC, R, 1>(ph, S, S.m, X, lidx, xidx, line_ok, fi, fc, f_ok, hid,
+                                                          TL, TC, [] {});
 }
 
 // J U and J of one node as loaded

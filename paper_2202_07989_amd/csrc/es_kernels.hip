@@ -774,26 +774,16 @@ hipError_t metrics(const Phys& ph, const Geo& g, const double* xn, const double*
 // ---------------------------------------------------------------------------
 static constexpr int RED_BLOCKS = 2048;
 
+// (the maximum is lambda: out[1] = a / lambda with a = cfl; the sum is scaled by a)
 template <int OP>
-__global__ void k_finish(const double* __restrict__ part, int nparts, double* __restrict__ out,
-                         int mode, double a, unsigned* status)
+__global__ void k_finish(const double* __restrict__ part, int nparts, double* __restrict__ out, double a)
 {
-    double v = (OP == RED_MAX) ? -INFINITY : (OP == RED_MIN ? INFINITY : 0.0);
+    double v = OP == RED_MAX ? -INFINITY : 0.0;
     for (int t = threadIdx.x; t < nparts; t += blockDim.x) v = red_combine<OP>(v, part[t]);
     v = block_reduce<OP>(v);
     if (threadIdx.x == 0) {
-        if (mode == 0) {
-            out[0] = v;
-        } else if (mode == 1) {           // CFL: out[0] = lambda, out[1] = cfl / lambda
-            out[0] = v;
-            out[1] = a / v;
-        } else if (mode == 2) {           // limiter: Delta_tau = min(1, v)
-            const double d = fmin(1.0, v);
-            out[0] = d;
-            if (!(d > 0.0)) atomicOr(status, 2u);
-        } else {                          // scaled sum
-            out[0] = v * a;
-        }
+        out[0] = OP == RED_MAX ? v : v * a;
+        if (OP == RED_MAX) out[1] = a / v;
     }
 }
 
@@ -945,7 +935,7 @@ hipError_t wavespeed(const Phys& ph, const Geo& g, const double* JU, const doubl
     const long nint = (long)g.n[0] * g.n[1] * (g.dim == 3 ? g.n[2] : 1);
     const int nb = red_grid(nint);
     ES_DISPATCH_ND(ph, g, launch_wavespeed, ph, g, JU, J, jxx, part, status, nb, s);
-    hipLaunchKernelGGL(k_finish<RED_MAX>, dim3(1), dim3(256), 0, s, part, nb, out2, 1, cfl, status);
+    hipLaunchKernelGGL(k_finish<RED_MAX>, dim3(1), dim3(256), 0, s, part, nb, out2, cfl);
     return hipGetLastError();
 }
 
@@ -1045,7 +1035,7 @@ hipError_t entropy_sum(const Phys& ph, const Geo& g, const double* JU, const dou
     double dv = 1.0;
     for (int k = 0; k < g.dim; k++) dv *= g.dxi[k];
     ES_DISPATCH_ND(ph, g, launch_entropy, ph, g, JU, J, dJU, dJ, part, nb, s);
-    hipLaunchKernelGGL(k_finish<RED_SUM>, dim3(1), dim3(256), 0, s, part, nb, out, 3, dv, nullptr);
+    hipLaunchKernelGGL(k_finish<RED_SUM>, dim3(1), dim3(256), 0, s, part, nb, out, dv);
     return hipGetLastError();
 }
 

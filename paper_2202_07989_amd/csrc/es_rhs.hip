@@ -117,7 +117,7 @@ k_rhs_z(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict_
     const int fc = t % TC;
     // node fi + 5 must be inside the padded grid (ragged last segment)
     const bool f_ok = (t < NI) && (line0 + fc < nlines) && (g.ng + seg0 + fi + 2 < g.np[K]);
-    interface_fluxes<N, D, NN, TL, TC, true, RC, R>(ph, S, X, lidx, xidx,
+    interface_fluxes<N, D, NN, TL, TC, RC, R>(ph, S, X, lidx, xidx,
                                           [&](int c) { return line0 + c < nlines; }, fi, fc, f_ok,
                                           t - (int)(blockIdx.x & 3) * 64);
 
@@ -169,7 +169,7 @@ k_rhs_xy(Phys ph, Geo g, const double* __restrict__ JU, const double* __restrict
     const double dt = MODE == MODE_RK ? *rk.dt : 0.0;
     const unsigned bad = xy_tile<N, D, TX, TY, 512, R, RC, MG>(
         ph, S, My, in, ox, oy, base, g.idxi[0], g.idxi[1], (int)blockIdx.x,
-        [&](int i, int cc, bool, long gn) {
+        [&](int i, int cc, long gn) {
             const bool isJ = cc == NC;
             if constexpr (ACC) ac[i] = (isJ ? accJ : accU + cc * P)[gn];
             if constexpr (MODE == MODE_RK) {

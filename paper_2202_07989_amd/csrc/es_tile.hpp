@@ -24,9 +24,9 @@ struct PlaneIn {
 // columns at the same time, each with the interface scheme of
 // interface_fluxes.  A node's term is the x difference plus the y difference,
 // each rounded on its own.  Each half of the block writes half of the
-// components (J U, then J) of the tile's nodes: fetch(i, cc, own, gn) runs before
-// the exchange (component cc of padded node gn, the thread's i-th; own: the
-// node exists) and out(i, cc, gn, ni, nj, term) writes.  rot spreads the pairs
+// components (J U, then J) of the tile's nodes: fetch(i, cc, gn) runs before the
+// exchange (component cc of padded node gn, the thread's i-th) and
+// out(i, cc, gn, ni, nj, term) writes.  rot spreads the pairs
 // left of a line's first interface over the waves.  Bound by FP64 issue and by
 // the waits of a block's phases; two blocks of 512 threads (70 KB, 123
 // registers for two species in 3D) share a compute unit.  Returns the status
@@ -117,12 +117,12 @@ __device__ __forceinline__ unsigned xy_tile(const Phys& ph, NodeTile<N, D, NN, R
     const int ni = u % TX, nj = u / TX, c0 = ydir ? NH : 0;
     const bool own = u < TX * TY && ox + ni < in.nx && oy + nj < in.ny;
     const long gn = own ? base + (long)(nj + 3) * np0 + (ni + 3) : base + 3L * np0 + 3;
-    interface_fluxes_m<N, D, NN, XS, true, RC, R, MG>(
+    interface_fluxes_m<N, D, NN, XS, RC, R, MG>(
         ph, S, ydir ? My : S.m, ydir ? Xb + NC : Xb, [=](int l, int c) { return l0 + l * sl + c * sc; },
         [=](int s, int c) { return s * xl + c * xc; }, [=](int c) { return o_line + c < n_line; }, fi, fc,
         f_ok, u - (rot % (NT / 128)) * 64, TL, TC, [&] {
 #pragma unroll
-            for (int i = 0; i < NH; i++) fetch(i, c0 + i < NC ? c0 + i : NC, own, gn);
+            for (int i = 0; i < NH; i++) fetch(i, c0 + i < NC ? c0 + i : NC, gn);
         });
 
     // ---- node outputs ------------------------------------------------------
