@@ -2,7 +2,8 @@
 folds over its blocks: monitors of several channels (the Laplacian form, the
 pressure alone, six variables) for one and two species on grids across the
 monitor's and the sweeps' tile edges, against the oracle at the FP64 parity bar;
-and the time of a small mesh step, which is what these folds cost."""
+the time of a small mesh step, which is what these folds cost; and the calls without
+residuals, 2D and 3D, on outputs that hold NaN before each call."""
 import time
 
 import numpy as np
@@ -59,6 +60,44 @@ def test_folded_scalars(monitor, nspec, n, smooth, sweeps):
         assert abs(float(host(gt)[0]) - tau) <= TOL_FP64
         if want:
             assert np.abs(host(gr) - resid).max() <= TOL_FP64 * h
+
+
+PER, REF, OUT, INF = I.BC_PERIODIC, I.BC_REFLECT, I.BC_OUTFLOW, I.BC_INFLOW
+
+
+@pytest.mark.parametrize("n", [(3, 3), (33, 17), (65, 40), (3, 3, 3), (31, 15, 17), (27, 33, 6)])
+@pytest.mark.parametrize("walled", [False, True])
+@pytest.mark.parametrize("smooth,sweeps", [(0, 0), (0, 1), (1, 2), (4, 5), (6, 6)])
+def test_without_residuals(n, walled, smooth, sweeps):
+    """Every node written by the call that takes no residuals (a whole step's), and to
+    the bit what the other writes."""
+    say(f"[mesh scalars] no residuals {n} walled={walled} smooth={smooth} sweeps={sweeps}")
+    dim = len(n)
+    bc = [(OUT, INF)] + [(REF, REF)] * (dim - 1) if walled else None
+    sp = I.make_spec(dim, 2, n, chi=I.CHI_SHOCK, gamma=(3.0, 1.4), cv=(1.0, 1.0), pinf=(100.0, 0.0), bc=bc,
+                     wall=[(0.0, 1.0)] * dim if walled else None)
+    if walled:
+        sp["inflow"] = {(0, 1): [1.0, 0.5] + [-0.3, 0.1, 0.2][:dim] + [400.0]}
+    JU, J, x = I.init_random(sp, seed=5, noise=0.2, mesh_amp=0.0 if walled else 0.02, p_range=(50.0, 200.0))
+    o = oracle.Oracle(sp)
+    o.fill_ghosts_state(JU, J)
+    o.fill_ghosts_x(x)
+    mon = dict(sigma=[0, 3], alpha=[60.0, 20.0], n_smooth=smooth, n_sweeps=sweeps)
+    rc, disp, tau, resid = o.mesh_redistribute(mon, JU, J, x)
+    assert rc == 0
+    from paper_2202_07989_amd import es
+    ctx = es.Context(sp)
+    gU, gJ, gx = dev(JU), dev(J), dev(x)
+    got = []
+    for want in (False, True):
+        gd = torch.full_like(gx, float("nan"))
+        gt = torch.full((1,), float("nan"), dtype=torch.float64, device="cuda")
+        gr = torch.full((max(1, sweeps),), float("nan"), dtype=torch.float64, device="cuda")
+        ctx.mesh_redistribute(mon, gU, gJ, gx, gd, gt, gr if want and sweeps else None)
+        assert np.abs(host(gd) - disp).max() <= TOL_FP64 * min(sp["dxi"][:dim])
+        assert abs(float(host(gt)[0]) - tau) <= TOL_FP64
+        got.append((gd, gt))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
 
 
 def test_small_mesh_step_time():
