@@ -335,7 +335,7 @@ __device__ __forceinline__ R mr5_jump(R q0, R q1, R q2, R q3, R q4, R q5, const 
 //   89/320 (S03 - 307/267 S12)^2 + 781/3204 S12^2,
 //   4405/4032 (A03 + 67923/22025 A21)^2 + 1421461/1321500 A21^2,
 // whose last ones beta_2 has too.  41 instructions a side (48 by the Legendre
-// coefficients: 512^2 stage 32.3 us, now 31.4; 256^3 stage 2766, now 2731).
+// coefficients: 512^2 stage 32.2 us, now 31.3; 256^3 stage 2807, now 2769).
 __device__ __forceinline__ void mr5_side64(double D0, double D1, double D2, double D3, double q1, double q2,
                                            const Phys& ph, double& num, double& den)
 {

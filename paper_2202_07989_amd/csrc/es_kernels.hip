@@ -1141,7 +1141,7 @@ __device__ __forceinline__ double lane_above(double v) { return lane_shift<0x130
 // one-node halo (a row is 32 lanes).  A variable is evaluated once per node of
 // the patch, 1.2 times per owned node; its neighbours along x are the
 // neighbouring lanes', along y in LDS (two planes), along z the thread's own
-// (256^3, density: 170 us; 64 x 4 columns with all neighbours in LDS 205).
+// (256^3, density: 160 us; 64 x 4 columns with all neighbours in LDS 205).
 template <int N, int SIG>
 __global__ void __launch_bounds__(512)
 k_monitor_grad3(Phys ph, Geo g, MonitorP mo, const double* __restrict__ JU, const double* __restrict__ Jv,
@@ -1331,8 +1331,10 @@ __device__ __forceinline__ double limit(double lim, double xm, double x0, double
 // nodes outside the grid are read through the face rules and updated like
 // any other, which the updates commute with, so no launch needs or writes the
 // ghost layers of Theta or of the moving mesh.  800 x 160, five-variable
-// monitor, 3 filter passes, 10 Jacobi sweeps: 8 launches instead of 29, 54
-// instead of 137 us.  A launch's loads are all issued before the first is used.
+// monitor, 3 filter passes, 10 Jacobi sweeps: 8 launches instead of 29, 52
+// instead of 140 us.  A launch's loads are all issued before the first is used.
+// The tile fills the device at that size (250 blocks) and leaves more than half of
+// it idle at 350 x 150 (110); no other tile has been measured.
 // ---------------------------------------------------------------------------
 constexpr int TX2 = 32, TY2 = 16, STEPS2 = 5;
 constexpr int RX2 = TX2 + 2 * STEPS2, RY2 = TY2 + 2 * STEPS2;
@@ -1669,7 +1671,7 @@ __global__ void k_disp(Geo g, const double* __restrict__ xmu, const double* __re
 }
 
 // ---------------------------------------------------------------------------
-// 3D: bound by HBM (two Jacobi sweeps move 1.33 GB at 4.4 TB/s), so several filter
+// 3D: bound by HBM (two Jacobi sweeps move 1.25 GB at 4.4 TB/s), so several filter
 // passes or Jacobi sweeps walk z together; three sweeps leave one block a
 // compute unit and half of its columns halo, 3 + 2 sweeps took 73 us more than
 // 2 + 2 + 1.  A block owns TX x TY columns over a chunk of z planes; every thread owns one
@@ -1772,7 +1774,7 @@ k_filter3(Geo g, MonitorP mo, const double* __restrict__ in, const double* __res
 // S Jacobi sweeps of the mesh equations (1 or 2); resid: their residuals; LIM (the
 // last launch of a call): also the movement limiter's bound against x_n, whose
 // planes walk along, into the ordered key `bound`.  Two blocks share a compute unit,
-// but for two sweeps with the limiter: 81 KB and 146 registers a thread.  Within 128
+// but for two sweeps with the limiter: 81 KB and 144 registers a thread.  Within 128
 // registers and 73 KB (no rows between the planes) 25 registers spill and ten sweeps
 // at 256^3 take 2473 us, as it is 2153, and with the last two sweeps in launches of
 // their own 2082, but six then take 1763 instead of 1555 and two 1087 instead of 938.

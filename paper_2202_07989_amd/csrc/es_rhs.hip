@@ -5,7 +5,7 @@
 // which writes its term, and then k_rhs_xy, which adds the x and y terms and
 // applies the stage combination: the z sweep is bound by HBM (its halo along
 // z is read again by every tile), the x-y launch by FP64 issue, so the operands
-// of the combination are read beside the latter (2.78 against 2.99 ms a stage
+// of the combination are read beside the latter (2.84 against 3.11 ms a stage
 // at 256^3 with the combination in the z sweep).  Every block stages node
 // quantities in LDS and builds the full numerical flux at its interfaces, one
 // thread per interface:
@@ -22,8 +22,8 @@ namespace es {
 
 // The z sweep.  A block of 256 threads owns TL nodes along z on TC lines of
 // consecutive x (16 on 15: 255 interfaces, rows of 120 bytes) plus a 3-node
-// halo along z.  What bounds it: HBM (5.9 GB in 1.2 ms at 256^3 with the stage
-// combination here, 3.4 GB in 0.95 ms without) and the latency of its loads
+// halo along z.  What bounds it: HBM (5.4 GB in 1.2 ms at 256^3 with the stage
+// combination here, 3.1 GB in 0.89 ms without) and the latency of its loads
 // and barriers, hidden by four blocks a compute unit (39.7 KB of LDS, 118
 // registers for two species).  Waves per SIMD: four in FP64, three in FP32
 // (one field group: splitting it costs more than a fourth wave gains).
