@@ -201,8 +201,8 @@ int es_rhs(es_ctx *c, const double *JU, const double *J, const double *jxi_x,
 /* Section 5, SSP-RK3 (Shu-Osher form) stage s = 0, 1, 2 on Q = (JU, J):
  *   Q_out = a_s Q_n + b_s (Q_s + dt L(Q_s)), (a, b) = (0, 1), (3/4, 1/4),
  *   (1/3, 2/3), fused with the right-hand side.  dt is read from dt_dev.
- *   Q_out accumulates the direction sweeps, so it must alias neither Q_s
- *   nor Q_n (ES_EINVAL). */
+ *   Q_out holds the z term between the two launches of a 3D stage, so it must
+ *   alias neither Q_s nor Q_n (ES_EINVAL; the same in 2D). */
 int es_rk_stage(es_ctx *c, int stage, const double *dt_dev,
                 const double *JU_n, const double *J_n,
                 const double *JU_s, const double *J_s,

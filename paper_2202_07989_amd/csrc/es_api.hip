@@ -417,7 +417,7 @@ int es_step(es_ctx* c, const es_monitor* m, double cfl, double dt_fixed, int mov
     static const double B[3] = {1.0, 1.0 / 4.0, 2.0 / 3.0};
     static const double Cs[3] = {0.0, 1.0, 0.5};
     // Q_n is the caller's (JU, J) itself: stages 0 and 1 only read it, and
-    // stage 2 accumulates its direction sweeps in bufA (free by then) and
+    // stage 2 keeps its z term (3D) in bufA (free by then) and
     // writes Q_{n+1} over Q_n, each node by the thread that read its Q_n
     const double* inU = JU;
     const double* inJ = J;
